@@ -432,12 +432,12 @@ __device__ __forceinline__ size_t patch_offset(int py, int px, int N) {
     return (size_t)(py >> lgL) * T + ((px >> lgP) << 6) + (px & ((1 << lgP) - 1)) + ((py & ((1 << lgL) - 1)) << lgP);
 }
 
-// Object gradient: each workgroup owns a 32 x 32 tile of one slice and sums,
-// in batch order, the patch gradients of every (position, mode) of batch rows
-// [j0, j1) covering it;
-// then applies the chain rule to amplitude and phase (O = a exp(i phase)):
+// Object gradient: each workgroup owns a tile of one slice, 32 columns by
+// 8 ROWS rows, and sums, in batch order, the patch gradients of every
+// (position, mode) of batch rows [j0, j1) covering it; then applies the chain
+// rule to amplitude and phase (O = a exp(i phase)):
 //   g_a += Re(conj(G) exp(i phase)),  g_phase += Im(G conj(O)).
-// A thread owns one column of the tile and four rows 8 apart, so each load
+// A thread owns one column of the tile and ROWS rows 8 apart, so each load
 // instruction reads two whole 256-byte tile rows of a patch; the loads of MB
 // consecutive (position, mode) items are issued together before they are
 // added (in item order), to keep enough bytes in flight per workgroup.  FUSE: the
@@ -447,83 +447,105 @@ __device__ __forceinline__ size_t patch_offset(int py, int px, int N) {
 // cleared, as each step's first scatter writes before the fused one reads.
 // MB: 8 when the probe modes come in eights, else 4 (fewer registers, more
 // resident workgroups).
-template <bool FUSE, int SCATTER_MB>
+// The rows that cover the tile are found 64 at a time, lane k of each wave
+// testing one row; the ballot is then walked bit by bit (batch order) and the
+// row's corner read from its lane.  Walking the rows' PosInfo one after the
+// other, a dependent memory read per batch row, bounded small launches: the
+// 20-row, 144 x 144 single-slice step 74.7 -> 64.7 us with 8-row tiles (this
+// kernel 18.7 us before); 64-row, 12 x 640 x 640 steps unchanged (bandwidth).
+// ROWS: 4, or 1 where the larger tile leaves compute units without work (see
+// scatter_rows).
+template <bool FUSE, int SCATTER_MB, int ROWS>
 __global__ __launch_bounds__(256) void k_scatter_object(const float2* gO, const PosInfo* pinfo, int j0, int j1, int M,
                                                         int Mc, int S, int N, int H, int W, const float* amp,
                                                         const float* phase, const double* scale, float* g_amp,
                                                         float* g_phase, ObjAdam ad, float sp) {
+    constexpr int TH = 8 * ROWS;
+    const int lane = threadIdx.x % 64;
     const int ntx = (W + 31) / 32;
     // blockIdx.y = o S + s: object mode o, slice s; patch-gradient entries o M .. o M + M - 1 of a
     // position (Mc per position: one per chain, or one per group of probe modes at N = 256)
     const int tile = blockIdx.x, s = blockIdx.y % S, om = (blockIdx.y / S) * M;
-    const int y0 = (tile / ntx) * 32, x0 = (tile % ntx) * 32;
+    const int y0 = (tile / ntx) * TH, x0 = (tile % ntx) * 32;
     const int x = x0 + (int)threadIdx.x % 32, yb = y0 + (int)threadIdx.x / 32;
-    float2 acc[4];
+    float2 acc[ROWS];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] = make_float2(0.f, 0.f);
+    for (int i = 0; i < ROWS; ++i) acc[i] = make_float2(0.f, 0.f);
     bool touched = false;
-    int cnt[4] = {0, 0, 0, 0};                 // patches covering the pixel (sparsity term)
+    int cnt[ROWS] = {};                        // patches covering the pixel (sparsity term)
     const size_t NN = (size_t)N * N;
-    // Work items are the (row, mode) pairs of the rows whose patch covers the
-    // tile, in row then mode order; SCATTER_MB consecutive items are loaded
-    // together, so with few modes the loads of several rows are in flight.
-    // The cursor (jc, mc) is the same for the whole workgroup; jc == j1 once
-    // no item is left.
-    int jc = j0 - 1, mc = M - 1;
-    PosInfo pc = {0, 0, 0.f, 0.f, 0, {0, 0, 0}};
-    auto advance = [&]() {
-        if (++mc < M) return;
-        mc = 0;
-        for (++jc; jc < j1; ++jc) {
-            pc = pinfo[jc];
-            if (pc.ty < 0) continue;
-            if (pc.ty >= y0 + 32 || pc.ty + N <= y0 || pc.tx >= x0 + 32 || pc.tx + N <= x0) continue;
-            touched = true;
-            if (sp != 0.f) {
-                const int px = x - pc.tx;
-                const bool xin = px >= 0 && px < N;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int py = yb + 8 * i - pc.ty;
-                    cnt[i] += (xin && py >= 0 && py < N) ? 1 : 0;
-                }
-            }
-            return;
-        }
+    auto covers = [&](int ty, int tx) {
+        return ty >= 0 && ty < y0 + TH && ty + N > y0 && tx < x0 + 32 && tx + N > x0;
     };
-    advance();
     // FUSE with gin: whether the assigning scatter of rows [0, j0) wrote this tile
     bool pre = false;
     if (FUSE && ad.gin)
-        for (int j = 0; j < j0 && !pre; ++j) {
-            const int ty = pinfo[j].ty, tx = pinfo[j].tx;
-            pre = ty >= 0 && ty < y0 + 32 && ty + N > y0 && tx < x0 + 32 && tx + N > x0;
+        for (int jb = 0; jb < j0 && !pre; jb += 64) {
+            const int j = jb + lane;
+            pre = __ballot(j < j0 && covers(pinfo[j].ty, pinfo[j].tx)) != 0;
         }
-    while (jc < j1) {
-        float2 buf[SCATTER_MB][4];
+    for (int jb = j0; jb < j1; jb += 64) {
+        const int j = jb + lane;
+        int ty = -1, tx = 0;
+        if (j < j1) {
+            ty = pinfo[j].ty;
+            tx = pinfo[j].tx;
+        }
+        unsigned long long left = __ballot(covers(ty, tx));          // rows still to take, in batch order
+        touched = touched || left != 0;
+        if (sp != 0.f)
+            for (unsigned long long m = left; m; m &= m - 1) {
+                const int k = __builtin_ctzll(m);
+                const int px = x - __builtin_amdgcn_readlane(tx, k), pty = __builtin_amdgcn_readlane(ty, k);
+                const bool xin = px >= 0 && px < N;
 #pragma unroll
-        for (int mm = 0; mm < SCATTER_MB; ++mm) {
-            const bool live = jc < j1;
-            const int px = x - pc.tx;
-            const bool xin = live && px >= 0 && px < N;
-            const float2* src = gO + ((size_t)(jc * Mc + om + mc) * S + s) * NN;   // read only when xin
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int py = yb + 8 * i - pc.ty;
-                const bool in = xin && py >= 0 && py < N;
-                buf[mm][i] = in ? src[patch_offset(py, px, N)] : make_float2(0.f, 0.f);
+                for (int i = 0; i < ROWS; ++i) {
+                    const int py = yb + 8 * i - pty;
+                    cnt[i] += (xin && py >= 0 && py < N) ? 1 : 0;
+                }
             }
-            if (live) advance();
+        // Work items are the (row, mode) pairs of the covering rows, in row then
+        // mode order; SCATTER_MB consecutive items are loaded together, so
+        // with few modes the loads of several rows are in flight.  The cursor
+        // (row, mc) is the same for the whole workgroup.
+        int mc = 0, pty = 0, ptx = 0, jc = 0;
+        auto row = [&]() {
+            const int k = left ? __builtin_ctzll(left) : 0;
+            pty = __builtin_amdgcn_readlane(ty, k);
+            ptx = __builtin_amdgcn_readlane(tx, k);
+            jc = jb + k;
+        };
+        row();
+        while (left) {
+            float2 buf[SCATTER_MB][ROWS];
+#pragma unroll
+            for (int mm = 0; mm < SCATTER_MB; ++mm) {
+                const bool live = left != 0;
+                const int px = x - ptx;
+                const bool xin = live && px >= 0 && px < N;
+                const float2* src = gO + ((size_t)(jc * Mc + om + mc) * S + s) * NN;   // read only when xin
+#pragma unroll
+                for (int i = 0; i < ROWS; ++i) {
+                    const int py = yb + 8 * i - pty;
+                    const bool in = xin && py >= 0 && py < N;
+                    buf[mm][i] = in ? src[patch_offset(py, px, N)] : make_float2(0.f, 0.f);
+                }
+                if (++mc == M) {
+                    mc = 0;
+                    left &= left - 1;
+                    row();
+                }
+            }
+#pragma unroll
+            for (int mm = 0; mm < SCATTER_MB; ++mm)
+#pragma unroll
+                for (int i = 0; i < ROWS; ++i) acc[i] = cadd(acc[i], buf[mm][i]);
         }
-#pragma unroll
-        for (int mm = 0; mm < SCATTER_MB; ++mm)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i] = cadd(acc[i], buf[mm][i]);
     }
     if ((!FUSE && !touched) || x >= W) return;
     const float sc = (float)*scale;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < ROWS; ++i) {
         const int y = yb + 8 * i;
         if (y >= H) continue;
         size_t o = ((size_t)blockIdx.y * H + y) * W + x;
@@ -1419,6 +1441,16 @@ int split_chains(const ptyr_ctx* c, int B) {
     return c->n_cu / Mc >= 1 ? c->n_cu : 0;
 }
 
+// rows per thread of the object scatter's tiles (32 x 32 or 32 x 8 pixels):
+// the small tile where the large one gives less than one workgroup per two
+// compute units.  By the geometry alone, as the assigning and the fused
+// scatter of a step must use the same tiles.
+int scatter_rows(const ptyr_ctx* c) {
+    const ptyr_geom& g = c->g;
+    const size_t tiles = (size_t)((g.H + 31) / 32) * ((g.W + 31) / 32) * g.S * obj_modes(g);
+    return 2 * tiles < (size_t)std::max(c->n_cu, 1) ? 1 : 4;
+}
+
 ptyr_status run_adjoint(ptyr_ctx* c, const float* amp, const float* phase, const float* probe, const float* pos,
                         const float* tilt, const float* dz, const int* idx, int n_rows, int B,
                         const float* I_meas, float* g_amp, float* g_phase, float* g_probe, float* g_pos,
@@ -1448,34 +1480,29 @@ ptyr_status run_adjoint(ptyr_ctx* c, const float* amp, const float* phase, const
     // j0 > 0 means rows [0, j0) were scattered into the gradient buffers first
     auto scatter = [&](int j0, int j1, hipStream_t st, bool last) {
         if (!(g_amp || g_phase)) return;
-        const int ntiles = ((g.H + 31) / 32) * ((g.W + 31) / 32);
-        const dim3 grid(ntiles, g.S * obj_modes(g));
+        const bool fused = last && fuse;
+        if (!fused && j1 <= j0) return;
+        ObjAdam ad{};
+        if (fused) {
+            ad = *fuse;
+            ad.gin = j0 > 0 ? 1 : 0;
+        } else {
+            // the first scatter of a fused step writes its sums, any other adds them
+            ad.assign = fuse && j0 == 0 ? 1 : 0;
+        }
         // patch gradients per position and object mode: one per group of
         // row_group(g) probe modes (the N = 256 row pass sums each group)
         const int mg = row_group(g), Mg = g.M / mg, Mcg = M / mg;
+        const int rows = scatter_rows(c);
+        const dim3 grid(((g.H + 8 * rows - 1) / (8 * rows)) * ((g.W + 31) / 32), g.S * obj_modes(g));
         const bool mb8 = Mg % 8 == 0;
-        const float2* gO = at<float2>(c, c->L.gO);
-        const PosInfo* pinfo = at<PosInfo>(c, c->L.pinfo);
-        if (last && fuse) {
-            ObjAdam ad = *fuse;
-            ad.gin = j0 > 0 ? 1 : 0;
-            if (mb8)
-                hipLaunchKernelGGL((k_scatter_object<true, 8>), grid, dim3(256), 0, st, gO, pinfo, j0, j1, Mg, Mcg,
-                                   g.S, g.N, g.H, g.W, amp, phase, scale, g_amp, g_phase, ad, sp);
-            else
-                hipLaunchKernelGGL((k_scatter_object<true, 4>), grid, dim3(256), 0, st, gO, pinfo, j0, j1, Mg, Mcg,
-                                   g.S, g.N, g.H, g.W, amp, phase, scale, g_amp, g_phase, ad, sp);
-        } else if (j1 > j0) {
-            // the first scatter of a fused step writes its sums, any other adds them
-            ObjAdam ad{};
-            ad.assign = fuse && j0 == 0 ? 1 : 0;
-            if (mb8)
-                hipLaunchKernelGGL((k_scatter_object<false, 8>), grid, dim3(256), 0, st, gO, pinfo, j0, j1, Mg, Mcg,
-                                   g.S, g.N, g.H, g.W, amp, phase, scale, g_amp, g_phase, ad, sp);
-            else
-                hipLaunchKernelGGL((k_scatter_object<false, 4>), grid, dim3(256), 0, st, gO, pinfo, j0, j1, Mg, Mcg,
-                                   g.S, g.N, g.H, g.W, amp, phase, scale, g_amp, g_phase, ad, sp);
-        }
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, at<float2>(c, c->L.gO), at<PosInfo>(c, c->L.pinfo), j0,
+                               j1, Mg, Mcg, g.S, g.N, g.H, g.W, amp, phase, scale, g_amp, g_phase, ad, sp);
+        };
+        if (rows == 1) go(fused ? k_scatter_object<true, 8, 1> : k_scatter_object<false, 8, 1>);
+        else if (mb8) go(fused ? k_scatter_object<true, 8, 4> : k_scatter_object<false, 8, 4>);
+        else go(fused ? k_scatter_object<true, 4, 4> : k_scatter_object<false, 4, 4>);
     };
     // probe-spectrum sum and inverse transform, position / tilt / dz partials
     auto reductions = [&](hipStream_t st) {
