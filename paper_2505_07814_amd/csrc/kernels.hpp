@@ -57,6 +57,8 @@ struct WaveArgs {
     float2* gO;            // B x M x S x N x N object-patch gradients
     float2* gPhat;         // B x M x N x N probe-spectrum gradients
     double* part;          // B x M x 8 scalar partial sums (N = 256: per line block)
+    const float4* tw;      // N = 64, 128: twiddles (k_twiddles) ...
+    const float4* tab;     // ... and B PosTab<N>, the rows' propagator and shift factors (k_prepare)
 };
 
 // probe spectrum and object transmission (all slices) of chain mode e
@@ -88,40 +90,61 @@ template <int N> struct Slots {
 };
 
 // ------------------------------------------------------------------ tables
-// Per-workgroup LDS tables: twiddles and the separable propagator factors.
+// The factors of one batch row: propagator along y (times 1/N^2) and x,
+// shift ramps exp(-2 pi i q_n dr_y), exp(-2 pi i q_n dr_x).
+template <int N> struct PosTab {
+    float4 hy[N], hx[N];
+    float2 ry[N], rx[N];
+};
+// Per-workgroup LDS tables: twiddles and the factors of the workgroup's row.
 template <int N> struct Tables {
     float4 tw[N];          // twiddles, b-major: tw[b*L + c] = exp(-2 pi i c b / N)
-    float4 hy[N], hx[N];   // propagator factors along y (times 1/N^2) and x
-    float2 ry[N], rx[N];   // shift ramp factors exp(-2 pi i q_n dr_y), exp(-2 pi i q_n dr_x)
+    float4 hy[N], hx[N];   // as PosTab
+    float2 ry[N], rx[N];
 };
+static_assert(sizeof(Tables<64>) == 64 * sizeof(float4) + sizeof(PosTab<64>), "Tables = twiddles, then PosTab");
 
+__device__ __forceinline__ float4 unit_exp(double ph) {
+    double s, c;
+    sincos(ph, &s, &c);
+    return unit_pair(c, s);
+}
+template <int N> __device__ __forceinline__ float4 twiddle_entry(int n) {
+    return unit_exp(-2.0 * 3.14159265358979323846 * (double)((n / (N / 16)) * (n % (N / 16))) / N);
+}
+// Entry n of factor `which` (0: hy, 1: hx, 2: ry, 3: rx) of one row, by double
+// sincos and tan: each takes some thousand cycles of dependent arithmetic, so
+// they are formed once per batch row, beside the other work of k_prepare, and
+// not by every workgroup of the forward and of the gradient before its first
+// slice (the single-slice forward of 100 rows at N = 64 took 17.4 us with the
+// factors formed in the kernel).
 template <int N>
-__device__ __forceinline__ void build_tables(Tables<N>& t, const WaveArgs& a, const PosInfo& pi, float thy,
-                                             float thx, float dz) {
-    constexpr int T = N * N / 16;
+__device__ __forceinline__ void table_entry(PosTab<N>& t, int which, int n, double dx, double lam, double dz, float thy,
+                                            float thx, float dry, float drx) {
     const double pi_d = 3.14159265358979323846;
-    for (int i = threadIdx.x; i < 5 * N; i += T) {
-        int which = i / N, n = i % N;
-        double q = (double)sfreq<N>(n) / N;            // cycles per pixel
-        double k = q / a.dx;                            // 1/angstrom
-        double ph;
-        if (which == 0) ph = -2.0 * pi_d * (double)((n / (N / 16)) * (n % (N / 16))) / N;
-        else if (which == 1) ph = -pi_d * a.lam * dz * k * k + 2.0 * pi_d * dz * k * tan((double)thy);
-        else if (which == 2) ph = -pi_d * a.lam * dz * k * k + 2.0 * pi_d * dz * k * tan((double)thx);
-        else if (which == 3) ph = -2.0 * pi_d * q * pi.dry;
-        else ph = -2.0 * pi_d * q * pi.drx;
-        double s, c;
-        sincos(ph, &s, &c);
-        float4 w = unit_pair(c, s);
-        if (which == 0) t.tw[n] = w;
-        else if (which == 1) {   // the 1/N^2 of the two unnormalised transforms rides on h_y (exact: 2^-k)
-            const float sc = 1.0f / ((float)N * N);
-            t.hy[n] = make_float4(w.x * sc, w.y * sc, w.z * sc, w.w * sc);
-        }
-        else if (which == 2) t.hx[n] = w;
-        else if (which == 3) t.ry[n] = make_float2(w.x, w.y);
-        else t.rx[n] = make_float2(w.x, w.y);
-    }
+    const double q = (double)sfreq<N>(n) / N;          // cycles per pixel
+    const double k = q / dx;                            // 1/angstrom
+    double ph;
+    if (which == 0) ph = -pi_d * lam * dz * k * k + 2.0 * pi_d * dz * k * tan((double)thy);
+    else if (which == 1) ph = -pi_d * lam * dz * k * k + 2.0 * pi_d * dz * k * tan((double)thx);
+    else if (which == 2) ph = -2.0 * pi_d * q * dry;
+    else ph = -2.0 * pi_d * q * drx;
+    const float4 w = unit_exp(ph);
+    if (which == 0) {        // the 1/N^2 of the two unnormalised transforms rides on h_y (exact: 2^-k)
+        const float sc = 1.0f / ((float)N * N);
+        t.hy[n] = make_float4(w.x * sc, w.y * sc, w.z * sc, w.w * sc);
+    } else if (which == 1) t.hx[n] = w;
+    else if (which == 2) t.ry[n] = make_float2(w.x, w.y);
+    else t.rx[n] = make_float2(w.x, w.y);
+}
+
+// the tables of batch row j into LDS: one 16-byte load per thread (4 N of them)
+template <int N> __device__ __forceinline__ void load_tables(Tables<N>& t, const WaveArgs& a, int j) {
+    static_assert(sizeof(PosTab<N>) == 3 * N * sizeof(float4) && 4 * N <= N * N / 16, "one load per thread");
+    const float4* row = a.tab + (size_t)j * 3 * N;
+    float4* dst = reinterpret_cast<float4*>(&t);
+    const int i = threadIdx.x;
+    if (i < 4 * N) dst[i] = i < N ? a.tw[i] : row[i - N];
     __syncthreads();
 }
 
@@ -253,8 +276,7 @@ __global__ __launch_bounds__(N * N / 16) void k_forward(WaveArgs a) {
         for (int i = threadIdx.x; i < N * N; i += blockDim.x) Iout[i] = 0.f;
         return;
     }
-    const float* th = a.global_tilt ? a.tilt : a.tilt + 2 * pi.row;
-    build_tables<N>(tab, a, pi, th[0], th[1], *a.dz);
+    load_tables<N>(tab, a, j);
     const Slots<N> sl(a, j * a.M + m);
     constexpr bool full = KEEP == KEEP_FULL;            // the store is always in the workspace
     const bool ckpt = KEEP == KEEP_CKPT && a.ckK <= a.S;
@@ -362,8 +384,7 @@ __global__ __launch_bounds__(N * N / 16) void k_gradient(WaveArgs a) {
         if (threadIdx.x < 8) part[threadIdx.x] = 0.0;
         return;   // the object-gradient scatter skips such rows
     }
-    const float* th = a.global_tilt ? a.tilt : a.tilt + 2 * pi.row;
-    build_tables<N>(tab, a, pi, th[0], th[1], *a.dz);
+    load_tables<N>(tab, a, j);
     const Slots<N> sl(a, j * a.M + m);
     const size_t HW = (size_t)a.H * a.W;
     const float inv_n = 1.0f / N, inv_n2 = 1.0f / ((float)N * N);
@@ -527,20 +548,17 @@ __global__ __launch_bounds__(N * N / 16) void k_gradient(WaveArgs a) {
 
 // One N x N 2-D DFT of sign SG by a whole workgroup (N*N/16 threads), scaled
 // by 1/N (orthonormal); the result is written to dst, or added to it (ACC).
+// twg: the twiddles of k_twiddles.
 template <int N, int SG, bool ACC>
-__device__ __forceinline__ void fft2_block(const float2* src, float2* dst) {
+__device__ __forceinline__ void fft2_block(const float2* src, float2* dst, const float4* twg) {
     __shared__ float2 lds[WaveGeo<N>::LDS_SLOTS];
     __shared__ float4 tw[N];
     int l, c;
     line_of<N>(threadIdx.x, l, c);
-    for (int n = threadIdx.x; n < N; n += blockDim.x) {
-        double s, co;
-        sincos(-2.0 * 3.14159265358979323846 * (double)((n / (N / 16)) * (n % (N / 16))) / N, &s, &co);
-        tw[n] = unit_pair(co, s);
-    }
-    __syncthreads();
     float2 v[16];
     wload<N, ROW, NAT>(v, src, N, l, c);
+    for (int n = threadIdx.x; n < N; n += blockDim.x) tw[n] = twg[n];
+    __syncthreads();
     nat2mid<WaveGeo<N>, SG>(v, lds, tw, l, c);
     relayout<N, ROW, MID, COL, NAT>(v, lds, l, c);
     nat2mid<WaveGeo<N>, SG>(v, lds, tw, l, c);
@@ -554,8 +572,12 @@ __device__ __forceinline__ void fft2_block(const float2* src, float2* dst) {
 
 // the 2-D DFT of each of gridDim.x fields (one workgroup each)
 template <int N, int SG, bool ACC>
-__global__ __launch_bounds__(N * N / 16) void k_fft2(const float2* in, float2* out) {
-    fft2_block<N, SG, ACC>(in + (size_t)blockIdx.x * N * N, out + (size_t)blockIdx.x * N * N);
+__global__ __launch_bounds__(N * N / 16) void k_fft2(const float2* in, float2* out, const float4* tw) {
+    fft2_block<N, SG, ACC>(in + (size_t)blockIdx.x * N * N, out + (size_t)blockIdx.x * N * N, tw);
+}
+// the twiddles of length N, once per context
+template <int N> __global__ void k_twiddles(float4* tw) {
+    if (threadIdx.x < N) tw[threadIdx.x] = twiddle_entry<N>(threadIdx.x);
 }
 
 }  // namespace ptyr

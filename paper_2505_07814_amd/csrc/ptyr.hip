@@ -131,23 +131,49 @@ __global__ void k_check_distinct(const int* idx, int B, PosInfo* pinfo, int* err
 }
 
 // The work a batch shares, in one launch (N = 64, 128): workgroups 0 .. M-1
-// transform the probe modes (long, one compute unit each), the others form
-// the transmission of every slice, and the first of them the positions, so
-// the transform overlaps the streaming pass instead of following it.
-template <int N>
-__global__ __launch_bounds__(N * N / 16) void k_prepare(const float* amp, const float* phase, float2* Oc, size_t nobj, const float* pos, const int* idx, int n_rows,
-                                                        int B, int H, int W, PosInfo* pinfo, int* err,
-                                                        const float2* probe, float2* Phat, int M, int distinct) {
+// transform the probe modes (long, one compute unit each), the next nt form
+// the rows' propagator and shift factors (PosTab, T / (4 N) rows each), the
+// others the transmission of every slice, and the first of them the
+// positions, so the transform overlaps the streaming pass instead of following
+// it.  A row whose index is bad or whose position is not finite gets no
+// factors: no kernel reads those of a skipped row.
+struct PrepareArgs {
+    const float *amp, *phase, *pos, *tilt, *dz;
+    const int* idx;
+    const float2* probe;
+    float2 *Oc, *Phat;
+    PosInfo* pinfo;
+    const float4* tw;
+    float4* tab;
+    int* err;
+    size_t nobj;
+    int n_rows, B, H, W, M, nt, distinct, global_tilt;
+    double dx, lam;
+};
+template <int N> __global__ __launch_bounds__(N * N / 16) void k_prepare(PrepareArgs p) {
+    constexpr int T = N * N / 16, RPB = T / (4 * N);
     const int b = blockIdx.x;
-    if (b < M) {
-        fft2_block<N, -1, false>(probe + (size_t)b * N * N, Phat + (size_t)b * N * N);
+    if (b < p.M) {
+        fft2_block<N, -1, false>(p.probe + (size_t)b * N * N, p.Phat + (size_t)b * N * N, p.tw);
         return;
     }
-    const int nb = gridDim.x - M;
-    if (b == M)
-        for (int j = threadIdx.x; j < B; j += blockDim.x)
-            position_info(j, pos, idx, n_rows, N, H, W, pinfo, err, distinct);
-    transmission(amp, phase, Oc, nobj, (size_t)(b - M) * blockDim.x + threadIdx.x, (size_t)nb * blockDim.x);
+    if (b < p.M + p.nt) {
+        const int j = (b - p.M) * RPB + (int)threadIdx.x / (4 * N), e = threadIdx.x % (4 * N);
+        if (j >= p.B) return;
+        const int row = p.idx ? p.idx[j] : j;
+        if (row < 0 || row >= p.n_rows) return;
+        const float py = p.pos[2 * row], px = p.pos[2 * row + 1];
+        if (!isfinite(py) || !isfinite(px)) return;
+        const float* th = p.global_tilt ? p.tilt : p.tilt + 2 * row;
+        table_entry<N>(reinterpret_cast<PosTab<N>*>(p.tab)[j], e / N, e % N, p.dx, p.lam, *p.dz, th[0], th[1],
+                       py - rintf(py), px - rintf(px));
+        return;
+    }
+    const int q = b - p.M - p.nt, nb = gridDim.x - p.M - p.nt;
+    if (q == 0)
+        for (int j = threadIdx.x; j < p.B; j += blockDim.x)
+            position_info(j, p.pos, p.idx, p.n_rows, N, p.H, p.W, p.pinfo, p.err, p.distinct);
+    transmission(p.amp, p.phase, p.Oc, p.nobj, (size_t)q * blockDim.x + threadIdx.x, (size_t)nb * blockDim.x);
 }
 
 // fftshift index of an N x N array (its own inverse for even N)
@@ -809,7 +835,7 @@ bool two_terms(const ptyr_geom& g) { return loss_terms(g).n > 1; }
 
 struct Layout {
     size_t Oc, Phat, pinfo, Imode, Ibuf, wbuf, lpart, scal, spart, pac, err, store, gO, gPhat, gPsum, part, gamp, gphase,
-        gprobe, gdz, gpos, gtilt, wave, cons, rzmat, kz, total, tab256;
+        gprobe, gdz, gpos, gtilt, wave, cons, rzmat, kz, total, tab256, tw, tab;
     int keep, ckK, nck, waves_per_chain;
 };
 
@@ -873,6 +899,8 @@ Layout make_layout(const ptyr_geom* g) {
     L.gtilt = take((size_t)std::max(g->n_scan, 1) * 2 * sizeof(float));
     L.wave = take(g->N == 256 ? B * Mc * NN * sizeof(float2) : 0);
     L.tab256 = take(g->N == 256 ? N256 * sizeof(float4) + B * sizeof(PosTab256) : 0);   // N = 256 pass factors
+    L.tw = take(g->N * sizeof(float4));                                     // N = 64, 128: twiddles, ...
+    L.tab = take(g->N == 256 ? 0 : B * 3 * g->N * sizeof(float4));          // ... PosTab of every row
     // probe orthogonalisation: partial overlap sums (double complex), mixing
     // matrix (float complex), eigenvalues
     L.cons = take((size_t)ORTH_MAX_M * (ORTH_MAX_M + 1) / 2 * GRAM_MAX_CHUNKS * sizeof(cd) +
@@ -1051,6 +1079,8 @@ ptyr_status ptyr_create(const ptyr_geom* g, void* workspace, size_t ws_bytes, vo
         return PTYR_E_DEVICE;
     }
     hipLaunchKernelGGL(k_zero, dim3(1), dim3(64), 0, c->stream, at<float>(c, L.err), (size_t)1);
+    if (g->N == 64) hipLaunchKernelGGL(k_twiddles<64>, dim3(1), dim3(64), 0, c->stream, at<float4>(c, L.tw));
+    if (g->N == 128) hipLaunchKernelGGL(k_twiddles<128>, dim3(1), dim3(128), 0, c->stream, at<float4>(c, L.tw));
     if (hipGetLastError() != hipSuccess) { (void)ptyr_destroy(c); return PTYR_E_DEVICE; }
     *out = c;
     return PTYR_OK;
@@ -1151,6 +1181,8 @@ WaveArgs wave_args(ptyr_ctx* c, const float* tilt, const float* dz, int B) {
     a.gO = at<float2>(c, c->L.gO);
     a.gPhat = at<float2>(c, c->L.gPhat);
     a.part = at<double>(c, c->L.part);
+    a.tw = at<float4>(c, c->L.tw);
+    a.tab = at<float4>(c, c->L.tab);
     return a;
 }
 
@@ -1237,35 +1269,38 @@ void gradient_chains(ptyr_ctx* c, const WaveArgs& a, int c0, int nc, hipStream_t
     else gradient256(c, a, c0, nc, st);
 }
 
-// probe transforms, positions and transmission in one launch; the streaming
-// part gets about two workgroups per compute unit (the transform's LDS allows
-// no more), four elements per thread at least
-template <int N>
-void launch_prepare(ptyr_ctx* c, const float* amp, const float* phase, const float* probe, const float* pos,
-                    const int* idx, int n_rows, int B, size_t nobj, hipStream_t st, int distinct) {
-    const ptyr_geom& g = c->g;
-    constexpr int T = N * N / 16;
-    const size_t want = (nobj + 4 * (size_t)T - 1) / (4 * (size_t)T);
+// probe transforms, row factors, positions and transmission in one launch; the
+// streaming part gets about two workgroups per compute unit (the transform's
+// LDS allows no more), four elements per thread at least
+template <int N> void launch_prepare(ptyr_ctx* c, PrepareArgs p) {
+    constexpr int T = N * N / 16, RPB = T / (4 * N);
+    const size_t want = (p.nobj + 4 * (size_t)T - 1) / (4 * (size_t)T);
     const int nb = (int)std::max<size_t>(1, std::min<size_t>(want, 2 * (size_t)std::max(c->n_cu, 1)));
-    hipLaunchKernelGGL(k_prepare<N>, dim3(g.M + nb), dim3(T), 0, st, amp, phase, at<float2>(c, c->L.Oc), nobj, pos,
-                       idx, idx ? n_rows : B, B, g.H, g.W, at<PosInfo>(c, c->L.pinfo), at<int>(c, c->L.err),
-                       reinterpret_cast<const float2*>(probe), at<float2>(c, c->L.Phat), g.M, distinct);
+    p.nt = (p.B + RPB - 1) / RPB;
+    hipLaunchKernelGGL(k_prepare<N>, dim3(p.M + p.nt + nb), dim3(T), 0, c->stream, p);
 }
 template <int N> void launch_probe_ifft_acc(ptyr_ctx* c, float* g_probe, hipStream_t st) {
     hipLaunchKernelGGL((k_fft2<N, +1, true>), dim3(c->g.M), dim3(N * N / 16), 0, st,
-                       at<float2>(c, c->L.gPsum), reinterpret_cast<float2*>(g_probe));
+                       at<float2>(c, c->L.gPsum), reinterpret_cast<float2*>(g_probe), at<float4>(c, c->L.tw));
 }
 
 // Work shared by every row of a batch: transmission of all slices, validated
-// positions, probe spectra.
+// positions, probe spectra, and (N = 64, 128) the rows' propagator and shift
+// factors.
 void prepare_forward(ptyr_ctx* c, const float* amp, const float* phase, const float* probe, const float* pos,
-                     const int* idx, int n_rows, int B, int distinct) {
+                     const float* tilt, const float* dz, const int* idx, int n_rows, int B, int distinct) {
     const hipStream_t st = c->stream;
     const ptyr_geom& g = c->g;
     size_t nobj = (size_t)obj_modes(g) * g.S * g.H * g.W;
-    if (g.N == 64) launch_prepare<64>(c, amp, phase, probe, pos, idx, n_rows, B, nobj, st, distinct);
-    else if (g.N == 128) launch_prepare<128>(c, amp, phase, probe, pos, idx, n_rows, B, nobj, st, distinct);
-    else {
+    if (g.N < 256) {
+        const PrepareArgs p{amp, phase, pos, tilt, dz, idx, reinterpret_cast<const float2*>(probe),
+                            at<float2>(c, c->L.Oc), at<float2>(c, c->L.Phat), at<PosInfo>(c, c->L.pinfo),
+                            at<float4>(c, c->L.tw), at<float4>(c, c->L.tab), at<int>(c, c->L.err), nobj,
+                            idx ? n_rows : B, B, g.H, g.W, g.M, 0, distinct, (g.flags & PTYR_GLOBAL_TILT) ? 1 : 0,
+                            g.dx, g.lambda};
+        if (g.N == 64) launch_prepare<64>(c, p);
+        else launch_prepare<128>(c, p);
+    } else {
         hipLaunchKernelGGL(k_transmission, dim3(grid_for((nobj + 7) / 8)), dim3(256), 0, st, amp, phase,
                            at<float2>(c, c->L.Oc), nobj);
         hipLaunchKernelGGL(k_positions, dim3((B + 63) / 64), dim3(64), 0, st, pos, idx, idx ? n_rows : B, B, g.N,
@@ -1288,7 +1323,7 @@ void modesum_rows(ptyr_ctx* c, int r0, int nr, hipStream_t st) {
 
 ptyr_status run_forward(ptyr_ctx* c, const float* amp, const float* phase, const float* probe, const float* pos,
                         const float* tilt, const float* dz, const int* idx, int n_rows, int B) {
-    prepare_forward(c, amp, phase, probe, pos, idx, n_rows, B, 0);
+    prepare_forward(c, amp, phase, probe, pos, tilt, dz, idx, n_rows, B, 0);
     forward_chains(c, wave_args(c, tilt, dz, B), 0, B * chain_modes(c->g), c->stream);
     modesum_rows(c, 0, B, c->stream);
     if (hipGetLastError() != hipSuccess) return PTYR_E_DEVICE;
@@ -1461,7 +1496,7 @@ ptyr_status run_adjoint(ptyr_ctx* c, const float* amp, const float* phase, const
     const bool reuse = (flags & PTYR_REUSE_FORWARD) && c->fwd_valid && c->fwd_B == B;
     const int nA = reuse ? 0 : split_chains(c, B);
     const bool fold = g.pacbed_w > 0.0 || two_terms(g);     // weights finished before the gradient
-    if (!reuse) prepare_forward(c, amp, phase, probe, pos, idx, n_rows, B, 1);
+    if (!reuse) prepare_forward(c, amp, phase, probe, pos, tilt, dz, idx, n_rows, B, 1);
     else if (idx)
         hipLaunchKernelGGL(k_check_distinct, dim3(1), dim3(256), 0, c->stream, idx, B, at<PosInfo>(c, c->L.pinfo),
                            at<int>(c, c->L.err));
