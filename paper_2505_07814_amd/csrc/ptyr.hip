@@ -1313,19 +1313,15 @@ void prepare_forward(ptyr_ctx* c, const float* amp, const float* phase, const fl
     }
 }
 
-void modesum_rows(ptyr_ctx* c, int r0, int nr, hipStream_t st) {
-    const ptyr_geom& g = c->g;
-    const size_t NN = (size_t)g.N * g.N;
-    hipLaunchKernelGGL(k_modesum, dim3(grid_for((size_t)nr * NN)), dim3(256), 0, st,
-                       at<float>(c, c->L.Imode) + (size_t)r0 * chain_modes(g) * NN,
-                       at<float>(c, c->L.Ibuf) + (size_t)r0 * NN, nr, chain_modes(g), g.N);
-}
-
 ptyr_status run_forward(ptyr_ctx* c, const float* amp, const float* phase, const float* probe, const float* pos,
-                        const float* tilt, const float* dz, const int* idx, int n_rows, int B) {
+                        const float* tilt, const float* dz, const int* idx, int n_rows, int B, float* I_out) {
+    const ptyr_geom& g = c->g;
     prepare_forward(c, amp, phase, probe, pos, tilt, dz, idx, n_rows, B, 0);
-    forward_chains(c, wave_args(c, tilt, dz, B), 0, B * chain_modes(c->g), c->stream);
-    modesum_rows(c, 0, B, c->stream);
+    forward_chains(c, wave_args(c, tilt, dz, B), 0, B * chain_modes(g), c->stream);
+    // straight into the caller's array: a gradient that reuses this forward
+    // sums the modes again in its loss pass
+    hipLaunchKernelGGL(k_modesum, dim3(grid_for((size_t)B * g.N * g.N)), dim3(256), 0, c->stream,
+                       at<float>(c, c->L.Imode), I_out, B, chain_modes(g), g.N);
     if (hipGetLastError() != hipSuccess) return PTYR_E_DEVICE;
     c->fwd_valid = 1;
     c->fwd_B = B;
@@ -1665,13 +1661,7 @@ ptyr_status ptyr_forward(ptyr_ctx* c, const float* amp, const float* phase, cons
     if (st != PTYR_OK) return st;
     if (!amp || !phase || !probe || !pos || !tilt || !dz || !I_out) return PTYR_E_ARG;
     if (idx && n_rows < 1) return PTYR_E_ARG;
-    st = run_forward(c, amp, phase, probe, pos, tilt, dz, idx, n_rows, B);
-    if (st != PTYR_OK) return st;
-    size_t n = (size_t)B * c->g.N * c->g.N;
-    if (hipMemcpyAsync(I_out, at<float>(c, c->L.Ibuf), n * sizeof(float), hipMemcpyDeviceToDevice, c->stream) !=
-        hipSuccess)
-        return PTYR_E_DEVICE;
-    return PTYR_OK;
+    return run_forward(c, amp, phase, probe, pos, tilt, dz, idx, n_rows, B, I_out);
 }
 
 ptyr_status ptyr_loss(ptyr_ctx* c, const float* I_model, const float* I_meas, const int* meas_idx, int n_meas,
