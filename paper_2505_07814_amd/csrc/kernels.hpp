@@ -158,7 +158,7 @@ __device__ __forceinline__ void transmit(float2 (&v)[16], const float2* Os, int 
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         v[r] = cmul(v[r], (base + Y::dy(r) * W)[o]);
-        if ((r & 7) == 7) __builtin_amdgcn_sched_barrier(0);
+        if (N == 128 && (r & 7) == 7) __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -173,29 +173,29 @@ __device__ __forceinline__ void load_patch(float2 (&ov)[16], const float2* Os, i
 }
 
 // phi_0 = F^-1[ Phat_m * R ] (orthonormal), leaves in (COL, NAT)
-template <int N>
+template <int N, class TW>
 __device__ __forceinline__ void shift_probe(float2 (&v)[16], const float2* Pm, float2* lds, const Tables<N>& t,
-                                            int l, int c) {
+                                            const TW& tw, int l, int c) {
     const float sc = 1.0f / N;
     wload<N, ROW, MID>(v, Pm, N, l, c);
     const float2 ru = cscale(t.ry[l], sc);
 #pragma unroll
     for (int r = 0; r < 16; ++r) v[r] = cmul(cmul(v[r], ru), t.rx[line_pos<N, MID>(c, r)]);
-    mid2nat<WaveGeo<N>, +1>(v, lds, t.tw, l, c);
+    mid2nat<WaveGeo<N>, +1>(v, lds, tw, l, c);
     relayout<N, ROW, NAT, COL, MID>(v, lds, l, c);
-    mid2nat<WaveGeo<N>, +1>(v, lds, t.tw, l, c);
+    mid2nat<WaveGeo<N>, +1>(v, lds, tw, l, c);
 }
 
 // unnormalised 2-D DFT of sign -1 from (COL, NAT); leaves in (ROW, MID)
-template <int N>
-__device__ __forceinline__ void fft2_from_col(float2 (&v)[16], float2* lds, const float4* tw, int l, int c) {
+template <int N, class TW>
+__device__ __forceinline__ void fft2_from_col(float2 (&v)[16], float2* lds, const TW& tw, int l, int c) {
     nat2mid<WaveGeo<N>, -1>(v, lds, tw, l, c);
     relayout<N, COL, MID, ROW, NAT>(v, lds, l, c);
     nat2mid<WaveGeo<N>, -1>(v, lds, tw, l, c);
 }
 // unnormalised 2-D inverse DFT from (ROW, MID); leaves in (COL, NAT)
-template <int N>
-__device__ __forceinline__ void ifft2_to_col(float2 (&v)[16], float2* lds, const float4* tw, int l, int c) {
+template <int N, class TW>
+__device__ __forceinline__ void ifft2_to_col(float2 (&v)[16], float2* lds, const TW& tw, int l, int c) {
     mid2nat<WaveGeo<N>, +1>(v, lds, tw, l, c);
     relayout<N, ROW, NAT, COL, MID>(v, lds, l, c);
     mid2nat<WaveGeo<N>, +1>(v, lds, tw, l, c);
@@ -209,21 +209,35 @@ __device__ __forceinline__ void apply_h(float2 (&v)[16], const Tables<N>& t, int
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         v[r] = tmul<CONJ>(tmul<CONJ>(v[r], hy), t.hx[line_pos<N, MID>(c, r)]);
-        if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+        if (N == 128 && (r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
     }
 }
 
 // One slice step: v = phi_s (COL, NAT) -> chi_s -> (F, H, F^-1) -> phi_{s+1}
 // (COL, NAT).  The spectrum Y'_{s+1} = H F_raw[chi_s] / N^2 = F_raw[phi_{s+1}] / N^2
 // is written to spec when spec != nullptr.
-template <int N>
+template <int N, class TW>
 __device__ __forceinline__ void slice_step(float2 (&v)[16], const float2* Os, int W, int ty, int tx, float2* spec,
-                                           float2* lds, const Tables<N>& t, int l, int c) {
+                                           float2* lds, const Tables<N>& t, const TW& tw, int l, int c) {
     transmit<N>(v, Os, W, ty, tx, l, c);
-    fft2_from_col<N>(v, lds, t.tw, l, c);
+    fft2_from_col<N>(v, lds, tw, l, c);
     apply_h<N, false>(v, t, l, c);
     if (spec) kstore<N>(v, spec);
-    ifft2_to_col<N>(v, lds, t.tw, l, c);
+    ifft2_to_col<N>(v, lds, tw, l, c);
+}
+
+// The twiddles of a fused kernel: in LDS (N = 128, where the wave leaves no
+// registers for them), or the thread's own in registers (WIDE).
+template <int N, bool WIDE> __device__ __forceinline__ auto kernel_twiddles(const Tables<N>& t, int c) {
+    if constexpr (WIDE) {
+        RegTw r;
+        r.w[0] = make_float4(1.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int b = 1; b < 16; ++b) r.w[b] = t.tw[b * (N / 16) + c];
+        return r;
+    } else {
+        return static_cast<const float4*>(t.tw);
+    }
 }
 
 // block-wide sum of NV values, result valid in thread 0
@@ -262,7 +276,7 @@ template <int N> constexpr int fwd_lds_slots() {
 // store plan) is a template parameter so that the hot loop has no
 // data-dependent branch around its writes: at such a merge the compiler's
 // wait for the object-patch reads would also wait for the writes.
-template <int N, int KEEP>
+template <int N, int KEEP, bool WIDE>
 __global__ __launch_bounds__(N * N / 16) void k_forward(WaveArgs a) {
     __shared__ float2 lds[fwd_lds_slots<N>()];
     __shared__ Tables<N> tab;
@@ -283,8 +297,9 @@ __global__ __launch_bounds__(N * N / 16) void k_forward(WaveArgs a) {
     const size_t HW = (size_t)a.H * a.W;
 
     const float2* Ocm = chain_object(a, m);
+    const auto tw = kernel_twiddles<N, WIDE>(tab, c);
     float2 v[16];
-    shift_probe<N>(v, chain_probe(a, m, N * N), lds, tab, l, c);
+    shift_probe<N>(v, chain_probe(a, m, N * N), lds, tab, tw, l, c);
     // the object patch of a slice is read one slice ahead, so that its
     // latency overlaps the previous slice's transforms (forward launch
     // 0.486 -> 0.467 ms)
@@ -302,7 +317,7 @@ __global__ __launch_bounds__(N * N / 16) void k_forward(WaveArgs a) {
         if (full) kstore_q<N, 0>(v, sl.phi(s));
         else if (ckpt && s % a.ckK == 0) kstore<N>(v, sl.ckpt(s / a.ckK));
         __builtin_amdgcn_sched_barrier(0);
-        nat2mid<WaveGeo<N>, -1>(ov, lds, tab.tw, l, c);
+        nat2mid<WaveGeo<N>, -1>(ov, lds, tw, l, c);
         __builtin_amdgcn_sched_barrier(0);
         if (full) kstore_q<N, 1>(v, sl.phi(s));
         __builtin_amdgcn_sched_barrier(0);
@@ -310,7 +325,7 @@ __global__ __launch_bounds__(N * N / 16) void k_forward(WaveArgs a) {
         __builtin_amdgcn_sched_barrier(0);
         if (full) kstore_q<N, 2>(v, sl.phi(s));
         __builtin_amdgcn_sched_barrier(0);
-        nat2mid<WaveGeo<N>, -1>(ov, lds, tab.tw, l, c);
+        nat2mid<WaveGeo<N>, -1>(ov, lds, tw, l, c);
         __builtin_amdgcn_sched_barrier(0);
         if (full) kstore_q<N, 3>(v, sl.phi(s));
         apply_h<N, false>(ov, tab, l, c);
@@ -318,18 +333,18 @@ __global__ __launch_bounds__(N * N / 16) void k_forward(WaveArgs a) {
         for (int r = 0; r < 16; ++r) v[r] = ov[r];
         if (full) kstore_half<N, 0>(ov, sl.spec(s + 1));
         __builtin_amdgcn_sched_barrier(0);
-        mid2nat<WaveGeo<N>, +1>(v, lds, tab.tw, l, c);
+        mid2nat<WaveGeo<N>, +1>(v, lds, tw, l, c);
         __builtin_amdgcn_sched_barrier(0);
         if (full) kstore_half<N, 1>(ov, sl.spec(s + 1));
         relayout<N, ROW, NAT, COL, MID>(v, lds, l, c);
         if (s + 1 < a.S - 1) load_patch<N>(ov, Ocm + (size_t)(s + 1) * HW, a.W, pi.ty, pi.tx, l, c);
-        mid2nat<WaveGeo<N>, +1>(v, lds, tab.tw, l, c);
+        mid2nat<WaveGeo<N>, +1>(v, lds, tw, l, c);
     }
     const int s = a.S - 1;
     if (full) kstore<N>(v, sl.phi(s));
     else if (ckpt && s % a.ckK == 0) kstore<N>(v, sl.ckpt(s / a.ckK));
     transmit<N>(v, Ocm + (size_t)s * HW, a.W, pi.ty, pi.tx, l, c);
-    fft2_from_col<N>(v, lds, tab.tw, l, c);
+    fft2_from_col<N>(v, lds, tw, l, c);
     if (full) kstore<N>(v, sl.far());
     // far field |F chi|^2 / N^2 (zero frequency at (0, 0); the mode sum shifts it)
     const float s2 = 1.0f / ((float)N * N);
@@ -343,21 +358,21 @@ __global__ __launch_bounds__(N * N / 16) void k_forward(WaveArgs a) {
 // from the last kept checkpoint at or before slice s-1 (or from the shifted
 // probe when none is kept), so that for s > 0 the last step also yields
 // Y'_s, written to spec.  Recomputed values are bitwise those of the forward.
-template <int N>
+template <int N, class TW>
 __device__ __forceinline__ void recompute_phi(float2 (&v)[16], int s, const WaveArgs& a, const Slots<N>& sl, int m,
-                                              int ty, int tx, float2* spec, float2* lds, const Tables<N>& t, int l,
-                                              int c) {
+                                              int ty, int tx, float2* spec, float2* lds, const Tables<N>& t,
+                                              const TW& tw, int l, int c) {
     int s0 = 0;
     if (a.ckK <= a.S) {
         s0 = s > 0 ? ((s - 1) / a.ckK) * a.ckK : 0;
         kload<N>(v, sl.ckpt(s0 / a.ckK));
     } else {
-        shift_probe<N>(v, chain_probe(a, m, N * N), lds, t, l, c);
+        shift_probe<N>(v, chain_probe(a, m, N * N), lds, t, tw, l, c);
     }
     const size_t HW = (size_t)a.H * a.W;
     const float2* Ocm = chain_object(a, m);
     for (int u = s0; u < s; ++u)
-        slice_step<N>(v, Ocm + (size_t)u * HW, a.W, ty, tx, u == s - 1 ? spec : nullptr, lds, t, l, c);
+        slice_step<N>(v, Ocm + (size_t)u * HW, a.W, ty, tx, u == s - 1 ? spec : nullptr, lds, t, tw, l, c);
 }
 
 // Gradient: one workgroup per (batch row j, probe mode m).  Walks the slices
@@ -367,7 +382,7 @@ __device__ __forceinline__ void recompute_phi(float2 (&v)[16], int s, const Wave
 // Writes per-slice object-patch gradients conj(phi_s) G_chi, the
 // probe-spectrum gradient conj(R) G^_0 and partial sums for the position,
 // tilt and dz gradients.
-template <int N, int KEEP>
+template <int N, int KEEP, bool WIDE>
 __global__ __launch_bounds__(N * N / 16) void k_gradient(WaveArgs a) {
     constexpr int T = N * N / 16;
     __shared__ float2 lds[WaveGeo<N>::LDS_SLOTS];
@@ -389,14 +404,15 @@ __global__ __launch_bounds__(N * N / 16) void k_gradient(WaveArgs a) {
     const size_t HW = (size_t)a.H * a.W;
     const float inv_n = 1.0f / N, inv_n2 = 1.0f / ((float)N * N);
 
+    const auto tw = kernel_twiddles<N, WIDE>(tab, c);
     float2 g[16];
     // far field: kept, or recomputed from phi_{S-1}
     if (KEEP == KEEP_FULL) {
         kload<N>(g, sl.far());
     } else {
-        recompute_phi<N>(g, a.S - 1, a, sl, m, pi.ty, pi.tx, sl.sc_spec(), lds, tab, l, c);
+        recompute_phi<N>(g, a.S - 1, a, sl, m, pi.ty, pi.tx, sl.sc_spec(), lds, tab, tw, l, c);
         transmit<N>(g, chain_object(a, m) + (size_t)(a.S - 1) * HW, a.W, pi.ty, pi.tx, l, c);
-        fft2_from_col<N>(g, lds, tab.tw, l, c);
+        fft2_from_col<N>(g, lds, tw, l, c);
     }
     {   // G_chi_{S-1} = F^-1[ w F[chi_{S-1}] ]   (w = 2 dL/dI)
         float wv[16];
@@ -404,16 +420,52 @@ __global__ __launch_bounds__(N * N / 16) void k_gradient(WaveArgs a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) g[r] = cscale(g[r], wv[r] * inv_n2);
     }
-    ifft2_to_col<N>(g, lds, tab.tw, l, c);
-
     using YC = Lay<N, COL, NAT>;
     using YR = Lay<N, ROW, MID>;
     const unsigned oW = YC::toff(l, c, a.W);
     const unsigned oM = YR::toff(l, c, N);
 
+    // WIDE: phi_s and O_s of the next slice are read while the current
+    // slice's transforms run, and Y_s while the first of them does.  With one
+    // wave per SIMD (few N = 64 chains) nothing else hides those latencies.
+    float2 ph_[WIDE ? 16 : 1], ov_[WIDE ? 16 : 1], yv_[WIDE ? 16 : 1];
+    auto fetch = [&](int s) {
+        if constexpr (WIDE) {
+            const float2* phi_s = sl.phi(s);
+            const float2* Os = chain_object(a, m) + (size_t)s * HW + (size_t)pi.ty * a.W + pi.tx;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) ph_[r] = (phi_s + r * T)[threadIdx.x];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) ov_[r] = (Os + YC::dy(r) * a.W)[oW];
+        }
+    };
+    fetch(a.S - 1);
+    ifft2_to_col<N>(g, lds, tw, l, c);
+
     // chi_s = O_s phi_s: gO_s = conj(phi_s) G_chi, then G_phi = conj(O_s) G_chi,
     // then G^ = F_raw G_phi.  Returns the stream of Y'_s for s > 0.
     auto slice_back = [&](int s) -> const float2* {
+        if constexpr (WIDE) {
+            float2* go = a.gO + ((size_t)(j * a.M + m) * a.S + s) * N * N;
+            float2 t[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                t[r] = cmulc(g[r], ph_[r]);
+                g[r] = cmulc(g[r], ov_[r]);
+            }
+            // every read before the writes: one in-order counter covers both
+            if (s > 0) {
+                const float2* Y_s = sl.spec(s);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) yv_[r] = (Y_s + r * T)[threadIdx.x];
+                fetch(s - 1);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) (go + r * T)[threadIdx.x] = t[r];
+            fft2_from_col<N>(g, lds, tw, l, c);
+            return nullptr;
+        }
         const float2 *phi_s, *Y_s;
         if (KEEP == KEEP_FULL) {
             phi_s = sl.phi(s);
@@ -421,7 +473,7 @@ __global__ __launch_bounds__(N * N / 16) void k_gradient(WaveArgs a) {
         } else {
             // park G, recompute phi_s and Y'_s into the scratch, take G back
             kstore<N>(g, sl.sc_g());
-            recompute_phi<N>(g, s, a, sl, m, pi.ty, pi.tx, sl.sc_spec(), lds, tab, l, c);
+            recompute_phi<N>(g, s, a, sl, m, pi.ty, pi.tx, sl.sc_spec(), lds, tab, tw, l, c);
             kstore<N>(g, sl.sc_phi());
             kload<N>(g, sl.sc_g());
             phi_s = sl.sc_phi();
@@ -473,7 +525,7 @@ __global__ __launch_bounds__(N * N / 16) void k_gradient(WaveArgs a) {
         // exchange (quarter 3 went out before the transform), so that the
         // chain's writes come in spaced groups
         __builtin_amdgcn_sched_barrier(0);
-        nat2mid<WaveGeo<N>, -1>(g, lds, tab.tw, l, c);
+        nat2mid<WaveGeo<N>, -1>(g, lds, tw, l, c);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int r = 0; r < 4; ++r) (go + r * T)[threadIdx.x] = t0[r];
@@ -484,7 +536,7 @@ __global__ __launch_bounds__(N * N / 16) void k_gradient(WaveArgs a) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int r = 4; r < 8; ++r) (go + r * T)[threadIdx.x] = t0[r];
-        nat2mid<WaveGeo<N>, -1>(g, lds, tab.tw, l, c);
+        nat2mid<WaveGeo<N>, -1>(g, lds, tw, l, c);
         return Y_s;
     };
 
@@ -505,7 +557,7 @@ __global__ __launch_bounds__(N * N / 16) void k_gradient(WaveArgs a) {
         asm volatile("" : "+v"(cc));
         float2 yv[16];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) yv[r] = (Y_s + r * T)[threadIdx.x];
+        for (int r = 0; r < 16; ++r) yv[r] = WIDE ? yv_[WIDE ? r : 0] : (Y_s + r * T)[threadIdx.x];
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const float2 y = yv[r];
@@ -516,7 +568,7 @@ __global__ __launch_bounds__(N * N / 16) void k_gradient(WaveArgs a) {
             acc_ky = fma(e, ky, acc_ky);
         }
         apply_h<N, true>(g, tab, l, c);                                       // conj(H) G^ / N^2
-        ifft2_to_col<N>(g, lds, tab.tw, l, c);                                // G_chi_{s-1}
+        ifft2_to_col<N>(g, lds, tw, l, c);                                // G_chi_{s-1}
     }
     slice_back(0);
     // probe spectrum and position: phi_0 = F^-1[Phat R]

@@ -1187,22 +1187,18 @@ WaveArgs wave_args(ptyr_ctx* c, const float* tilt, const float* dz, int B) {
 }
 
 // the fused kernels over chains [c0, c0 + nc) (chain = row * M + mode) on stream st
-template <int N> void launch_forward(ptyr_ctx* c, WaveArgs a, int c0, int nc, hipStream_t st) {
+// WIDE (N = 64, every wave kept): see wide_chains.
+template <int N, bool WIDE = false> void launch_forward(ptyr_ctx* c, WaveArgs a, int c0, int nc, hipStream_t st) {
     TimedLaunch t(c, PTYR_K_FORWARD, st, true);
     a.chain0 = c0;
-    if (a.keep == KEEP_FULL)
-        hipExtLaunchKernelGGL((k_forward<N, KEEP_FULL>), dim3(nc), dim3(N * N / 16), 0, st, t.start(), t.stop(), 0, a);
-    else
-        hipExtLaunchKernelGGL((k_forward<N, KEEP_CKPT>), dim3(nc), dim3(N * N / 16), 0, st, t.start(), t.stop(), 0, a);
+    const auto kernel = a.keep == KEEP_FULL ? k_forward<N, KEEP_FULL, WIDE> : k_forward<N, KEEP_CKPT, false>;
+    hipExtLaunchKernelGGL(kernel, dim3(nc), dim3(N * N / 16), 0, st, t.start(), t.stop(), 0, a);
 }
-template <int N> void launch_gradient(ptyr_ctx* c, WaveArgs a, int c0, int nc, hipStream_t st) {
+template <int N, bool WIDE = false> void launch_gradient(ptyr_ctx* c, WaveArgs a, int c0, int nc, hipStream_t st) {
     TimedLaunch t(c, PTYR_K_GRADIENT, st, true);
     a.chain0 = c0;
-    if (a.keep == KEEP_FULL)
-        hipExtLaunchKernelGGL((k_gradient<N, KEEP_FULL>), dim3(nc), dim3(N * N / 16), 0, st, t.start(), t.stop(), 0, a);
-    else
-        hipExtLaunchKernelGGL((k_gradient<N, KEEP_CKPT>), dim3(nc), dim3(N * N / 16), 0, st, t.start(), t.stop(), 0,
-                              a);
+    const auto kernel = a.keep == KEEP_FULL ? k_gradient<N, KEEP_FULL, WIDE> : k_gradient<N, KEEP_CKPT, false>;
+    hipExtLaunchKernelGGL(kernel, dim3(nc), dim3(N * N / 16), 0, st, t.start(), t.stop(), 0, a);
 }
 // N = 256: forward and gradient as line passes (lines256.hpp)
 Pass256 pass256(ptyr_ctx* c, const WaveArgs& a, int s) {
@@ -1258,13 +1254,23 @@ void gradient256(ptyr_ctx* c, WaveArgs a, int c0, int nc, hipStream_t st) {
         hipLaunchKernelGGL(k256_grad_col, grid, blk, 0, st, pass256(c, a, s));
     }
 }
+// N = 64 with at most two chains per compute unit: the fused kernels run with
+// their twiddles in registers, without the fences that bound N = 128's
+// register use, and the gradient reads a slice ahead (WIDE: one workgroup per
+// compute unit in the gradient, 288 registers).  Measured, step of 12 slices:
+// 400 chains 494 -> 469 us, 480 chains 524 -> 494 us; 24 slices, 16 chains
+// 425 -> 393 us; but 1200 chains of 6 slices 626 -> 695 us, where three
+// narrow workgroups per compute unit hide each other's latencies.
+bool wide_chains(const ptyr_ctx* c, const WaveArgs& a) { return a.B * a.M <= 2 * c->n_cu; }
 void forward_chains(ptyr_ctx* c, const WaveArgs& a, int c0, int nc, hipStream_t st) {
-    if (c->g.N == 64) launch_forward<64>(c, a, c0, nc, st);
+    if (c->g.N == 64 && wide_chains(c, a)) launch_forward<64, true>(c, a, c0, nc, st);
+    else if (c->g.N == 64) launch_forward<64>(c, a, c0, nc, st);
     else if (c->g.N == 128) launch_forward<128>(c, a, c0, nc, st);
     else forward256(c, a, c0, nc, st);
 }
 void gradient_chains(ptyr_ctx* c, const WaveArgs& a, int c0, int nc, hipStream_t st) {
-    if (c->g.N == 64) launch_gradient<64>(c, a, c0, nc, st);
+    if (c->g.N == 64 && wide_chains(c, a)) launch_gradient<64, true>(c, a, c0, nc, st);
+    else if (c->g.N == 64) launch_gradient<64>(c, a, c0, nc, st);
     else if (c->g.N == 128) launch_gradient<128>(c, a, c0, nc, st);
     else gradient256(c, a, c0, nc, st);
 }

@@ -186,9 +186,11 @@ template <int N> struct WaveGeo {
     static constexpr int SYF = N + L;
     static constexpr int XCH_SLOTS = (N - 1) * SL + (HALF ? 7 : 15) * SB + L;
     static constexpr int T_SLOTS = HALF ? (N * SYF + 1) / 2 : N * SY;
-    static constexpr int LDS_SLOTS = XCH_SLOTS > T_SLOTS ? XCH_SLOTS : T_SLOTS;
     static constexpr bool WAVE_LOCAL = true;      // a line's lanes share a wave
     static constexpr bool XLANE = true;           // line exchanges by cross-lane swaps (line_of placement)
+    // with them only the transposes use the buffer (N = 64: 34 KiB instead of
+    // 50, four workgroups per compute unit instead of two)
+    static constexpr int LDS_SLOTS = XLANE ? T_SLOTS : (XCH_SLOTS > T_SLOTS ? XCH_SLOTS : T_SLOTS);
 };
 
 // (line l, lane c within the line) of thread tid for WaveGeo<N>: the wave
@@ -321,6 +323,23 @@ template <int L, int SG> __device__ __forceinline__ void twiddle_pass(float2 (&v
     }
 }
 
+// The same from the thread's own fifteen entries held in registers (w[b] =
+// tw[b*L + c]): no LDS read and no fence per pass, for kernels with the
+// registers to spare (60 VGPRs).
+struct RegTw {
+    float4 w[16];
+};
+template <int L, int SG> __device__ __forceinline__ void twiddle_pass(float2 (&v)[16], const RegTw& t) {
+#pragma unroll
+    for (int b = 1; b < 16; ++b) v[b] = tmul<(SG > 0)>(v[b], t.w[b]);
+}
+template <int L, int SG> __device__ __forceinline__ void twiddles(float2 (&v)[16], const float4* tw, int c) {
+    twiddle_pass<L, SG>(v, tw + c);
+}
+template <int L, int SG> __device__ __forceinline__ void twiddles(float2 (&v)[16], const RegTw& tw, int) {
+    twiddle_pass<L, SG>(v, tw);
+}
+
 // ------------------------------------------------------------ line transforms
 // Each line owns its exchange slots (l * SL .. l * SL + 15 * SB + L - 1, below
 // (l + 1) * SL).  Where the lanes of a line sit in one wave (GEO::WAVE_LOCAL:
@@ -391,12 +410,12 @@ template <int L> __device__ __forceinline__ void xlane_transpose(float2 (&v)[16]
 // With HALF the exchange runs in two rounds through the slots of b < 8: the
 // first moves registers 0..7 (read back by the blocks be < G/2, whose
 // sources b = c + L*be are < 8), the second registers 8..15.
-template <class GEO, int SG>
-__device__ __forceinline__ void nat2mid(float2 (&v)[16], float2* lds, const float4* tw, int l, int c) {
+template <class GEO, int SG, class TW>
+__device__ __forceinline__ void nat2mid(float2 (&v)[16], float2* lds, const TW& tw, int l, int c) {
     constexpr int L = GEO::L, G = 16 / L;
     constexpr int R = HalfX<GEO>::value ? 2 : 1;      // rounds
     dft16<SG>(v);
-    twiddle_pass<L, SG>(v, tw + c);
+    twiddles<L, SG>(v, tw, c);
     if constexpr (XLaneX<GEO>::value) {
         xlane_transpose<L>(v);
 #pragma unroll
@@ -420,15 +439,15 @@ __device__ __forceinline__ void nat2mid(float2 (&v)[16], float2* lds, const floa
 }
 
 // MID -> NAT, DFT of sign SG along every line.
-template <class GEO, int SG>
-__device__ __forceinline__ void mid2nat(float2 (&v)[16], float2* lds, const float4* tw, int l, int c) {
+template <class GEO, int SG, class TW>
+__device__ __forceinline__ void mid2nat(float2 (&v)[16], float2* lds, const TW& tw, int l, int c) {
     constexpr int L = GEO::L, G = 16 / L;
     constexpr int R = HalfX<GEO>::value ? 2 : 1;      // rounds, as in nat2mid
 #pragma unroll
     for (int be = 0; be < G; ++be) dftL<L, SG>(&v[be * L]);
     if constexpr (XLaneX<GEO>::value) {
         xlane_transpose<L>(v);
-        twiddle_pass<L, SG>(v, tw + c);
+        twiddles<L, SG>(v, tw, c);
         dft16<SG>(v);
         return;
     }
@@ -444,7 +463,7 @@ __device__ __forceinline__ void mid2nat(float2 (&v)[16], float2* lds, const floa
         for (int b = 0; b < NB; ++b) v[h * NB + b] = lds[slot_x<GEO>(l, b, c)];
         exchange_sync<GEO>();
     }
-    twiddle_pass<L, SG>(v, tw + c);
+    twiddles<L, SG>(v, tw, c);
     dft16<SG>(v);
 }
 

@@ -17,3 +17,12 @@ def test_scatter_tiles_and_more_than_64_rows(S, H, W):
     print(f"scatter S={S} H={H} W={W} B=67", flush=True)
     c = Case(synth.small_case(N=64, S=S, M=1, B=67, H=H, W=W, seed=41))
     _check_grads(c, c.engine())
+
+
+@pytest.mark.parametrize("B,M,budget", [(3, 1, None), (130, 4, None), (6, 2, 0)])
+def test_gradient_by_chains_per_compute_unit(B, M, budget):
+    """N = 64 with few chains, with more than two chains per compute unit, and
+    with no wave kept (the gradient recomputes them)."""
+    print(f"gradient N=64 S=3 B={B} M={M} budget={budget}", flush=True)
+    c = Case(synth.small_case(N=64, S=3, M=M, B=B, H=110, W=121, seed=43))
+    _check_grads(c, c.engine(wave_budget=budget))
