@@ -59,27 +59,199 @@ __global__ __launch_bounds__(256) void k_rz_filter(float* v, int S, size_t HW, R
 }
 
 // The depth filter as an S x S matrix: B[s][s'] = sum of the taps w_k with
-// mirror(s + k) = s' (the mirrored boundary folded in).  One thread per entry.
-__global__ void k_rz_matrix(RzTaps taps, int S, float* Bm) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= S * S) return;
-    const int s = i / S, s2 = i % S;
-    float b = 0.f;
-    for (int k = -taps.R; k <= taps.R; ++k)
-        if (mirror_slice(s + k, S) == s2) b += taps.w[k + taps.R];
-    Bm[i] = b;
+// mirror(s + k) = s' (the mirrored boundary folded in).  A whole workgroup.
+__device__ __forceinline__ void rz_matrix(const RzTaps& taps, int S, float* Bm) {
+    for (int i = threadIdx.x; i < S * S; i += blockDim.x) {
+        const int s = i / S, s2 = i % S;
+        float b = 0.f;
+        for (int k = -taps.R; k <= taps.R; ++k)
+            if (mirror_slice(s + k, S) == s2) b += taps.w[k + taps.R];
+        Bm[i] = b;
+    }
 }
 
+// ------------------------------------------------------------ probe modes
+struct cd {
+    double re, im;
+};
+__device__ __forceinline__ cd cd_mul(cd a, cd b) { return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
+__device__ __forceinline__ cd cd_conj(cd a) { return {a.re, -a.im}; }
+__device__ __forceinline__ cd cd_add(cd a, cd b) { return {a.re + b.re, a.im + b.im}; }
+__device__ __forceinline__ cd cd_scale(cd a, double s) { return {a.re * s, a.im * s}; }
+
+struct EigLds {
+    cd A[ORTH_MAX_M * ORTH_MAX_M], V[ORTH_MAX_M * ORTH_MAX_M], e[ORTH_MAX_M / 2];
+    double c[ORTH_MAX_M / 2], s[ORTH_MAX_M / 2];
+    int p[ORTH_MAX_M / 2], q[ORTH_MAX_M / 2];
+    double lam[ORTH_MAX_M];
+    int order[ORTH_MAX_M];
+};
+
+// LDS accesses of one wave in order: what one lane wrote before is seen after
+__device__ __forceinline__ void eig_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Eigenvectors of the Hermitian overlap matrix (summed from the chunk
+// partials) by complex Jacobi rotations in double, by one wave (lane k =
+// 0..63), then ordered by decreasing eigenvalue; each eigenvector is scaled by
+// a unit phase so that its largest-magnitude entry (first of equals) is real
+// and positive.  Writes V (M x M, column k = mode k's mixing coefficients) as
+// float pairs and the eigenvalues.
+// A sweep is m - 1 rounds (m = M rounded up to even) of m / 2 disjoint pairs
+// in the round-robin order, whose rotations are formed and applied together:
+// the kernel is one serial chain of square roots and divisions, M (M - 1) / 2
+// per sweep when the pairs follow one another (six modes: 61 us) and m - 1
+// this way.
+__device__ void probe_eig(EigLds& L, int k, const cd* part, int nchunk, int M, float2* Vout, double* lam_out) {
+    const int m = M + (M & 1), K = m / 2;
+    cd *A = L.A, *V = L.V;
+    for (int i = k; i < M * M; i += 64) V[i] = {(i / M) == (i % M) ? 1.0 : 0.0, 0.0};
+    // overlap matrix from the chunk sums (fixed order)
+    for (int pid = k; pid < M * (M + 1) / 2; pid += 64) {
+        int pr = pid, a = 0;
+        while (pr >= M - a) { pr -= M - a; ++a; }
+        const int b = a + pr;
+        double re = 0.0, im = 0.0;
+        for (int ch = 0; ch < nchunk; ++ch) {
+            re += part[(size_t)pid * nchunk + ch].re;
+            im += part[(size_t)pid * nchunk + ch].im;
+        }
+        A[a * M + b] = {re, a == b ? 0.0 : im};
+        A[b * M + a] = {re, a == b ? 0.0 : -im};
+    }
+    eig_sync();
+    double scale = 0.0;
+    for (int i = 0; i < M; ++i) scale += A[i * M + i].re;
+    const double tol = 1e-28 * scale * scale;     // off-diagonal norm 1e-14 of the trace
+    for (int sweep = 0; sweep < 64; ++sweep) {
+        double off = 0.0;
+        for (int i = k; i < M * M; i += 64)
+            if (i / M != i % M) off += A[i].re * A[i].re + A[i].im * A[i].im;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) off += __shfl_xor(off, o, 64);
+        if (off <= tol) break;                    // the same sum in every lane
+        for (int r = 0; r < m - 1; ++r) {
+            // round r of the round robin: m - 1 stays, the others rotate
+            if (k < K) {
+                int p = k == 0 ? m - 1 : (r + k) % (m - 1), q = k == 0 ? r : (r - k + m - 1) % (m - 1);
+                if (p > q) { const int t = p; p = q; q = t; }
+                double c = 1.0, s = 0.0;
+                cd e = {1.0, 0.0};
+                const cd apq = q < M ? A[p * M + q] : cd{0.0, 0.0};
+                const double mag = sqrt(apq.re * apq.re + apq.im * apq.im);
+                if (mag > 0.0) {
+                    // U = D P: D_qq = exp(-i alpha) makes the (p, q) entry real
+                    // (alpha = arg a_pq), P the real Jacobi rotation that zeroes it
+                    e = {apq.re / mag, -apq.im / mag};     // exp(-i alpha)
+                    const double zeta = (A[q * M + q].re - A[p * M + p].re) / (2.0 * mag);
+                    const double t = (zeta >= 0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(zeta * zeta + 1.0));
+                    c = 1.0 / sqrt(t * t + 1.0);
+                    s = t * c;
+                }
+                L.c[k] = c; L.s[k] = s; L.e[k] = e;
+                L.p[k] = p;
+                L.q[k] = mag > 0.0 ? q : -1;      // -1: nothing to rotate
+            }
+            eig_sync();
+            // columns p, q of A U and of V U
+            for (int i = k; i < K * M; i += 64) {
+                const int pr = i / M, row = i % M, p = L.p[pr], q = L.q[pr];
+                if (q < 0) continue;
+                const double c = L.c[pr], s = L.s[pr];
+                const cd e = L.e[pr];
+                const cd ap = A[row * M + p], aq = cd_mul(A[row * M + q], e);
+                A[row * M + p] = {c * ap.re - s * aq.re, c * ap.im - s * aq.im};
+                A[row * M + q] = {s * ap.re + c * aq.re, s * ap.im + c * aq.im};
+                const cd vp = V[row * M + p], vq = cd_mul(V[row * M + q], e);
+                V[row * M + p] = {c * vp.re - s * vq.re, c * vp.im - s * vq.im};
+                V[row * M + q] = {s * vp.re + c * vq.re, s * vp.im + c * vq.im};
+            }
+            eig_sync();
+            // rows p, q of U^H (A U); the rotated entry is zero, the diagonal real
+            for (int i = k; i < K * M; i += 64) {
+                const int pr = i / M, col = i % M, p = L.p[pr], q = L.q[pr];
+                if (q < 0) continue;
+                const double c = L.c[pr], s = L.s[pr];
+                const cd bp = A[p * M + col], bq = cd_mul(A[q * M + col], cd_conj(L.e[pr]));
+                cd np = {c * bp.re - s * bq.re, c * bp.im - s * bq.im};
+                cd nq = {s * bp.re + c * bq.re, s * bp.im + c * bq.im};
+                if (col == p) { np.im = 0.0; nq = {0.0, 0.0}; }
+                if (col == q) { nq.im = 0.0; np = {0.0, 0.0}; }
+                A[p * M + col] = np;
+                A[q * M + col] = nq;
+            }
+            eig_sync();
+        }
+    }
+    if (k < M) L.lam[k] = A[k * M + k].re;
+    eig_sync();
+    if (k < M) {                                          // rank by decreasing eigenvalue, ties in index order
+        int rank = 0;
+        for (int j = 0; j < M; ++j) rank += L.lam[j] > L.lam[k] || (L.lam[j] == L.lam[k] && j < k) ? 1 : 0;
+        L.order[rank] = k;
+    }
+    eig_sync();
+    if (k < M) {                                          // lane k: output column k
+        const int src = L.order[k];
+        int best = 0;
+        double bm = -1.0;
+        for (int a = 0; a < M; ++a) {
+            const cd x = V[a * M + src];
+            const double v = x.re * x.re + x.im * x.im;
+            if (v > bm) { bm = v; best = a; }
+        }
+        const cd x = V[best * M + src];
+        const double r = sqrt(x.re * x.re + x.im * x.im);
+        const cd ph = r > 0 ? cd{x.re / r, -x.im / r} : cd{1.0, 0.0};
+        for (int a = 0; a < M; ++a) {
+            const cd y = cd_mul(V[a * M + src], ph);
+            Vout[a * M + k] = make_float2((float)y.re, (float)y.im);
+        }
+        lam_out[k] = L.lam[src];
+    }
+}
+
+// the arguments of probe_eig (M = 0: no orthogonalisation in this call)
+struct EigArgs {
+    const cd* part;
+    int nchunk, M;
+    float2* V;
+    double* lam;
+};
+__global__ __launch_bounds__(64) void k_probe_eig(EigArgs a) {
+    __shared__ EigLds L;
+    probe_eig(L, threadIdx.x, a.part, a.nchunk, a.M, a.V, a.lam);
+}
+
+// ------------------------------------------------------------ r_z filter
 // r_z filter for S <= RZ_REG_S: a thread keeps its pixel's column in
 // registers and forms out = B x with the matrix read through the scalar
-// cache (every thread of the launch reads the same entries).
+// cache (every thread of the launch reads the same entries).  EIG: workgroup
+// (0, 0) runs the probe modes' eigen-solve instead, one wave of serial double
+// arithmetic that the filter's stream through memory hides ((0, 1) is idle).
 constexpr int RZ_REG_S = 32;
+template <bool EIG> __device__ __forceinline__ bool rz_eig_block(const EigArgs& eig) {
+    if constexpr (EIG) {
+        __shared__ EigLds L;
+        if (blockIdx.x == 0) {
+            if (blockIdx.y == 0 && threadIdx.x < 64)
+                probe_eig(L, threadIdx.x, eig.part, eig.nchunk, eig.M, eig.V, eig.lam);
+            return true;
+        }
+    }
+    return false;
+}
+template <bool EIG>
 __global__ __launch_bounds__(256) void k_rz_filter_reg(float* v0, float* v1, int S, size_t HW,
-                                                       const float* __restrict__ Bm, int positive1) {
+                                                       const float* __restrict__ Bm, int positive1, EigArgs eig) {
+    if (rz_eig_block<EIG>(eig)) return;
     // blockIdx.y: 0 filters v0 (amplitude), 1 filters v1 (phase; clipped at 0 with positive1)
     float* const v = blockIdx.y ? v1 : v0;
     const int positive = blockIdx.y ? positive1 : 0;
-    const size_t px = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const size_t px = (size_t)(blockIdx.x - (EIG ? 1 : 0)) * blockDim.x + threadIdx.x;
     if (px >= HW) return;
     float x[RZ_REG_S];
 #pragma unroll
@@ -99,11 +271,13 @@ __global__ __launch_bounds__(256) void k_rz_filter_reg(float* v0, float* v1, int
 
 // The same for fields whose slice size is a multiple of 4: a thread owns four
 // consecutive pixels (16-byte reads and writes).
+template <bool EIG>
 __global__ __launch_bounds__(256) void k_rz_filter_reg4(float* v0, float* v1, int S, size_t HW,
-                                                        const float* __restrict__ Bm, int positive1) {
+                                                        const float* __restrict__ Bm, int positive1, EigArgs eig) {
+    if (rz_eig_block<EIG>(eig)) return;
     float* const v = blockIdx.y ? v1 : v0;
     const int positive = blockIdx.y ? positive1 : 0;
-    const size_t px = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
+    const size_t px = ((size_t)(blockIdx.x - (EIG ? 1 : 0)) * blockDim.x + threadIdx.x) * 4;
     if (px >= HW) return;
     float4 x[RZ_REG_S];
 #pragma unroll
@@ -464,21 +638,18 @@ inline size_t kz_lds_bytes(const KzPass& a) {
     return (nl * (a.gi == 1 ? a.ls : a.n) + a.n) * sizeof(float2);
 }
 
-// ------------------------------------------------------------ probe modes
-struct cd {
-    double re, im;
-};
-__device__ __forceinline__ cd cd_mul(cd a, cd b) { return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
-__device__ __forceinline__ cd cd_conj(cd a) { return {a.re, -a.im}; }
-__device__ __forceinline__ cd cd_add(cd a, cd b) { return {a.re + b.re, a.im + b.im}; }
-__device__ __forceinline__ cd cd_scale(cd a, double s) { return {a.re * s, a.im * s}; }
-
 // Partial overlaps conj(P_m(r)) P_n(r) summed over one chunk of GRAM_CHUNK
-// pixels, in double: one workgroup per (chunk, pair m <= n), written to
-// part[pair * nchunk + chunk]; the eigen kernel adds the chunks in order.
-__global__ __launch_bounds__(256) void k_probe_gram(const float2* P, int M, int NN, cd* part) {
-    const int chunk = blockIdx.x, nchunk = gridDim.x;
-    int pair = blockIdx.y, m = 0;
+// pixels, in double: workgroup (pair m <= n) * nchunk + chunk, written to
+// part[pair * nchunk + chunk]; the eigen kernel adds the chunks in order.  A
+// last workgroup (with Bm) forms the depth filter's matrix.
+__global__ __launch_bounds__(256) void k_constrain_head(const float2* P, int M, int NN, cd* part, int nchunk,
+                                                        RzTaps taps, int S, float* Bm) {
+    if (Bm && blockIdx.x == gridDim.x - 1) {
+        rz_matrix(taps, S, Bm);
+        return;
+    }
+    const int chunk = blockIdx.x % nchunk;
+    int pair = blockIdx.x / nchunk, m = 0;
     const int pair_id = pair;
     while (pair >= M - m) { pair -= M - m; ++m; }
     const int n = m + pair;
@@ -503,119 +674,6 @@ __global__ __launch_bounds__(256) void k_probe_gram(const float2* P, int M, int 
         __syncthreads();
     }
     if (threadIdx.x == 0) part[(size_t)pair_id * nchunk + chunk] = {sr[0], si[0]};
-}
-
-// Eigenvectors of the Hermitian overlap matrix (summed from the chunk
-// partials) by cyclic complex Jacobi
-// rotations in double (one workgroup, thread k owning row / column k), then
-// ordered by decreasing eigenvalue; each eigenvector is scaled by a unit
-// phase so that its largest-magnitude entry (first of equals) is real and
-// positive.  Writes V (M x M, column k = mode k's mixing coefficients) as
-// float pairs and the eigenvalues.
-__global__ __launch_bounds__(64) void k_probe_eig(const cd* part, int nchunk, int M, float2* Vout, double* lam_out) {
-    __shared__ cd A[ORTH_MAX_M * ORTH_MAX_M], V[ORTH_MAX_M * ORTH_MAX_M];
-    __shared__ double lam[ORTH_MAX_M];
-    __shared__ int order[ORTH_MAX_M];
-    __shared__ double off;
-    const int k = threadIdx.x;
-    for (int i = k; i < M * M; i += blockDim.x) V[i] = {(i / M) == (i % M) ? 1.0 : 0.0, 0.0};
-    // overlap matrix from the chunk sums (fixed order)
-    for (int pid = k; pid < M * (M + 1) / 2; pid += blockDim.x) {
-        int pr = pid, m = 0;
-        while (pr >= M - m) { pr -= M - m; ++m; }
-        const int n = m + pr;
-        double re = 0.0, im = 0.0;
-        for (int ch = 0; ch < nchunk; ++ch) {
-            re += part[(size_t)pid * nchunk + ch].re;
-            im += part[(size_t)pid * nchunk + ch].im;
-        }
-        A[m * M + n] = {re, m == n ? 0.0 : im};
-        A[n * M + m] = {re, m == n ? 0.0 : -im};
-    }
-    __syncthreads();
-    double scale = 0.0;
-    for (int i = 0; i < M; ++i) scale += A[i * M + i].re;
-    const double tol = 1e-28 * scale * scale;     // off-diagonal norm 1e-14 of the trace
-    for (int sweep = 0; sweep < 64; ++sweep) {
-        if (k == 0) {
-            double s = 0.0;
-            for (int i = 0; i < M; ++i)
-                for (int j = 0; j < M; ++j)
-                    if (i != j) s += A[i * M + j].re * A[i * M + j].re + A[i * M + j].im * A[i * M + j].im;
-            off = s;
-        }
-        __syncthreads();
-        if (off <= tol) break;
-        for (int p = 0; p < M - 1; ++p)
-            for (int q = p + 1; q < M; ++q) {
-                const cd apq = A[p * M + q];
-                const double mag = sqrt(apq.re * apq.re + apq.im * apq.im);
-                if (mag == 0.0) continue;                       // uniform: every thread reads the same value
-                // U = D P: D_qq = exp(-i alpha) makes the (p, q) entry real
-                // (alpha = arg a_pq), P the real Jacobi rotation that zeroes it
-                const cd e = {apq.re / mag, -apq.im / mag};     // exp(-i alpha)
-                const double zeta = (A[q * M + q].re - A[p * M + p].re) / (2.0 * mag);
-                const double t = (zeta >= 0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(zeta * zeta + 1.0));
-                const double c = 1.0 / sqrt(t * t + 1.0), s = t * c;
-                __syncthreads();
-                // columns p, q of A U and of V U (thread k: row k)
-                if (k < M) {
-                    const cd akp = A[k * M + p], akq = cd_mul(A[k * M + q], e);
-                    A[k * M + p] = {c * akp.re - s * akq.re, c * akp.im - s * akq.im};
-                    A[k * M + q] = {s * akp.re + c * akq.re, s * akp.im + c * akq.im};
-                    const cd vkp = V[k * M + p], vkq = cd_mul(V[k * M + q], e);
-                    V[k * M + p] = {c * vkp.re - s * vkq.re, c * vkp.im - s * vkq.im};
-                    V[k * M + q] = {s * vkp.re + c * vkq.re, s * vkp.im + c * vkq.im};
-                }
-                __syncthreads();
-                // rows p, q of U^H (A U) (thread k: column k)
-                if (k < M) {
-                    const cd bpk = A[p * M + k], bqk = cd_mul(A[q * M + k], cd_conj(e));
-                    A[p * M + k] = {c * bpk.re - s * bqk.re, c * bpk.im - s * bqk.im};
-                    A[q * M + k] = {s * bpk.re + c * bqk.re, s * bpk.im + c * bqk.im};
-                }
-                __syncthreads();
-                if (k == 0) {
-                    A[p * M + q] = {0.0, 0.0};
-                    A[q * M + p] = {0.0, 0.0};
-                    A[p * M + p].im = 0.0;
-                    A[q * M + q].im = 0.0;
-                }
-                __syncthreads();
-            }
-    }
-    if (k == 0) {
-        for (int i = 0; i < M; ++i) {
-            lam[i] = A[i * M + i].re;
-            order[i] = i;
-        }
-        for (int i = 0; i < M; ++i)                       // selection sort, decreasing; stable for ties
-            for (int j = i + 1; j < M; ++j)
-                if (lam[order[j]] > lam[order[i]]) {
-                    const int tmp = order[i];
-                    order[i] = order[j];
-                    order[j] = tmp;
-                }
-    }
-    __syncthreads();
-    if (k < M) {                                          // thread k: output column k
-        const int src = order[k];
-        int best = 0;
-        double bm = -1.0;
-        for (int m = 0; m < M; ++m) {
-            const cd x = V[m * M + src];
-            const double a = x.re * x.re + x.im * x.im;
-            if (a > bm) { bm = a; best = m; }
-        }
-        const cd x = V[best * M + src];
-        const double r = sqrt(x.re * x.re + x.im * x.im);
-        const cd ph = r > 0 ? cd{x.re / r, -x.im / r} : cd{1.0, 0.0};
-        for (int m = 0; m < M; ++m) {
-            const cd y = cd_mul(V[m * M + src], ph);
-            Vout[m * M + k] = make_float2((float)y.re, (float)y.im);
-        }
-        lam_out[k] = lam[src];
-    }
 }
 
 // Q_k(r) = sum_m V[m][k] P_m(r), in place: a workgroup stages the M values of

@@ -1736,6 +1736,31 @@ ptyr_status ptyr_constrain(ptyr_ctx* c, float* amp, float* phase, float* probe, 
     const hipStream_t st = c->stream;
     const size_t HW = (size_t)g.H * g.W;
     const int nob = obj_modes(g);
+    const bool filter = rz && g.S > 1, filter_reg = filter && g.S <= RZ_REG_S;
+    const bool orth = cfg->probe_orthogonal && g.M > 1;
+    const int NN = g.N * g.N, nchunk = (NN + GRAM_CHUNK - 1) / GRAM_CHUNK;
+    RzTaps taps{};
+    if (filter) {
+        // taps in double, normalised, then rounded (the same on every call)
+        taps.R = (int)ceil(4.0 * (double)cfg->rz_sigma);
+        double w[2 * RZ_MAX_R + 1], sum = 0.0;
+        for (int k = -taps.R; k <= taps.R; ++k) {
+            w[k + taps.R] = exp(-(double)k * k / (2.0 * (double)cfg->rz_sigma * cfg->rz_sigma));
+            sum += w[k + taps.R];
+        }
+        for (int k = 0; k <= 2 * taps.R; ++k) taps.w[k] = (float)(w[k] / sum);
+    }
+    // the probe modes' overlaps and the depth filter's matrix in one launch;
+    // the eigen-solve then rides on the first depth-filter launch
+    float* const Bm = at<float>(c, c->L.rzmat);
+    cd* const part = at<cd>(c, c->L.cons);
+    float2* const V = reinterpret_cast<float2*>(part + (size_t)ORTH_MAX_M * (ORTH_MAX_M + 1) / 2 * GRAM_MAX_CHUNKS);
+    EigArgs eig{part, nchunk, orth ? g.M : 0, V, reinterpret_cast<double*>(V + ORTH_MAX_M * ORTH_MAX_M)};
+    const unsigned ngram = orth ? (unsigned)(nchunk * (g.M * (g.M + 1) / 2)) : 0;
+    if (ngram || filter_reg)
+        hipLaunchKernelGGL(k_constrain_head, dim3(ngram + (filter_reg ? 1 : 0)), dim3(256), 0, st,
+                           reinterpret_cast<const float2*>(probe), g.M, NN, part, nchunk, taps, g.S,
+                           filter_reg ? Bm : nullptr);
     // every object mode is filtered on its own (S x H x W each)
     for (int ob = 0; ob < nob; ++ob) {
         float* const amp_o = amp ? amp + (size_t)ob * g.S * HW : nullptr;
@@ -1765,55 +1790,40 @@ ptyr_status ptyr_constrain(ptyr_ctx* c, float* amp, float* phase, float* probe, 
             hipLaunchKernelGGL((k_kz_lines<KZ_OUT_FIELDS, +1>), dim3(gx), blk, kz_lds_bytes(px), st, zb, amp_o,
                                phase_o, px, kw);
         }
-        if (rz && g.S > 1) {
-            // taps in double, normalised, then rounded (the same on every call)
-            RzTaps t;
-            t.R = (int)ceil(4.0 * (double)cfg->rz_sigma);
-            double w[2 * RZ_MAX_R + 1], sum = 0.0;
-            for (int k = -t.R; k <= t.R; ++k) {
-                w[k + t.R] = exp(-(double)k * k / (2.0 * (double)cfg->rz_sigma * cfg->rz_sigma));
-                sum += w[k + t.R];
-            }
-            for (int k = 0; k <= 2 * t.R; ++k) t.w[k] = (float)(w[k] / sum);
+        if (filter) {
             float* fields[2] = {amp_o, phase_o};
-            if (g.S <= RZ_REG_S) {
-                float* Bm = at<float>(c, c->L.rzmat);
-                hipLaunchKernelGGL(k_rz_matrix, dim3((g.S * g.S + 255) / 256), dim3(256), 0, st, t, g.S, Bm);
+            if (filter_reg) {
                 const bool vec4 = HW % 4 == 0 && reinterpret_cast<uintptr_t>(amp_o) % 16 == 0 &&
                                   reinterpret_cast<uintptr_t>(phase_o) % 16 == 0;
                 // amplitude (grid row 0) and phase (row 1) in one launch
-                const dim3 grid((unsigned)((HW / (vec4 ? 4 : 1) + 255) / 256), 2);
-                const int pos = cfg->phase_positive ? 1 : 0;
+                const bool with_eig = eig.M > 0;
+                const dim3 grid((unsigned)((HW / (vec4 ? 4 : 1) + 255) / 256) + (with_eig ? 1 : 0), 2);
                 TimedLaunch tl(c, PTYR_K_RZ, st);
-                if (vec4)
-                    hipLaunchKernelGGL(k_rz_filter_reg4, grid, dim3(256), 0, st, fields[0], fields[1], g.S, HW, Bm, pos);
-                else
-                    hipLaunchKernelGGL(k_rz_filter_reg, grid, dim3(256), 0, st, fields[0], fields[1], g.S, HW, Bm, pos);
+                const auto kernel = vec4 ? (with_eig ? k_rz_filter_reg4<true> : k_rz_filter_reg4<false>)
+                                         : (with_eig ? k_rz_filter_reg<true> : k_rz_filter_reg<false>);
+                hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, fields[0], fields[1], g.S, HW, Bm,
+                                   cfg->phase_positive ? 1 : 0, eig);
+                eig.M = 0;                           // solved
             } else {
                 const int T = rz_threads(g.S);
                 const dim3 grid((unsigned)((HW + T - 1) / T));
                 const size_t lds = (size_t)g.S * T * sizeof(float);
                 for (int f = 0; f < 2; ++f) {
                     TimedLaunch tl(c, PTYR_K_RZ, st);
-                    hipLaunchKernelGGL(k_rz_filter, grid, dim3(T), lds, st, fields[f], g.S, HW, t,
+                    hipLaunchKernelGGL(k_rz_filter, grid, dim3(T), lds, st, fields[f], g.S, HW, taps,
                                        f == 1 && cfg->phase_positive ? 1 : 0);
                 }
             }
         }
     }
-    if (!(rz && g.S > 1) && cfg->phase_positive)
+    if (!filter && cfg->phase_positive)
         hipLaunchKernelGGL(k_clip_negative, dim3(grid_for((size_t)nob * g.S * HW)), dim3(256), 0, st, phase,
                            (size_t)nob * g.S * HW);
-    if (cfg->probe_orthogonal && g.M > 1) {
-        const int M = g.M, NN = g.N * g.N, nchunk = (NN + GRAM_CHUNK - 1) / GRAM_CHUNK;
-        cd* part = at<cd>(c, c->L.cons);
-        float2* V = reinterpret_cast<float2*>(part + (size_t)ORTH_MAX_M * (ORTH_MAX_M + 1) / 2 * GRAM_MAX_CHUNKS);
-        double* lam = reinterpret_cast<double*>(V + ORTH_MAX_M * ORTH_MAX_M);
-        float2* P = reinterpret_cast<float2*>(probe);
-        hipLaunchKernelGGL(k_probe_gram, dim3(nchunk, M * (M + 1) / 2), dim3(256), 0, st, P, M, NN, part);
-        hipLaunchKernelGGL(k_probe_eig, dim3(1), dim3(64), 0, st, part, nchunk, M, V, lam);
-        const size_t lds = ((size_t)M * 256 + (size_t)M * M) * sizeof(float2);
-        hipLaunchKernelGGL(k_probe_mix, dim3((NN + 255) / 256), dim3(256), lds, st, P, M, NN, V);
+    if (orth) {
+        if (eig.M > 0) hipLaunchKernelGGL(k_probe_eig, dim3(1), dim3(64), 0, st, eig);
+        const size_t lds = ((size_t)g.M * 256 + (size_t)g.M * g.M) * sizeof(float2);
+        hipLaunchKernelGGL(k_probe_mix, dim3((NN + 255) / 256), dim3(256), lds, st, reinterpret_cast<float2*>(probe),
+                           g.M, NN, V);
     }
     return hipGetLastError() == hipSuccess ? PTYR_OK : PTYR_E_DEVICE;
 }

@@ -5,6 +5,8 @@ import pytest
 
 from paper_2505_07814_amd import synth
 
+from oracle import constraints as oc
+from test_gpu_constraints import T, engine, rz_bound
 from test_gpu_parity import Case, _check_grads
 
 pytestmark = pytest.mark.gpu
@@ -26,3 +28,27 @@ def test_gradient_by_chains_per_compute_unit(B, M, budget):
     print(f"gradient N=64 S=3 B={B} M={M} budget={budget}", flush=True)
     c = Case(synth.small_case(N=64, S=3, M=M, B=B, H=110, W=121, seed=43))
     _check_grads(c, c.engine(wave_budget=budget))
+
+
+@pytest.mark.parametrize("S,H,W,M", [(5, 64, 66, 2), (5, 65, 67, 7), (17, 64, 66, 24), (33, 64, 64, 3)])
+def test_orthogonalisation_beside_the_depth_filter(S, H, W, M):
+    """The eigen-solve inside the depth filter's launch (both filter kernels),
+    after it (deep stacks), for odd and even numbers of modes."""
+    print(f"rz + orthogonalisation S={S} {H}x{W} M={M}", flush=True)
+    rng = np.random.default_rng(S * M)
+    amp = rng.uniform(0.5, 1.5, (S, H, W)).astype(np.float32)
+    ph = rng.uniform(-0.5, 1.0, (S, H, W)).astype(np.float32)
+    scale = 1.0 / (1 + np.arange(M))[:, None, None]              # well-separated powers
+    probe = (scale * (rng.standard_normal((M, 64, 64)) + 1j * rng.standard_normal((M, 64, 64)))).astype(np.complex64)
+    eng = engine(S, H, W, 64, M)
+    a, p, P = T(amp), T(ph), T(probe)
+    eng.constrain(a, p, P, rz_sigma=1.0, phase_positive=True, probe_orthogonal=True)
+    eng.sync()
+    ra, rp, rP = oc.apply(amp, ph, probe, rz_sigma=1.0, phase_positive=True, probe_orthogonal=True)
+    assert np.max(np.abs(a.cpu().numpy() - ra)) <= rz_bound(1.0, amp)
+    assert np.max(np.abs(p.cpu().numpy() - rp)) <= rz_bound(1.0, ph)
+    got = P.cpu().numpy()
+    for m in range(M):                                           # up to each mode's unit phase
+        u = np.vdot(got[m], rP[m])
+        d = np.linalg.norm(got[m] * (u / abs(u)) - rP[m]) / np.linalg.norm(rP[m])
+        assert d <= 1e-5, (m, d)
