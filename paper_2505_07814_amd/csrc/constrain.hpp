@@ -80,9 +80,13 @@ __device__ __forceinline__ cd cd_add(cd a, cd b) { return {a.re + b.re, a.im + b
 __device__ __forceinline__ cd cd_scale(cd a, double s) { return {a.re * s, a.im * s}; }
 
 struct EigLds {
-    cd A[ORTH_MAX_M * ORTH_MAX_M], V[ORTH_MAX_M * ORTH_MAX_M], e[ORTH_MAX_M / 2];
-    double c[ORTH_MAX_M / 2], s[ORTH_MAX_M / 2];
-    int p[ORTH_MAX_M / 2], q[ORTH_MAX_M / 2];
+    cd A[ORTH_MAX_M * ORTH_MAX_M], V[ORTH_MAX_M * ORTH_MAX_M];
+    struct Rot {                     // the pairs' rotations of one round
+        cd e;
+        double c, s;
+        int p, q;
+    } rot[2][ORTH_MAX_M / 2];
+    int done;
     double lam[ORTH_MAX_M];
     int order[ORTH_MAX_M];
 };
@@ -94,9 +98,27 @@ __device__ __forceinline__ void eig_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// 1 / sqrt(x) and 1 / x for normal positive x: the hardware's estimate and two
+// Newton steps (each squares the relative error, about 2^-26 to start with).
+// The rotations' chain of library square roots and divisions was most of the
+// eigen-solve's time.
+__device__ __forceinline__ double rsqrt_nr(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+    return y;
+}
+__device__ __forceinline__ double rcp_nr(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) y = fma(y, fma(-x, y, 1.0), y);
+    return y;
+}
+
 // Eigenvectors of the Hermitian overlap matrix (summed from the chunk
-// partials) by complex Jacobi rotations in double, by one wave (lane k =
-// 0..63), then ordered by decreasing eigenvalue; each eigenvector is scaled by
+// partials) by complex Jacobi rotations in double, by a workgroup of at least
+// two waves, of which wave 0 rotates the matrix and wave 1 the vectors (lane k
+// = 0..63 of either), then ordered by decreasing eigenvalue; each eigenvector is scaled by
 // a unit phase so that its largest-magnitude entry (first of equals) is real
 // and positive.  Writes V (M x M, column k = mode k's mixing coefficients) as
 // float pairs and the eigenvalues.
@@ -105,87 +127,104 @@ __device__ __forceinline__ void eig_sync() {
 // the kernel is one serial chain of square roots and divisions, M (M - 1) / 2
 // per sweep when the pairs follow one another (six modes: 61 us) and m - 1
 // this way.
-__device__ void probe_eig(EigLds& L, int k, const cd* part, int nchunk, int M, float2* Vout, double* lam_out) {
+__device__ void probe_eig(EigLds& L, const cd* part, int nchunk, int M, float2* Vout, double* lam_out) {
+    const int k = threadIdx.x % 64, wave = threadIdx.x / 64;
     const int m = M + (M & 1), K = m / 2;
     cd *A = L.A, *V = L.V;
-    for (int i = k; i < M * M; i += 64) V[i] = {(i / M) == (i % M) ? 1.0 : 0.0, 0.0};
-    // overlap matrix from the chunk sums (fixed order)
-    for (int pid = k; pid < M * (M + 1) / 2; pid += 64) {
-        int pr = pid, a = 0;
-        while (pr >= M - a) { pr -= M - a; ++a; }
-        const int b = a + pr;
-        double re = 0.0, im = 0.0;
-        for (int ch = 0; ch < nchunk; ++ch) {
-            re += part[(size_t)pid * nchunk + ch].re;
-            im += part[(size_t)pid * nchunk + ch].im;
+    if (wave == 1)
+        for (int i = k; i < M * M; i += 64) V[i] = {(i / M) == (i % M) ? 1.0 : 0.0, 0.0};
+    double tol = 0.0, small = 0.0;
+    if (wave == 0) {
+        // overlap matrix from the chunk sums (fixed order)
+        for (int pid = k; pid < M * (M + 1) / 2; pid += 64) {
+            int pr = pid, a = 0;
+            while (pr >= M - a) { pr -= M - a; ++a; }
+            const int b = a + pr;
+            double re = 0.0, im = 0.0;
+            for (int ch = 0; ch < nchunk; ++ch) {
+                re += part[(size_t)pid * nchunk + ch].re;
+                im += part[(size_t)pid * nchunk + ch].im;
+            }
+            A[a * M + b] = {re, a == b ? 0.0 : im};
+            A[b * M + a] = {re, a == b ? 0.0 : -im};
         }
-        A[a * M + b] = {re, a == b ? 0.0 : im};
-        A[b * M + a] = {re, a == b ? 0.0 : -im};
+        eig_sync();
+        double scale = 0.0;
+        for (int i = 0; i < M; ++i) scale += A[i * M + i].re;
+        tol = 1e-28 * scale * scale;              // off-diagonal norm 1e-14 of the trace
+        small = fmax(1e-6 * tol / (M * M), 1e-280);   // entries that cannot matter to it stay (and none is denormal)
     }
-    eig_sync();
-    double scale = 0.0;
-    for (int i = 0; i < M; ++i) scale += A[i * M + i].re;
-    const double tol = 1e-28 * scale * scale;     // off-diagonal norm 1e-14 of the trace
+    int buf = 0;
     for (int sweep = 0; sweep < 64; ++sweep) {
-        double off = 0.0;
-        for (int i = k; i < M * M; i += 64)
-            if (i / M != i % M) off += A[i].re * A[i].re + A[i].im * A[i].im;
+        if (wave == 0) {
+            double off = 0.0;
+            for (int i = k; i < M * M; i += 64)
+                if (i / M != i % M) off += A[i].re * A[i].re + A[i].im * A[i].im;
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) off += __shfl_xor(off, o, 64);
-        if (off <= tol) break;                    // the same sum in every lane
-        for (int r = 0; r < m - 1; ++r) {
+            for (int o = 32; o > 0; o >>= 1) off += __shfl_xor(off, o, 64);
+            if (k == 0) L.done = off <= tol;
+        }
+        __syncthreads();
+        if (L.done) break;
+        for (int r = 0; r < m - 1; ++r, buf ^= 1) {
             // round r of the round robin: m - 1 stays, the others rotate
-            if (k < K) {
+            EigLds::Rot* rot = L.rot[buf];
+            if (wave == 0 && k < K) {
                 int p = k == 0 ? m - 1 : (r + k) % (m - 1), q = k == 0 ? r : (r - k + m - 1) % (m - 1);
                 if (p > q) { const int t = p; p = q; q = t; }
-                double c = 1.0, s = 0.0;
-                cd e = {1.0, 0.0};
+                EigLds::Rot w{{1.0, 0.0}, 1.0, 0.0, p, -1};             // q = -1: nothing to rotate
                 const cd apq = q < M ? A[p * M + q] : cd{0.0, 0.0};
-                const double mag = sqrt(apq.re * apq.re + apq.im * apq.im);
-                if (mag > 0.0) {
+                const double mag2 = apq.re * apq.re + apq.im * apq.im;
+                if (mag2 > small) {
                     // U = D P: D_qq = exp(-i alpha) makes the (p, q) entry real
                     // (alpha = arg a_pq), P the real Jacobi rotation that zeroes it
-                    e = {apq.re / mag, -apq.im / mag};     // exp(-i alpha)
-                    const double zeta = (A[q * M + q].re - A[p * M + p].re) / (2.0 * mag);
-                    const double t = (zeta >= 0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(zeta * zeta + 1.0));
-                    c = 1.0 / sqrt(t * t + 1.0);
-                    s = t * c;
+                    const double inv = rsqrt_nr(mag2);
+                    w.e = {apq.re * inv, -apq.im * inv};                // exp(-i alpha)
+                    const double zeta = (A[q * M + q].re - A[p * M + p].re) * (0.5 * inv);
+                    const double az = fmin(fabs(zeta), 1e100), h = fma(az, az, 1.0);
+                    const double t = copysign(rcp_nr(fma(h, rsqrt_nr(h), az)), zeta);
+                    w.c = rsqrt_nr(fma(t, t, 1.0));
+                    w.s = t * w.c;
+                    w.q = q;
                 }
-                L.c[k] = c; L.s[k] = s; L.e[k] = e;
-                L.p[k] = p;
-                L.q[k] = mag > 0.0 ? q : -1;      // -1: nothing to rotate
+                rot[k] = w;
             }
-            eig_sync();
-            // columns p, q of A U and of V U
-            for (int i = k; i < K * M; i += 64) {
-                const int pr = i / M, row = i % M, p = L.p[pr], q = L.q[pr];
-                if (q < 0) continue;
-                const double c = L.c[pr], s = L.s[pr];
-                const cd e = L.e[pr];
-                const cd ap = A[row * M + p], aq = cd_mul(A[row * M + q], e);
-                A[row * M + p] = {c * ap.re - s * aq.re, c * ap.im - s * aq.im};
-                A[row * M + q] = {s * ap.re + c * aq.re, s * ap.im + c * aq.im};
-                const cd vp = V[row * M + p], vq = cd_mul(V[row * M + q], e);
-                V[row * M + p] = {c * vp.re - s * vq.re, c * vp.im - s * vq.im};
-                V[row * M + q] = {s * vp.re + c * vq.re, s * vp.im + c * vq.im};
+            // wave 1 is at most one round behind: it has passed this barrier
+            // before wave 0 writes this half of rot again
+            __syncthreads();
+            // columns p, q of A U (wave 0) and of V U (wave 1)
+            if (wave < 2) {
+                cd* X = wave == 0 ? A : V;
+                for (int i = k; i < K * M; i += 64) {
+                    const int pr = i / M, row = i % M;
+                    const EigLds::Rot w = rot[pr];
+                    if (w.q < 0) continue;
+                    const cd ap = X[row * M + w.p], aq = cd_mul(X[row * M + w.q], w.e);
+                    X[row * M + w.p] = {w.c * ap.re - w.s * aq.re, w.c * ap.im - w.s * aq.im};
+                    X[row * M + w.q] = {w.s * ap.re + w.c * aq.re, w.s * ap.im + w.c * aq.im};
+                }
             }
-            eig_sync();
-            // rows p, q of U^H (A U); the rotated entry is zero, the diagonal real
-            for (int i = k; i < K * M; i += 64) {
-                const int pr = i / M, col = i % M, p = L.p[pr], q = L.q[pr];
-                if (q < 0) continue;
-                const double c = L.c[pr], s = L.s[pr];
-                const cd bp = A[p * M + col], bq = cd_mul(A[q * M + col], cd_conj(L.e[pr]));
-                cd np = {c * bp.re - s * bq.re, c * bp.im - s * bq.im};
-                cd nq = {s * bp.re + c * bq.re, s * bp.im + c * bq.im};
-                if (col == p) { np.im = 0.0; nq = {0.0, 0.0}; }
-                if (col == q) { nq.im = 0.0; np = {0.0, 0.0}; }
-                A[p * M + col] = np;
-                A[q * M + col] = nq;
+            if (wave == 0) {
+                eig_sync();
+                // rows p, q of U^H (A U); the rotated entry is zero, the diagonal real
+                for (int i = k; i < K * M; i += 64) {
+                    const int pr = i / M, col = i % M;
+                    const EigLds::Rot w = rot[pr];
+                    if (w.q < 0) continue;
+                    const cd bp = A[w.p * M + col], bq = cd_mul(A[w.q * M + col], cd_conj(w.e));
+                    cd np = {w.c * bp.re - w.s * bq.re, w.c * bp.im - w.s * bq.im};
+                    cd nq = {w.s * bp.re + w.c * bq.re, w.s * bp.im + w.c * bq.im};
+                    if (col == w.p) { np.im = 0.0; nq = {0.0, 0.0}; }
+                    if (col == w.q) { nq.im = 0.0; np = {0.0, 0.0}; }
+                    A[w.p * M + col] = np;
+                    A[w.q * M + col] = nq;
+                }
+                eig_sync();
             }
-            eig_sync();
         }
     }
+    __syncthreads();
+    if (wave != 0) return;
     if (k < M) L.lam[k] = A[k * M + k].re;
     eig_sync();
     if (k < M) {                                          // rank by decreasing eigenvalue, ties in index order
@@ -221,24 +260,23 @@ struct EigArgs {
     float2* V;
     double* lam;
 };
-__global__ __launch_bounds__(64) void k_probe_eig(EigArgs a) {
+__global__ __launch_bounds__(128) void k_probe_eig(EigArgs a) {
     __shared__ EigLds L;
-    probe_eig(L, threadIdx.x, a.part, a.nchunk, a.M, a.V, a.lam);
+    probe_eig(L, a.part, a.nchunk, a.M, a.V, a.lam);
 }
 
 // ------------------------------------------------------------ r_z filter
 // r_z filter for S <= RZ_REG_S: a thread keeps its pixel's column in
 // registers and forms out = B x with the matrix read through the scalar
 // cache (every thread of the launch reads the same entries).  EIG: workgroup
-// (0, 0) runs the probe modes' eigen-solve instead, one wave of serial double
+// (0, 0) runs the probe modes' eigen-solve instead, two waves of serial double
 // arithmetic that the filter's stream through memory hides ((0, 1) is idle).
 constexpr int RZ_REG_S = 32;
 template <bool EIG> __device__ __forceinline__ bool rz_eig_block(const EigArgs& eig) {
     if constexpr (EIG) {
         __shared__ EigLds L;
         if (blockIdx.x == 0) {
-            if (blockIdx.y == 0 && threadIdx.x < 64)
-                probe_eig(L, threadIdx.x, eig.part, eig.nchunk, eig.M, eig.V, eig.lam);
+            if (blockIdx.y == 0) probe_eig(L, eig.part, eig.nchunk, eig.M, eig.V, eig.lam);
             return true;
         }
     }
@@ -271,7 +309,10 @@ __global__ __launch_bounds__(256) void k_rz_filter_reg(float* v0, float* v1, int
 
 // The same for fields whose slice size is a multiple of 4: a thread owns four
 // consecutive pixels (16-byte reads and writes).
-template <bool EIG>
+// SM: the registers' stack depth, 16 or 32 (S <= SM): at 32 the columns take
+// 142 registers, at 16 half, which leaves twice the waves to keep reads in
+// flight.
+template <bool EIG, int SM>
 __global__ __launch_bounds__(256) void k_rz_filter_reg4(float* v0, float* v1, int S, size_t HW,
                                                         const float* __restrict__ Bm, int positive1, EigArgs eig) {
     if (rz_eig_block<EIG>(eig)) return;
@@ -279,16 +320,16 @@ __global__ __launch_bounds__(256) void k_rz_filter_reg4(float* v0, float* v1, in
     const int positive = blockIdx.y ? positive1 : 0;
     const size_t px = ((size_t)(blockIdx.x - (EIG ? 1 : 0)) * blockDim.x + threadIdx.x) * 4;
     if (px >= HW) return;
-    float4 x[RZ_REG_S];
+    float4 x[SM];
 #pragma unroll
-    for (int s = 0; s < RZ_REG_S; ++s)
+    for (int s = 0; s < SM; ++s)
         x[s] = s < S ? *reinterpret_cast<const float4*>(v + (size_t)s * HW + px) : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-    for (int s = 0; s < RZ_REG_S; ++s) {
+    for (int s = 0; s < SM; ++s) {
         if (s < S) {
             float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-            for (int s2 = 0; s2 < RZ_REG_S; ++s2)
+            for (int s2 = 0; s2 < SM; ++s2)
                 if (s2 < S) {
                     const float b = Bm[s * S + s2];
                     acc.x = fmaf(b, x[s2].x, acc.x);

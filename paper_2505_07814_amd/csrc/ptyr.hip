@@ -1799,8 +1799,10 @@ ptyr_status ptyr_constrain(ptyr_ctx* c, float* amp, float* phase, float* probe, 
                 const bool with_eig = eig.M > 0;
                 const dim3 grid((unsigned)((HW / (vec4 ? 4 : 1) + 255) / 256) + (with_eig ? 1 : 0), 2);
                 TimedLaunch tl(c, PTYR_K_RZ, st);
-                const auto kernel = vec4 ? (with_eig ? k_rz_filter_reg4<true> : k_rz_filter_reg4<false>)
-                                         : (with_eig ? k_rz_filter_reg<true> : k_rz_filter_reg<false>);
+                const auto kernel =
+                    !vec4 ? (with_eig ? k_rz_filter_reg<true> : k_rz_filter_reg<false>)
+                    : g.S <= 16 ? (with_eig ? k_rz_filter_reg4<true, 16> : k_rz_filter_reg4<false, 16>)
+                                : (with_eig ? k_rz_filter_reg4<true, 32> : k_rz_filter_reg4<false, 32>);
                 hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, fields[0], fields[1], g.S, HW, Bm,
                                    cfg->phase_positive ? 1 : 0, eig);
                 eig.M = 0;                           // solved
@@ -1820,7 +1822,7 @@ ptyr_status ptyr_constrain(ptyr_ctx* c, float* amp, float* phase, float* probe, 
         hipLaunchKernelGGL(k_clip_negative, dim3(grid_for((size_t)nob * g.S * HW)), dim3(256), 0, st, phase,
                            (size_t)nob * g.S * HW);
     if (orth) {
-        if (eig.M > 0) hipLaunchKernelGGL(k_probe_eig, dim3(1), dim3(64), 0, st, eig);
+        if (eig.M > 0) hipLaunchKernelGGL(k_probe_eig, dim3(1), dim3(128), 0, st, eig);
         const size_t lds = ((size_t)g.M * 256 + (size_t)g.M * g.M) * sizeof(float2);
         hipLaunchKernelGGL(k_probe_mix, dim3((NN + 255) / 256), dim3(256), lds, st, reinterpret_cast<float2*>(probe),
                            g.M, NN, V);
