@@ -4,6 +4,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace ptyr {
 
 constexpr int RZ_MAX_R = 64;        // largest tap radius (rz_sigma <= 16)
@@ -354,47 +356,54 @@ __global__ void k_clip_negative(float* v, size_t n) {
 }
 
 // ------------------------------------------------------------ k_z filter
-// The 3-D transform of one S x H x W object stack (sides with no prime factor
-// other than 2, 3 and 5, e.g. 12 x 640 x 640) runs as line passes, each one
-// round trip through device memory: a workgroup loads a tile of lines into
-// LDS, runs every radix stage of their DFTs there (Stockham stages in place,
-// each butterfly's values held in registers across a barrier) and writes the
-// tile back.  Amplitude and phase travel as one complex field a + i phase:
-// the weight W_a is real and even in k, so the filtered real and imaginary
-// parts are the two filtered fields.  Per call: forward x (reading amplitude
-// and phase), forward y, one z pass (forward, weight, inverse), inverse y,
-// inverse x (writing amplitude and phase): five passes, 16 bytes per voxel
-// each.
+// The 3-D transform of one S x H x W object stack (sides up to 4096 with no prime factor
+// other than 2, 3 and 5, e.g. 12 x 640 x 640).  Amplitude and phase travel as
+// one complex field a + i phase: the weight W_a is real and even in k, so the
+// filtered real and imaginary parts are the two filtered fields.  The
+// transform is separable, so its axes may go in any order, and it runs as
+// three passes through device memory:
+//   1. x and z forward: a workgroup holds the S rows of one y
+//   2. y forward, weight, y inverse: a workgroup holds a few columns of one k_z
+//   3. z and x inverse
+// (five, with x and z apart, where the S rows do not fit one workgroup).  A
+// tile's lines are transformed in LDS stage by stage, one butterfly of radix
+// 2 to 15 per thread and stage, so 640 = 8 8 10 takes three stages and 12 one;
+// the first stage reads its operands straight from device memory and the last
+// writes its results there.  At most 64 registers, for two 1024-thread
+// workgroups per compute unit: with one (80 registers, five passes, four
+// stages of at most radix 8, tiles staged through LDS at both ends) every
+// barrier left the unit idle and a 12 x 640 x 640 call took 235 us; now 104 us
+// (31 + 46 + 30 us, 79 MB each).
 
-constexpr int KZ_THREADS = 1024;
-constexpr int KZ_LDS = 8192;        // complex values of LDS per workgroup (64 KiB): tile + twiddles
-constexpr int KZ_EPT = KZ_LDS / KZ_THREADS;
-constexpr int KZ_MAX_SIDE = KZ_LDS / 2;
-constexpr int KZ_MAX_RAD = 16;
-constexpr int KZ_BATCH = 8;        // loads in flight per thread
-
-enum : int { KZ_IN_FIELDS = 1, KZ_OUT_FIELDS = 2, KZ_FILTER = 4 };
-
-// One axis: the lines form `groups` groups of lpg lines; line c of group q
-// starts at q * gs + c * gc and its element i sits i * gi further.  A tile is
-// nl consecutive lines of one group (the last tile of a group may hold fewer);
-// tile t covers group t / tpg.
-struct KzPass {
-    int n, lg, ls, lpg, tpg;    // line length, log2 lines per tile, LDS row pitch (rows), lines per group, tiles per group
-    int tiles;                  // tiles of the pass (the grid is rounded up to a multiple of 8)
-    size_t gs, gc, gi;
-    int nrad;
-    unsigned long long rads;    // radix k in bits 4k .. 4k + 3
-    const float2* tw;           // exp(-2 pi i k / n), k < n
-};
-struct KzWeight {
-    int S, H, W;
-    double beta, alpha, dx, dz;
-};
+constexpr int KZ_MAX_THREADS = 1024;
+constexpr int KZ_MAX_SIDE = 4096;
+constexpr int KZ_MAX_ST = 6;                   // stages of one axis
+constexpr int KZ_LDS_MAX = 80 * 1024;          // bytes per workgroup of a pass with a choice of tile
 
 __device__ __forceinline__ float2 kz_mul_i(float2 a, int sg) {       // a * (sg i)
     return sg > 0 ? make_float2(-a.y, a.x) : make_float2(a.y, -a.x);
 }
+
+// cos and sin of 2 pi m / R at compile time (Taylor series on [-pi, pi])
+constexpr double kz_series(double x, double term, int k) {
+    double s = 0.0;
+    for (int i = k; i < k + 40; i += 2) {
+        s += term;
+        term *= -x * x / ((i + 1) * (i + 2));
+    }
+    return s;
+}
+template <int R> struct KzRoots {
+    float c[R] = {}, s[R] = {};
+    constexpr KzRoots() {
+        for (int m = 0; m < R; ++m) {
+            const double x = 2.0 * 3.14159265358979323846 * (2 * m > R ? m - R : m) / R;
+            c[m] = (float)kz_series(x, 1.0, 0);
+            s[m] = (float)kz_series(x, x, 1);
+        }
+    }
+};
+template <int R1, int R2, int SG> __device__ __forceinline__ void kz_dft2(float2* x);
 
 // R-point DFT X_b = sum_q x_q exp(SG 2 pi i q b / R) in place
 template <int R, int SG> __device__ __forceinline__ void kz_dft(float2* x) {
@@ -433,8 +442,18 @@ template <int R, int SG> __device__ __forceinline__ void kz_dft(float2* x) {
         x[0] = make_float2(x[0].x + s.x, x[0].y + s.y);
         x[1] = make_float2(t.x + u.x, t.y + u.y);
         x[2] = make_float2(t.x - u.x, t.y - u.y);
+    } else if constexpr (R == 6) {
+        kz_dft2<2, 3, SG>(x);
+    } else if constexpr (R == 9) {
+        kz_dft2<3, 3, SG>(x);
+    } else if constexpr (R == 10) {
+        kz_dft2<2, 5, SG>(x);
+    } else if constexpr (R == 12) {
+        kz_dft2<3, 4, SG>(x);
+    } else if constexpr (R == 15) {
+        kz_dft2<3, 5, SG>(x);
     } else {
-        static_assert(R == 5, "radix 2, 3, 4, 5 or 8");
+        static_assert(R == 5, "radix 2, 3, 4, 5, 6, 8, 9, 10, 12 or 15");
         constexpr float c1 = 0.30901699437494742410f, c2 = -0.80901699437494742410f;   // cos(2 pi / 5), cos(4 pi / 5)
         constexpr float s1 = 0.95105651629515357212f, s2 = 0.58778525229247312917f;    // sin(2 pi / 5), sin(4 pi / 5)
         const float2 t1 = make_float2(x[1].x + x[4].x, x[1].y + x[4].y);
@@ -453,230 +472,378 @@ template <int R, int SG> __device__ __forceinline__ void kz_dft(float2* x) {
     }
 }
 
+// R = R1 R2: q = R2 q1 + q2, b = b1 + R1 b2
+template <int R1, int R2, int SG> __device__ __forceinline__ void kz_dft2(float2* x) {
+    constexpr KzRoots<R1 * R2> w;
+    float2 y[R1][R2];
+#pragma unroll
+    for (int q2 = 0; q2 < R2; ++q2) {
+        float2 t[R1];
+#pragma unroll
+        for (int q1 = 0; q1 < R1; ++q1) t[q1] = x[R2 * q1 + q2];
+        kz_dft<R1, SG>(t);
+#pragma unroll
+        for (int b1 = 0; b1 < R1; ++b1) {
+            const int m = q2 * b1;             // < R
+            const float wc = w.c[m], ws = SG > 0 ? w.s[m] : -w.s[m];
+            y[b1][q2] = m == 0 ? t[b1] : make_float2(t[b1].x * wc - t[b1].y * ws, t[b1].x * ws + t[b1].y * wc);
+        }
+    }
+#pragma unroll
+    for (int b1 = 0; b1 < R1; ++b1) {
+        kz_dft<R2, SG>(y[b1]);
+#pragma unroll
+        for (int b2 = 0; b2 < R2; ++b2) x[b1 + R1 * b2] = y[b1][b2];
+    }
+}
+
 // j / d for 0 <= j < 2^13 and 1 <= d < 2^13 from a float reciprocal: the
 // product (j + 1/2) (1/d) is within 2^-23 (j + 1/2) / d of the exact quotient,
 // less than its distance 1 / (2 d) to the nearest integer
 __device__ __forceinline__ int kz_div(int j, float inv_d) { return (int)(((float)j + 0.5f) * inv_d); }
 
-// One Stockham stage over the tile's lines of length n in LDS (element i of
-// line c at c * ls + i * es; lines c >= cnt of a short tile are skipped),
-// Ns = product of the earlier radices: butterfly (c, j), j < n / R, takes
-// elements j + r n / R, multiplies element r by exp(SG 2 pi i r (j mod Ns) /
-// (Ns R)), takes their R-point DFT and puts output r at (j / Ns) Ns R +
-// (j mod Ns) + r Ns.  tw[k] = exp(-2 pi i k / n).  Butterfly b of the tile is
-// (c, j) = (b mod nl, b / nl) (nl = 2^lg lines per tile).  Every thread reads
-// all its butterflies before the barrier and writes them after it, so the
-// stage runs in place.
-template <int R, int SG>
-__device__ void kz_stage(float2* z, const float2* tw, int n, int lg, int cnt, int ls, int es, int Ns) {
-    constexpr int Q = (KZ_EPT + R - 1) / R;
-    const int nl = 1 << lg, m = n / R, total = m << lg, tstep = n / (Ns * R);
-    const float inv_ns = 1.0f / (float)Ns;
-    float2 v[Q][R];
-    int out[Q];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const int b = (int)threadIdx.x + q * KZ_THREADS;
-        const int c = b & (nl - 1), j = b >> lg;
-        out[q] = -1;
-        if (b < total && c < cnt) {
-            const int jd = kz_div(j, inv_ns), k = j - jd * Ns;
-            const int base = c * ls;
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const float2 x = z[base + (j + r * m) * es];
-                if (r == 0) {
-                    v[q][0] = x;
-                } else {
-                    const float2 w = tw[r * k * tstep];
-                    const float wy = SG < 0 ? w.y : -w.y;
-                    v[q][r] = make_float2(x.x * w.x - x.y * wy, x.x * wy + x.y * w.x);
-                }
-            }
-            kz_dft<R, SG>(v[q]);
-            out[q] = base + (jd * Ns * R + k) * es;
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < Q; ++q)
-        if (out[q] >= 0) {
-#pragma unroll
-            for (int r = 0; r < R; ++r) z[out[q] + r * Ns * es] = v[q][r];
-        }
-    __syncthreads();
-}
+enum : int { KZ_IN_FIELDS = 1, KZ_OUT_FIELDS = 2 };
 
-template <int SG>
-__device__ void kz_line_dft(float2* z, const float2* tw, const KzPass& a, int cnt, int ls, int es) {
-    int Ns = 1;
-    for (int p = 0; p < a.nrad; ++p) {
-        const int R = (int)((a.rads >> (4 * p)) & 15);
-        switch (R) {
-            case 2: kz_stage<2, SG>(z, tw, a.n, a.lg, cnt, ls, es, Ns); break;
-            case 3: kz_stage<3, SG>(z, tw, a.n, a.lg, cnt, ls, es, Ns); break;
-            case 4: kz_stage<4, SG>(z, tw, a.n, a.lg, cnt, ls, es, Ns); break;
-            case 5: kz_stage<5, SG>(z, tw, a.n, a.lg, cnt, ls, es, Ns); break;
-            default: kz_stage<8, SG>(z, tw, a.n, a.lg, cnt, ls, es, Ns); break;
-        }
-        Ns *= R;
-    }
-}
+// A pass over tiles of A x B elements, element (a, b) at base + a * ga + b in
+// the field, (a, b) in LDS at a * pitch + b + b / 8 (the padding spreads the
+// strided writes of the first stages over the banks).  Tile t starts at
+// (t / tpg) * gs + (t % tpg) * gt and holds cnt_a of the A lines (gt lines
+// apart, la in all per group) or cnt_b of the B columns.  The stages run in
+// order: along b (axis 0) or a (axis 1).
+struct KzStage {
+    short R, axis;       // radix; 0: along b, 1: along a
+    int Ns, n;           // product of the axis's earlier radices, axis length
+};
+struct KzPass {
+    int A, B, pitch, tiles, tpg;
+    int rest_a, rest_b;  // lines / columns in the last tile of a group
+    size_t gs, gt, ga;
+    int nst, nfwd;       // stages; the first nfwd are forward transforms, the others inverse
+    KzStage st[2 * KZ_MAX_ST];
+    const float2 *twa, *twb;   // exp(-2 pi i k / A), exp(-2 pi i k / B)
+    int use_a, use_b;          // entries of them the stages need
+    int wgroup, W;             // weight: slice = t / tpg (wgroup), row length of the table
+    float kz_step;             // 1 / (S dz)
+    int S;
+};
 
-// One line pass.  F: KZ_IN_FIELDS reads amplitude and phase instead of z,
-// KZ_OUT_FIELDS writes them instead of z, KZ_FILTER runs the forward
-// transform, the weight and the inverse transform (the z pass: its lines are
-// the H W pixels, line p at spectral (y, x) = (p / W, p mod W)); otherwise one
-// transform of sign SG.  Rows (x: lines contiguous in memory) sit in LDS as
-// [c][i] with row pitch a.ls; columns (y, z) as [i][c] with pitch nl.
-// Dynamic LDS: kz_lds_bytes(a).
-template <int F, int SG>
-__global__ __launch_bounds__(KZ_THREADS) void k_kz_lines(float2* z, float* amp, float* phase, KzPass a, KzWeight w) {
-    extern __shared__ float2 kz_lds[];
-    // workgroups are dealt to the 8 XCDs in turn; tile t runs as workgroup
-    // (t mod G8) * 8 + t / G8, so neighbouring tiles (which share cache lines
-    // along a row in the column passes) run side by side on one XCD's L2
-    const int g8 = (int)gridDim.x >> 3, tt = ((int)blockIdx.x & 7) * g8 + ((int)blockIdx.x >> 3);
-    if (tt >= a.tiles) return;
-    const int q = tt / a.tpg, u = tt % a.tpg;
-    const int nl = 1 << a.lg, c0 = u * nl, cnt = min(nl, a.lpg - c0);
-    const int n = a.n;
-    const bool rows = a.gi == 1;
-    const int ls = rows ? a.ls : 1, es = rows ? 1 : nl;
-    float2* t = kz_lds;
-    float2* tw = kz_lds + (size_t)nl * (rows ? a.ls : n);
-    for (int k = threadIdx.x; k < n; k += KZ_THREADS) tw[k] = a.tw[k];
-    const size_t base = (size_t)q * a.gs + (size_t)c0 * a.gc;
-    // tile element e: rows e = c n + i (contiguous in memory), columns
-    // e = i nl + c; returns the LDS slot, or -1 past the tile
-    const float inv_n = 1.0f / (float)n;
-    auto slot = [&](int e, size_t& g) -> int {
-        if (rows) {
-            if (e >= cnt * n) return -1;
-            const int c = kz_div(e, inv_n), i = e - c * n;
-            g = base + (size_t)e;
-            return c * ls + i;
-        }
-        const int c = e & (nl - 1), i = e >> a.lg;
-        if (i >= n || c >= cnt) return -1;
-        g = base + (size_t)c + (size_t)i * a.gi;
-        return e;
+template <int R, int SG, int F>
+__device__ __forceinline__ void kz_stage(const KzPass& p, int i, float2* t, const float2* twl, float2* z, float* amp,
+                                         float* phase, const float2* wtab, size_t base, int tile, int cnt_a,
+                                         int cnt_b) {
+    const KzStage s = p.st[i];
+    const int m = s.n / R, id = threadIdx.x;
+    int line, j;
+    if (s.axis == 0) {
+        line = kz_div(id, 1.0f / (float)m);
+        j = id - line * m;
+    } else {
+        j = kz_div(id, 1.0f / (float)p.B);
+        line = id - j * p.B;
+    }
+    const bool on = s.axis == 0 ? line < cnt_a : (j < m && line < cnt_b);
+    const int jd = kz_div(j, 1.0f / (float)s.Ns), k = j - jd * s.Ns;
+    const int o0 = jd * s.Ns * R + k;                     // first output
+    // LDS slot and field offset of element e of the butterfly's line
+    auto slot = [&](int e) {
+        return s.axis == 0 ? line * p.pitch + e + (e >> 3) : e * p.pitch + line + (line >> 3);
     };
-    // loads in batches of KZ_BATCH per thread, all in flight before the
-    // batch is put into LDS
-    const int ne = rows ? cnt * n : n << a.lg;
-    for (int e0 = 0; e0 < ne; e0 += KZ_BATCH * KZ_THREADS) {
-        float2 v[KZ_BATCH];
-        int sl[KZ_BATCH];
+    auto field = [&](int e) {
+        return base + (s.axis == 0 ? (size_t)line * p.ga + (size_t)e : (size_t)e * p.ga + (size_t)line);
+    };
+    float2 v[R];
+    if (on) {
 #pragma unroll
-        for (int r = 0; r < KZ_BATCH; ++r) {
-            size_t g = 0;
-            sl[r] = slot(e0 + (int)threadIdx.x + r * KZ_THREADS, g);
-            if (sl[r] >= 0) {
+        for (int r = 0; r < R; ++r) {
+            const int e = j + r * m;
+            if (i == 0) {
+                const size_t g = field(e);
                 if constexpr ((F & KZ_IN_FIELDS) != 0) v[r] = make_float2(amp[g], phase[g]);
                 else v[r] = z[g];
+            } else {
+                v[r] = t[slot(e)];
             }
         }
+        if (s.Ns > 1) {
+            const float2* tw = twl + (s.axis == 0 ? 0 : p.use_b);
+            const int step = k * (s.n / (s.Ns * R));
 #pragma unroll
-        for (int r = 0; r < KZ_BATCH; ++r)
-            if (sl[r] >= 0) t[sl[r]] = v[r];
+            for (int r = 1; r < R; ++r) {
+                const float2 w = tw[r * step];
+                const float wy = SG < 0 ? w.y : -w.y;
+                v[r] = make_float2(v[r].x * w.x - v[r].y * wy, v[r].x * wy + v[r].y * w.x);
+            }
+        }
+        kz_dft<R, SG>(v);
+        if (p.wgroup && i == p.nfwd - 1) {
+            // W_a(k) / (S H W) of element (k_z, k_y, k_x): (1 - (2 / pi) atan(A k_z^2)) E
+            const int sl = tile / p.tpg, x0 = (tile % p.tpg) * (int)p.gt;
+            const float kz = (float)(sl < (p.S + 1) / 2 ? sl : sl - p.S) * p.kz_step, kz2 = kz * kz;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const float2 ae = wtab[(size_t)(o0 + r * s.Ns) * p.W + x0 + line];
+                const float wt = (1.0f - 0.63661977236758134308f * atanf(ae.x * kz2)) * ae.y;
+                v[r] = make_float2(v[r].x * wt, v[r].y * wt);
+            }
+        }
+    }
+    if (i == p.nst - 1) {
+        if (on) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const size_t g = field(o0 + r * s.Ns);
+                if constexpr ((F & KZ_OUT_FIELDS) != 0) {
+                    amp[g] = v[r].x;
+                    phase[g] = v[r].y;
+                } else {
+                    z[g] = v[r];
+                }
+            }
+        }
+        return;
+    }
+    if (i > 0) __syncthreads();                          // every operand of the stage is read
+    if (on) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) t[slot(o0 + r * s.Ns)] = v[r];
     }
     __syncthreads();
-    if constexpr ((F & KZ_FILTER) != 0) {
-        kz_line_dft<-1>(t, tw, a, cnt, ls, es);
-        // W_a(k) / (S H W): per pixel A = beta^2 / (k_r^2 + 1e-3) and
-        // E = exp(-alpha k_r^2) / (S H W) (k_r^2 in double), per element
-        // (1 - (2 / pi) atan(A k_z^2)) E; k from fftfreq with the pixel size
-        // dx and the slice spacing dz (1/angstrom).  nl divides KZ_THREADS,
-        // so every element a thread visits belongs to its pixel c.
-        const int c = (int)threadIdx.x & (nl - 1);
-        float fa = 0.f, fe = 0.f;
-        if (c < cnt) {
-            const int p = c0 + c, y = p / w.W, x = p - y * w.W;
+}
+
+// F: KZ_IN_FIELDS reads amplitude and phase instead of z, KZ_OUT_FIELDS writes
+// them.  Workgroups past the tiles (nw of them, before the others) form the
+// weight table: per (k_y, k_x) A = beta^2 / (k_r^2 + 1e-3) and E = exp(-alpha
+// k_r^2) / (S H W), k_r^2 in double, k from fftfreq with the pixel size.
+struct KzWeight {
+    int nw, S, H, W;
+    double beta, alpha, dx;
+};
+template <int F>
+__global__ __launch_bounds__(KZ_MAX_THREADS, 8) void k_kz_pass(KzPass p, KzWeight w, float2* z, float* amp,
+                                                               float* phase, float2* wtab) {
+    extern __shared__ float2 kz_lds[];
+    if ((int)blockIdx.x < w.nw) {
+        for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < w.H * w.W; i += w.nw * blockDim.x) {
+            const int y = i / w.W, x = i - y * w.W;
             const double kx = (x < (w.W + 1) / 2 ? x : x - w.W) / (w.W * w.dx);
             const double ky = (y < (w.H + 1) / 2 ? y : y - w.H) / (w.H * w.dx);
             const double kr2 = kx * kx + ky * ky;
-            fa = (float)(w.beta * w.beta / (kr2 + 1e-3));
-            fe = (float)(exp(-w.alpha * kr2) / ((double)w.S * w.H * w.W));
+            wtab[i] = make_float2((float)(w.beta * w.beta / (kr2 + 1e-3)),
+                                  (float)(exp(-w.alpha * kr2) / ((double)w.S * w.H * w.W)));
         }
-        for (int e = threadIdx.x; e < (n << a.lg); e += KZ_THREADS) {
-            const int s = e >> a.lg;
-            if (c < cnt) {
-                const float kz = (float)((s < (w.S + 1) / 2 ? s : s - w.S) / (w.S * w.dz));
-                const float wt = (1.0f - 0.63661977236758134308f * atanf(fa * kz * kz)) * fe;
-                float2& v = t[c * ls + s * es];
-                v = make_float2(v.x * wt, v.y * wt);
-            }
-        }
-        __syncthreads();
-        kz_line_dft<+1>(t, tw, a, cnt, ls, es);
-    } else {
-        kz_line_dft<SG>(t, tw, a, cnt, ls, es);
+        return;
     }
-    for (int e = threadIdx.x; e < ne; e += KZ_THREADS) {
-        size_t g = 0;
-        const int sl = slot(e, g);
-        if (sl < 0) continue;
-        const float2 x = t[sl];
-        if constexpr ((F & KZ_OUT_FIELDS) != 0) {
-            amp[g] = x.x;
-            phase[g] = x.y;
-        } else {
-            z[g] = x;
-        }
+    // workgroups are dealt to the 8 XCDs in turn; tile t runs as workgroup
+    // (t mod G8) * 8 + t / G8, so neighbouring tiles (which share cache lines
+    // along a row in the column passes) run side by side on one XCD's L2
+    const int bid = (int)blockIdx.x - w.nw, g8 = ((int)gridDim.x - w.nw) >> 3;
+    const int tile = (bid & 7) * g8 + (bid >> 3);
+    if (tile >= p.tiles) return;
+    const int u = tile % p.tpg;
+    const bool last = u == p.tpg - 1;
+    const int cnt_a = last ? p.rest_a : p.A, cnt_b = last ? p.rest_b : p.B;
+    const size_t base = (size_t)(tile / p.tpg) * p.gs + (size_t)u * p.gt;
+    float2* tw = kz_lds + p.A * p.pitch;                  // twiddles along b, then along a
+    for (int k = threadIdx.x; k < p.use_b + p.use_a; k += blockDim.x)
+        tw[k] = k < p.use_b ? p.twb[k] : p.twa[k - p.use_b];
+    // the first stage needs no twiddles; its closing barrier publishes them
+    for (int i = 0; i < p.nst; ++i) {
+        auto run = [&](auto sg) {
+            constexpr int SG = decltype(sg)::value;
+            switch (p.st[i].R) {
+                case 2: kz_stage<2, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
+                case 3: kz_stage<3, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
+                case 4: kz_stage<4, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
+                case 5: kz_stage<5, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
+                case 6: kz_stage<6, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
+                case 8: kz_stage<8, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
+                case 9: kz_stage<9, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
+                case 10: kz_stage<10, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
+                case 15: kz_stage<15, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
+                default: kz_stage<12, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
+            }
+        };
+        if (i < p.nfwd) run(std::integral_constant<int, -1>());
+        else run(std::integral_constant<int, +1>());
     }
 }
 
 // exp(-2 pi i k / n) for k < n (in double, rounded to float)
-__global__ void k_kz_twiddles(float2* tw, int n) {
-    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) {
+__global__ void k_kz_twiddles(float2* tw, int n0, int n1, int n2) {      // three tables, one after the other
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n0 + n1 + n2; i += gridDim.x * blockDim.x) {
+        const int n = i < n0 ? n0 : (i < n0 + n1 ? n1 : n2), k = i < n0 ? i : (i < n0 + n1 ? i - n0 : i - n0 - n1);
         double sn, cs;
         sincospi(2.0 * k / n, &sn, &cs);
-        tw[k] = make_float2((float)cs, (float)-sn);
+        tw[i] = make_float2((float)cs, (float)-sn);
     }
 }
 
-// radices of n (5s, 3s, then 8s, 4s, 2s); 0 if n has another prime factor
+// Radices of a length-n line: the fewest stages, then the largest smallest
+// radix (a stage has n / R butterflies per line).  Returns the number of
+// stages, 0 for n = 1, or -1 if n has a prime factor other than 2, 3 and 5 or
+// needs more than KZ_MAX_ST stages.
 inline int fft_radices(int n, int* rs) {
-    int k = 0;
-    for (int r : {5, 3})
-        while (n % r == 0) { rs[k++] = r; n /= r; }
-    while (n % 8 == 0) { rs[k++] = 8; n /= 8; }
-    while (n % 4 == 0) { rs[k++] = 4; n /= 4; }
-    while (n % 2 == 0) { rs[k++] = 2; n /= 2; }
-    return n == 1 ? k : -1;
+    constexpr int RAD[] = {15, 12, 10, 9, 8, 6, 5, 4, 3, 2};
+    if (n == 1) return 0;
+    const int from = n == 3375 ? 0 : 1;       // 15 only where a stage would need more than KZ_MAX_THREADS butterflies
+    int cur[KZ_MAX_ST], best_min = 0;
+    for (int want = 1; want <= KZ_MAX_ST; ++want) {
+        // radices in non-increasing order
+        auto search = [&](auto&& self, int left, int depth, int first) -> void {
+            if (depth == want) {
+                if (left == 1 && cur[depth - 1] > best_min) {
+                    best_min = cur[depth - 1];
+                    for (int i = 0; i < depth; ++i) rs[i] = cur[i];
+                }
+                return;
+            }
+            for (int i = first; i < 10; ++i)
+                if (left % RAD[i] == 0) {
+                    cur[depth] = RAD[i];
+                    self(self, left / RAD[i], depth + 1, i);
+                }
+        };
+        search(search, n, 0, from);
+        if (best_min) return want;
+    }
+    return -1;
 }
 
-// the line pass over `groups` groups of lpg lines of length n with the radices
-// rad[0..nrad): 2^lg lines per tile, the most up to nl_max (at most
-// KZ_THREADS) whose tile and twiddle table fit in KZ_LDS; rows
-// (gi == 1) get a row pitch of n + 8 where it fits (LDS reads of the lines'
-// elements side by side then fall in different banks); *grid = the tiles
-inline KzPass kz_pass(int n, int groups, int lpg, size_t gs, size_t gc, size_t gi, const int* rad, int nrad,
-                      int nl_max, const float2* tw, int* grid) {
-    KzPass a{};
-    a.tw = tw;
-    a.n = n;
-    a.lpg = lpg;
-    a.gs = gs;
-    a.gc = gc;
-    a.gi = gi;
-    a.nrad = nrad;
-    for (int k = 0; k < nrad && k < KZ_MAX_RAD; ++k) a.rads |= (unsigned long long)rad[k] << (4 * k);
-    const bool rows = gi == 1;
-    auto fits = [&](int nl, int pitch) { return nl * pitch + n <= KZ_LDS; };
-    a.ls = rows && fits(1, n + 8) ? n + 8 : n;
-    a.lg = 0;
-    while ((2 << a.lg) <= nl_max && fits(2 << a.lg, a.ls)) ++a.lg;
-    a.tpg = (lpg + (1 << a.lg) - 1) >> a.lg;
-    a.tiles = groups * a.tpg;
-    *grid = (a.tiles + 7) & ~7;
-    return a;
+// appends the stages of one axis (lengths n, radices rs); returns the
+// butterflies of its largest stage per line
+inline int kz_add_axis(KzPass& p, int axis, int n, const int* rs, int nr) {
+    int Ns = 1, most = 0;
+    for (int i = 0; i < nr; ++i) {
+        p.st[p.nst++] = KzStage{(short)rs[i], (short)axis, Ns, n};
+        most = most > n / rs[i] ? most : n / rs[i];
+        Ns *= rs[i];
+    }
+    return most;
 }
-// tile and twiddles
-inline size_t kz_lds_bytes(const KzPass& a) {
-    const size_t nl = (size_t)1 << a.lg;
-    return (nl * (a.gi == 1 ? a.ls : a.n) + a.n) * sizeof(float2);
+inline int kz_pitch(int B) { return (B + (B >> 3)) | 1; }
+inline size_t kz_lds_bytes(const KzPass& p) {
+    return ((size_t)p.A * p.pitch + p.use_a + p.use_b) * sizeof(float2);
+}
+inline int kz_most(int n, const int* rs, int nr) {      // butterflies of the largest stage of a line
+    int most = 0;
+    for (int i = 0; i < nr; ++i) most = most > n / rs[i] ? most : n / rs[i];
+    return most;
+}
+
+// The passes of a call: plans[0 .. n).  in / out: whether the pass reads or
+// writes the two fields.  rx, ry, rz: radices of W, H and S.
+struct KzPlan {
+    KzPass p;
+    int threads, in, out;
+};
+inline int kz_plan(int S, int H, int W, const int* rx, int nx, const int* ry, int ny, const int* rz, int nz,
+                   const float2* twx, const float2* twy, const float2* twz, float kz_step, KzPlan* plans) {
+    const size_t HW = (size_t)H * W;
+    int np = 0;
+    auto finish = [&](KzPass& p, int threads, int in, int out) {
+        plans[np].p = p;
+        plans[np].threads = (threads + 63) / 64 * 64;
+        plans[np].in = in;
+        plans[np++].out = out;
+    };
+    // lines side by side in a tile: a power of two, as many as `threads`
+    // butterflies and KZ_LDS_MAX allow (at least one), no more than there are
+    auto lines = [&](int n, int most, int threads, int cap, size_t total) {
+        int nl = 1;
+        while (2 * nl <= cap && (size_t)nl < total && 2 * nl * most <= threads &&
+               ((size_t)n * kz_pitch(2 * nl) + n) * sizeof(float2) <= KZ_LDS_MAX)
+            nl *= 2;
+        return nl;
+    };
+    const int mx = kz_most(W, rx, nx), my = kz_most(H, ry, ny), mz = kz_most(S, rz, nz);
+    // x and z together: S rows of one y
+    KzPass xz{};
+    xz.A = S;
+    xz.B = W;
+    xz.pitch = kz_pitch(W);
+    xz.tiles = xz.tpg = H;
+    xz.rest_a = S;
+    xz.rest_b = W;
+    xz.gt = W;
+    xz.ga = HW;
+    xz.twa = twz;
+    xz.twb = twx;
+    xz.use_a = S;
+    xz.use_b = W;
+    const int xzt = mx * S > mz * W ? mx * S : mz * W;
+    const bool fused = S > 1 && xzt <= KZ_MAX_THREADS && kz_lds_bytes(xz) <= KZ_LDS_MAX;
+    // x alone: rows of the whole stack, one after the other
+    KzPass x{};
+    {
+        int nl = 1;
+        const size_t rows = (size_t)S * H;
+        while (2 * nl <= 16 && 2 * nl * mx <= 512 && ((size_t)2 * nl * kz_pitch(W) + W) * sizeof(float2) <= KZ_LDS_MAX)
+            nl *= 2;
+        x.A = nl;
+        x.B = W;
+        x.pitch = kz_pitch(W);
+        x.tiles = x.tpg = (int)((rows + nl - 1) / nl);
+        x.rest_a = (int)(rows - (size_t)(x.tiles - 1) * nl);
+        x.rest_b = W;
+        x.gt = (size_t)nl * W;
+        x.ga = W;
+        x.twb = twx;
+        x.use_b = W;
+    }
+    // z alone: columns of S over consecutive pixels
+    KzPass zc{};
+    {
+        const int nl = lines(S, mz, 512, 256, HW);
+        zc.A = S;
+        zc.B = nl;
+        zc.pitch = kz_pitch(nl);
+        zc.tiles = zc.tpg = (int)((HW + nl - 1) / nl);
+        zc.rest_a = S;
+        zc.rest_b = (int)(HW - (size_t)(zc.tiles - 1) * nl);
+        zc.gt = nl;
+        zc.ga = HW;
+        zc.twa = twz;
+        zc.use_a = S;
+    }
+    // y forward, weight, y inverse: columns of one slice
+    KzPass y{};
+    const int ynl = lines(H, my, KZ_MAX_THREADS, 16, W);
+    y.A = H;
+    y.B = ynl;
+    y.pitch = kz_pitch(ynl);
+    y.tpg = (W + ynl - 1) / ynl;
+    y.tiles = S * y.tpg;
+    y.rest_a = H;
+    y.rest_b = W - (y.tpg - 1) * ynl;
+    y.gs = HW;
+    y.gt = ynl;
+    y.ga = W;
+    y.twa = twy;
+    y.use_a = H;
+    y.wgroup = 1;
+    y.W = W;
+    y.S = S;
+    y.kz_step = kz_step;
+    kz_add_axis(y, 1, H, ry, ny);
+    y.nfwd = y.nst;
+    kz_add_axis(y, 1, H, ry, ny);
+
+    auto add = [&](KzPass p, bool ax, bool az, bool fwd, int threads, int in, int out) {
+        if (ax && fwd) kz_add_axis(p, 0, W, rx, nx);
+        if (az) kz_add_axis(p, 1, S, rz, nz);
+        if (ax && !fwd) kz_add_axis(p, 0, W, rx, nx);
+        p.nfwd = fwd ? p.nst : 0;
+        finish(p, threads, in, out);
+    };
+    const bool z_apart = !fused && S > 1;
+    if (fused) add(xz, true, true, true, xzt, 1, 0);
+    else add(x, true, false, true, x.A * mx, 1, 0);
+    if (z_apart) add(zc, false, true, true, zc.B * mz, 0, 0);
+    finish(y, ynl * my, 0, 0);
+    if (z_apart) add(zc, false, true, false, zc.B * mz, 0, 0);
+    if (fused) add(xz, true, true, false, xzt, 0, 1);
+    else add(x, true, false, false, x.A * mx, 0, 1);
+    return np;
 }
 
 // Partial overlaps conj(P_m(r)) P_n(r) summed over one chunk of GRAM_CHUNK

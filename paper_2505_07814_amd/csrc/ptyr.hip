@@ -906,7 +906,7 @@ Layout make_layout(const ptyr_geom* g) {
     L.cons = take((size_t)ORTH_MAX_M * (ORTH_MAX_M + 1) / 2 * GRAM_MAX_CHUNKS * sizeof(cd) +
                   (size_t)ORTH_MAX_M * ORTH_MAX_M * sizeof(float2) + ORTH_MAX_M * sizeof(double));
     L.rzmat = take((size_t)RZ_REG_S * RZ_REG_S * sizeof(float));     // depth-filter matrix
-    L.kz = take((S * HW + g->W + g->H + S) * sizeof(float2));       // k_z filter: the complex field, twiddles
+    L.kz = take((S * HW + g->W + g->H + S + HW) * sizeof(float2));  // k_z filter: complex field, twiddles, weights
     L.total = o;
     return L;
 }
@@ -1722,7 +1722,7 @@ ptyr_status ptyr_constrain(ptyr_ctx* c, float* amp, float* phase, float* probe, 
     if (cfg->phase_positive && !phase) return PTYR_E_ARG;
     if (cfg->probe_orthogonal && (!probe || g.M > ORTH_MAX_M)) return PTYR_E_ARG;
     const bool kz = cfg->kz_beta > 0.f || cfg->kz_alpha > 0.f;
-    int rad[3][32], nrad[3] = {0, 0, 0};
+    int rad[3][KZ_MAX_ST], nrad[3] = {0, 0, 0};
     if (!(cfg->kz_beta >= 0.f) || !(cfg->kz_alpha >= 0.f) || !isfinite(cfg->kz_beta) || !isfinite(cfg->kz_alpha))
         return PTYR_E_ARG;
     if (kz) {
@@ -1766,29 +1766,26 @@ ptyr_status ptyr_constrain(ptyr_ctx* c, float* amp, float* phase, float* probe, 
         float* const amp_o = amp ? amp + (size_t)ob * g.S * HW : nullptr;
         float* const phase_o = phase ? phase + (size_t)ob * g.S * HW : nullptr;
         if (kz) {
-            // amplitude + i phase: forward x and y passes, the z pass (forward,
-            // weight, inverse), inverse y and x passes
+            // amplitude + i phase through the passes of kz_plan; the first
+            // launch also forms the weight table
             float2* zb = at<float2>(c, c->L.kz);
             float2* twx = zb + (size_t)g.S * HW;           // twiddle tables of the three line lengths
             float2* twy = twx + g.W;
             float2* twz = twy + g.H;
-            hipLaunchKernelGGL(k_kz_twiddles, dim3(grid_for(g.W)), dim3(256), 0, st, twx, g.W);
-            hipLaunchKernelGGL(k_kz_twiddles, dim3(grid_for(g.H)), dim3(256), 0, st, twy, g.H);
-            hipLaunchKernelGGL(k_kz_twiddles, dim3(grid_for(g.S)), dim3(256), 0, st, twz, g.S);
-            int gx, gy, gz;
-            const KzPass px = kz_pass(g.W, 1, g.S * g.H, 0, (size_t)g.W, 1, rad[0], nrad[0], 16, twx, &gx);
-            const KzPass py = kz_pass(g.H, g.S, g.W, HW, 1, (size_t)g.W, rad[1], nrad[1], 16, twy, &gy);
-            const KzPass pz = kz_pass(g.S, 1, g.H * g.W, 0, 1, HW, rad[2], nrad[2], 256, twz, &gz);
-            const KzWeight kw{g.S, g.H, g.W, (double)cfg->kz_beta, (double)cfg->kz_alpha, g.dx, (double)cfg->kz_dz};
-            const dim3 blk(KZ_THREADS);
-            hipLaunchKernelGGL((k_kz_lines<KZ_IN_FIELDS, -1>), dim3(gx), blk, kz_lds_bytes(px), st, zb, amp_o, phase_o,
-                               px, kw);
-            hipLaunchKernelGGL((k_kz_lines<0, -1>), dim3(gy), blk, kz_lds_bytes(py), st, zb, amp_o, phase_o, py, kw);
-            hipLaunchKernelGGL((k_kz_lines<KZ_FILTER, 0>), dim3(gz), blk, kz_lds_bytes(pz), st, zb, amp_o, phase_o, pz,
-                               kw);
-            hipLaunchKernelGGL((k_kz_lines<0, +1>), dim3(gy), blk, kz_lds_bytes(py), st, zb, amp_o, phase_o, py, kw);
-            hipLaunchKernelGGL((k_kz_lines<KZ_OUT_FIELDS, +1>), dim3(gx), blk, kz_lds_bytes(px), st, zb, amp_o,
-                               phase_o, px, kw);
+            float2* wtab = twz + g.S;
+            if (ob == 0)
+                hipLaunchKernelGGL(k_kz_twiddles, dim3(grid_for(g.W + g.H + g.S)), dim3(256), 0, st, twx, g.W, g.H, g.S);
+            KzPlan plans[5];
+            const int np = kz_plan(g.S, g.H, g.W, rad[0], nrad[0], rad[1], nrad[1], rad[2], nrad[2], twx, twy, twz,
+                                   (float)(1.0 / (g.S * (double)cfg->kz_dz)), plans);
+            for (int i = 0; i < np; ++i) {
+                const KzPlan& q = plans[i];
+                KzWeight kw{0, g.S, g.H, g.W, (double)cfg->kz_beta, (double)cfg->kz_alpha, g.dx};
+                if (i == 0 && ob == 0) kw.nw = (int)((HW + q.threads - 1) / q.threads);
+                const auto kernel = q.in ? k_kz_pass<KZ_IN_FIELDS> : (q.out ? k_kz_pass<KZ_OUT_FIELDS> : k_kz_pass<0>);
+                hipLaunchKernelGGL(kernel, dim3(kw.nw + ((q.p.tiles + 7) & ~7)), dim3(q.threads), kz_lds_bytes(q.p), st,
+                                   q.p, kw, zb, amp_o, phase_o, wtab);
+            }
         }
         if (filter) {
             float* fields[2] = {amp_o, phase_o};

@@ -52,3 +52,20 @@ def test_orthogonalisation_beside_the_depth_filter(S, H, W, M):
         u = np.vdot(got[m], rP[m])
         d = np.linalg.norm(got[m] * (u / abs(u)) - rP[m]) / np.linalg.norm(rP[m])
         assert d <= 1e-5, (m, d)
+
+
+@pytest.mark.parametrize("S,H,W", [(16, 96, 250), (24, 100, 640), (3, 64, 3375), (4, 3375, 64)])
+def test_kz_filter_passes(S, H, W):
+    """x and z in one pass and apart (by what fits a workgroup), radices 15,
+    12, 10 and 9, padded pitches, a ragged last tile of columns."""
+    print(f"kz passes {S}x{H}x{W}", flush=True)
+    rng = np.random.default_rng(S + H + W)
+    amp = rng.uniform(0.5, 1.5, (S, H, W)).astype(np.float32)
+    ph = rng.uniform(-0.5, 1.0, (S, H, W)).astype(np.float32)
+    eng = engine(S, H, W)
+    a, p = T(amp), T(ph)
+    eng.constrain(a, p, kz_beta=0.8, kz_alpha=0.5, kz_dz=5.0)
+    eng.sync()
+    for got, field in ((a, amp), (p, ph)):
+        ref = oc.kz_filter(field, 0.8, 0.5, 0.2, 5.0)
+        assert np.linalg.norm(got.cpu().numpy() - ref) <= 1e-5 * np.linalg.norm(ref)
