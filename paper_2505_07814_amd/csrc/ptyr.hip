@@ -291,15 +291,18 @@ __global__ __launch_bounds__(256) void k_loss_partial(const float* Im, const flo
 // when two terms are folded into the weights by k_loss_mix); scal[2] = Z_0.
 __global__ void k_loss_final(const double* part, int nblk, double K, LossTerms lt, int check, double* scal,
                              double* loss_out, int* err, const double* spart, int nsp, double spw) {
-    __shared__ double sh[NLP * 256];
-    double s[NLP] = {0, 0, 0, 0, 0};
+    // the sparsity term's partial sums ride along as one more column (one
+    // thread adding its B S entries in turn took 27 us at 882 of them)
+    __shared__ double sh[(NLP + 1) * 256];
+    double s[NLP + 1] = {0, 0, 0, 0, 0, 0};
     for (int b = threadIdx.x; b < nblk; b += 256)
         for (int k = 0; k < NLP; ++k) s[k] += part[NLP * b + k];
-    for (int k = 0; k < NLP; ++k) sh[k * 256 + threadIdx.x] = s[k];
+    for (int b = threadIdx.x; b < nsp; b += 256) s[NLP] += spart[b];
+    for (int k = 0; k <= NLP; ++k) sh[k * 256 + threadIdx.x] = s[k];
     __syncthreads();
     for (int o = 128; o > 0; o >>= 1) {
         if ((int)threadIdx.x < o)
-            for (int k = 0; k < NLP; ++k) sh[k * 256 + threadIdx.x] += sh[k * 256 + threadIdx.x + o];
+            for (int k = 0; k <= NLP; ++k) sh[k * 256 + threadIdx.x] += sh[k * 256 + threadIdx.x + o];
         __syncthreads();
     }
     if (threadIdx.x == 0) {
@@ -324,11 +327,7 @@ __global__ void k_loss_final(const double* part, int nblk, double K, LossTerms l
             atomicOr(err, ERR_ZERO_MEAN);
             L = 0.0; c[0] = c[1] = 0.0;
         }
-        if (nsp > 0) {                                  // + sparsity term, sums in order
-            double t = 0.0;
-            for (int i = 0; i < nsp; ++i) t += spart[i];
-            L += spw * t;
-        }
+        if (nsp > 0) L += spw * sh[NLP * 256];         // + sparsity term
         if (check && (bad > 0.0 || !isfinite(L))) atomicOr(err, ERR_NONFINITE);
         scal[0] = L;
         scal[1] = lt.n > 1 ? 1.0 : c[0];
@@ -682,9 +681,18 @@ __global__ __launch_bounds__(256) void k_sparse_partial(const float* phase, cons
     const int j = blockIdx.x, s = blockIdx.y;
     const PosInfo pi = pinfo[j];
     double acc = 0.0;
-    if (pi.ty >= 0)
-        for (int e = threadIdx.x; e < N * N; e += blockDim.x)
-            acc += fabs((double)phase[((size_t)s * H + pi.ty + e / N) * W + pi.tx + e % N]);
+    if (pi.ty >= 0) {
+        // 256 / N rows at a time (N <= 256), eight of a thread's reads in flight
+        const int y0 = threadIdx.x / N, dy = 256 / N;
+        const float* src = phase + ((size_t)s * H + pi.ty + y0) * W + pi.tx + threadIdx.x % N;
+        for (int y = 0; y < N; y += 8 * dy) {
+            float v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = src[(size_t)(y + q * dy) * W];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) acc += fabs((double)v[q]);
+        }
+    }
     __shared__ double sh[256];
     sh[threadIdx.x] = acc;
     __syncthreads();
@@ -719,40 +727,52 @@ __global__ void k_sum_rows(const float2* src, float2* dst, int B, int M, int NN,
 //   g_rho   = 2 pi sum_m sum_k q Im(Phat R conj(G^_0))
 //   g_th    = 2 pi dz sec^2(th) sum_s,m,k k Im(G^ conj(Y))
 //   g_dz    = sum [-pi lam |k|^2 + 2 pi (k_x tan th_x + k_y tan th_y)] Im(G^ conj(Y))
-// One thread per batch row (rows of a batch are distinct, so the row
-// updates do not collide); dz and a global tilt are summed over rows in
-// fixed order by a block tree.
-__global__ __launch_bounds__(256) void k_param_grads(const double* part, int nblk, const PosInfo* pinfo, int B,
-                                                     int M, const float* tilt, int global_tilt, const float* dzp,
-                                                     double lam, const double* scale, float* g_pos, float* g_tilt,
-                                                     float* g_dz) {
-    __shared__ double sh[3][256];
+// One workgroup of up to 1024 threads, 16 lanes per batch row (rows of a batch are
+// distinct, so the row updates do not collide), which add the row's partial
+// sums in a fixed order; dz and a global tilt are summed over rows in fixed
+// order by a block tree.  (With one thread per row the chain of dependent
+// reads took 34 us for 8 modes at N = 256, 10 us for 12 at N = 128.)
+__global__ __launch_bounds__(1024) void k_param_grads(const double* part, int nblk, const PosInfo* pinfo, int B, int M,
+                                                      const float* tilt, int global_tilt, const float* dzp,
+                                                      double lam, const double* scale, float* g_pos, float* g_tilt,
+                                                      float* g_dz) {
+    __shared__ double sh[3][64];
     const double two_pi = 6.283185307179586;
     const double sc = *scale;                 // batch factor of the loss gradient
     const double dz = *dzp;
+    const int slot = threadIdx.x / 16, lane = threadIdx.x % 16, n = M * nblk;
     double sdz = 0.0, sty = 0.0, stx = 0.0;
-    for (int j = threadIdx.x; j < B; j += blockDim.x) {
-        if (pinfo[j].ty < 0) continue;
-        const int row = pinfo[j].row;
-        double k2 = 0, kx = 0, ky = 0, py = 0, px = 0;
-        for (int m = 0; m < M; ++m)
-            for (int b = 0; b < nblk; ++b) {
-                const double* q = part + ((size_t)(j * M + m) * nblk + b) * 8;
-                k2 += q[0]; kx += q[1]; ky += q[2]; py += q[3]; px += q[4];
+    if (threadIdx.x < 64) sh[0][threadIdx.x] = sh[1][threadIdx.x] = sh[2][threadIdx.x] = 0.0;
+    __syncthreads();
+    for (int j0 = 0; j0 < B; j0 += blockDim.x / 16) {
+        const int j = j0 + slot;
+        const bool live = j < B && pinfo[j].ty >= 0;
+        double v[5] = {0, 0, 0, 0, 0};
+        if (live)
+            for (int e = lane; e < n; e += 16) {
+                const double* q = part + ((size_t)j * n + e) * 8;
+#pragma unroll
+                for (int k = 0; k < 5; ++k) v[k] += q[k];
             }
+#pragma unroll
+        for (int k = 0; k < 5; ++k)
+#pragma unroll
+            for (int o = 8; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
+        if (!live || lane != 0) continue;
+        const int row = pinfo[j].row;
         const float* th = global_tilt ? tilt : tilt + 2 * row;
         const double ty = tan((double)th[0]), tx = tan((double)th[1]);
         const double cy = cos((double)th[0]), cx = cos((double)th[1]);
-        k2 *= sc; kx *= sc; ky *= sc; py *= sc; px *= sc;
+        const double k2 = v[0] * sc, kx = v[1] * sc, ky = v[2] * sc, py = v[3] * sc, px = v[4] * sc;
         sdz += -3.141592653589793 * lam * k2 + two_pi * (tx * kx + ty * ky);
         const double gy = two_pi * dz * ky / (cy * cy), gx = two_pi * dz * kx / (cx * cx);
         if (global_tilt) { sty += gy; stx += gx; }
         else if (g_tilt) { g_tilt[2 * row] += (float)gy; g_tilt[2 * row + 1] += (float)gx; }
         if (g_pos) { g_pos[2 * row] += (float)(two_pi * py); g_pos[2 * row + 1] += (float)(two_pi * px); }
     }
-    sh[0][threadIdx.x] = sdz; sh[1][threadIdx.x] = sty; sh[2][threadIdx.x] = stx;
+    if (lane == 0) { sh[0][slot] = sdz; sh[1][slot] = sty; sh[2][slot] = stx; }
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
+    for (int o = 32; o > 0; o >>= 1) {
         if ((int)threadIdx.x < o)
             for (int k = 0; k < 3; ++k) sh[k][threadIdx.x] += sh[k][threadIdx.x + o];
         __syncthreads();
@@ -1558,7 +1578,7 @@ ptyr_status run_adjoint(ptyr_ctx* c, const float* amp, const float* phase, const
             }
         }
         if (g_pos || g_tilt || g_dz)
-            hipLaunchKernelGGL(k_param_grads, dim3(1), dim3(256), 0, st, at<double>(c, c->L.part),
+            hipLaunchKernelGGL(k_param_grads, dim3(1), dim3(std::min(1024, (B * 16 + 63) / 64 * 64)), 0, st, at<double>(c, c->L.part),
                                g.N == 256 ? NBLK256 : 1, at<PosInfo>(c, c->L.pinfo), B, M, tilt, a.global_tilt, dz,
                                g.lambda, scale, g_pos, g_tilt, g_dz);
     };
