@@ -33,7 +33,9 @@ struct PosInfo {      // integer crop corner and sub-pixel shift of one batch ro
 //   FULL : phi_s for every slice, Y_s for s >= 1, and the far field
 //   CKPT : phi_s for s % ckK == 0 (ckK <= S) or nothing (ckK > S); the gradient
 //          recomputes phi_s / Y_s into a 3-wave scratch per chain (phi, Y, G)
-enum : int { KEEP_FULL = 0, KEEP_CKPT = 1 };
+//   PHI  : as FULL without the Y_s (same slots), where neither the tilt nor
+//          the dz gradient is wanted
+enum : int { KEEP_FULL = 0, KEEP_CKPT = 1, KEEP_PHI = 2 };
 
 // Arguments shared by the fused forward / gradient kernels.
 struct WaveArgs {
@@ -44,6 +46,7 @@ struct WaveArgs {
     const float* dz;       // 1
     float2* store;         // kept waves, per chain: FULL 2S waves, CKPT nck + 3
     int keep;              // KEEP_FULL / KEEP_CKPT
+    int spectra;           // whether the Y_s and the tilt / dz sums are wanted
     int ckK;               // checkpoint spacing (CKPT)
     int nck;               // checkpoints per chain (CKPT)
     int B, M, S, H, W;     // M: chain modes per row (probe modes x object modes)
@@ -292,7 +295,7 @@ __global__ __launch_bounds__(N * N / 16) void k_forward(WaveArgs a) {
     }
     load_tables<N>(tab, a, j);
     const Slots<N> sl(a, j * a.M + m);
-    constexpr bool full = KEEP == KEEP_FULL;            // the store is always in the workspace
+    constexpr bool full = KEEP != KEEP_CKPT, specs = KEEP == KEEP_FULL;    // the store is always in the workspace
     const bool ckpt = KEEP == KEEP_CKPT && a.ckK <= a.S;
     const size_t HW = (size_t)a.H * a.W;
 
@@ -331,11 +334,11 @@ __global__ __launch_bounds__(N * N / 16) void k_forward(WaveArgs a) {
         apply_h<N, false>(ov, tab, l, c);
 #pragma unroll
         for (int r = 0; r < 16; ++r) v[r] = ov[r];
-        if (full) kstore_half<N, 0>(ov, sl.spec(s + 1));
+        if (specs) kstore_half<N, 0>(ov, sl.spec(s + 1));
         __builtin_amdgcn_sched_barrier(0);
         mid2nat<WaveGeo<N>, +1>(v, lds, tw, l, c);
         __builtin_amdgcn_sched_barrier(0);
-        if (full) kstore_half<N, 1>(ov, sl.spec(s + 1));
+        if (specs) kstore_half<N, 1>(ov, sl.spec(s + 1));
         relayout<N, ROW, NAT, COL, MID>(v, lds, l, c);
         if (s + 1 < a.S - 1) load_patch<N>(ov, Ocm + (size_t)(s + 1) * HW, a.W, pi.ty, pi.tx, l, c);
         mid2nat<WaveGeo<N>, +1>(v, lds, tw, l, c);
@@ -378,7 +381,8 @@ __device__ __forceinline__ void recompute_phi(float2 (&v)[16], int s, const Wave
 // Gradient: one workgroup per (batch row j, probe mode m).  Walks the slices
 // backwards (chain rule through Eq. 2-4) holding only the adjoint field G in
 // registers; phi_s, Y_s and the far field are streamed from the store
-// (KEEP = KEEP_FULL) or recomputed into the chain's scratch (KEEP_CKPT).
+// (KEEP = KEEP_FULL; KEEP_PHI without the Y_s and the sums they enter) or
+// recomputed into the chain's scratch (KEEP_CKPT).
 // Writes per-slice object-patch gradients conj(phi_s) G_chi, the
 // probe-spectrum gradient conj(R) G^_0 and partial sums for the position,
 // tilt and dz gradients.
@@ -407,7 +411,7 @@ __global__ __launch_bounds__(N * N / 16) void k_gradient(WaveArgs a) {
     const auto tw = kernel_twiddles<N, WIDE>(tab, c);
     float2 g[16];
     // far field: kept, or recomputed from phi_{S-1}
-    if (KEEP == KEEP_FULL) {
+    if (KEEP != KEEP_CKPT) {
         kload<N>(g, sl.far());
     } else {
         recompute_phi<N>(g, a.S - 1, a, sl, m, pi.ty, pi.tx, sl.sc_spec(), lds, tab, tw, l, c);
@@ -455,9 +459,11 @@ __global__ __launch_bounds__(N * N / 16) void k_gradient(WaveArgs a) {
             }
             // every read before the writes: one in-order counter covers both
             if (s > 0) {
-                const float2* Y_s = sl.spec(s);
+                if constexpr (KEEP == KEEP_FULL) {
+                    const float2* Y_s = sl.spec(s);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) yv_[r] = (Y_s + r * T)[threadIdx.x];
+                    for (int r = 0; r < 16; ++r) yv_[r] = (Y_s + r * T)[threadIdx.x];
+                }
                 fetch(s - 1);
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -467,7 +473,7 @@ __global__ __launch_bounds__(N * N / 16) void k_gradient(WaveArgs a) {
             return nullptr;
         }
         const float2 *phi_s, *Y_s;
-        if (KEEP == KEEP_FULL) {
+        if (KEEP != KEEP_CKPT) {
             phi_s = sl.phi(s);
             Y_s = s > 0 ? sl.spec(s) : nullptr;
         } else {
@@ -553,6 +559,7 @@ __global__ __launch_bounds__(N * N / 16) void k_gradient(WaveArgs a) {
         // Y is read in one batch; the per-register k_x are recomputed each
         // slice (the opaque copy of the lane index keeps the compiler from
         // hoisting all sixteen out of the loop into spills)
+        if constexpr (KEEP != KEEP_PHI) {
         int cc = c;
         asm volatile("" : "+v"(cc));
         float2 yv[16];
@@ -566,6 +573,7 @@ __global__ __launch_bounds__(N * N / 16) void k_gradient(WaveArgs a) {
             acc_k2 = fma(e, fma(kx, kx, ky2), acc_k2);
             acc_kx = fma(e, kx, acc_kx);
             acc_ky = fma(e, ky, acc_ky);
+        }
         }
         apply_h<N, true>(g, tab, l, c);                                       // conj(H) G^ / N^2
         ifft2_to_col<N>(g, lds, tw, l, c);                                // G_chi_{s-1}

@@ -270,9 +270,10 @@ __global__ __launch_bounds__(256) void k256_grad_col(Pass256 P) {
     }
     cols_load(v, w, x, c);
     float2 yv_[16];                      // Z_s, read now so that its latency overlaps the DFT
-    if (P.s > 0) cols_load(yv_, sl.phi(P.s), x, c);
+    const bool specs = P.s > 0 && a.spectra;          // Y_s only enters the dz / tilt sums
+    if (specs) cols_load(yv_, sl.phi(P.s), x, c);
     nat2mid<ColGeo256, -1>(v, lds, tab.tw, l, c);                       // G^ (raw), (k_y, k_x)
-    if (P.s > 0) {
+    if (specs) {
         // Y'_s = F_y[Z_s] / N: the forward's inverse along y undone (1/N is exact)
         nat2mid<ColGeo256, -1>(yv_, lds, tab.tw, l, c);
 #pragma unroll
@@ -287,12 +288,14 @@ __global__ __launch_bounds__(256) void k256_grad_col(Pass256 P) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int ky_i = c + 16 * r;
-            const float2 yv = yv_[r];
-            const double e = fma((double)v[r].y, (double)yv.x, -((double)v[r].x * (double)yv.y));   // Im(G^ conj(Y))
-            const double ky = sfreq<N256>(ky_i) * dk;
-            acc[0] = fma(e, fma(ky, ky, kx2), acc[0]);
-            acc[1] = fma(e, kx, acc[1]);
-            acc[2] = fma(e, ky, acc[2]);
+            if (specs) {
+                const float2 yv = yv_[r];
+                const double e = fma((double)v[r].y, (double)yv.x, -((double)v[r].x * (double)yv.y));   // Im(G^ conj(Y))
+                const double ky = sfreq<N256>(ky_i) * dk;
+                acc[0] = fma(e, fma(ky, ky, kx2), acc[0]);
+                acc[1] = fma(e, kx, acc[1]);
+                acc[2] = fma(e, ky, acc[2]);
+            }
             v[r] = cscale(tmul<true>(tmul<true>(v[r], tab.h[ky_i]), hx), inv_n2);
         }
         mid2nat<ColGeo256, +1>(v, lds, tab.tw, l, c);
@@ -313,6 +316,7 @@ __global__ __launch_bounds__(256) void k256_grad_col(Pass256 P) {
             acc[4] = fma((double)z.y, qx, acc[4]);
         }
     }
+    if (P.s > 0 && !specs) return;                      // nothing to add to the partial sums
     block_sum<5>(acc, reinterpret_cast<double*>(lds));
     if (threadIdx.x == 0)
         for (int k = 0; k < 5; ++k) part[k] += acc[k];

@@ -1203,6 +1203,7 @@ WaveArgs wave_args(ptyr_ctx* c, const float* tilt, const float* dz, int B) {
     a.part = at<double>(c, c->L.part);
     a.tw = at<float4>(c, c->L.tw);
     a.tab = at<float4>(c, c->L.tab);
+    a.spectra = 1;
     return a;
 }
 
@@ -1211,13 +1212,17 @@ WaveArgs wave_args(ptyr_ctx* c, const float* tilt, const float* dz, int B) {
 template <int N, bool WIDE = false> void launch_forward(ptyr_ctx* c, WaveArgs a, int c0, int nc, hipStream_t st) {
     TimedLaunch t(c, PTYR_K_FORWARD, st, true);
     a.chain0 = c0;
-    const auto kernel = a.keep == KEEP_FULL ? k_forward<N, KEEP_FULL, WIDE> : k_forward<N, KEEP_CKPT, false>;
+    const auto kernel = a.keep != KEEP_FULL ? k_forward<N, KEEP_CKPT, false>
+                        : a.spectra         ? k_forward<N, KEEP_FULL, WIDE>
+                                            : k_forward<N, KEEP_PHI, WIDE>;
     hipExtLaunchKernelGGL(kernel, dim3(nc), dim3(N * N / 16), 0, st, t.start(), t.stop(), 0, a);
 }
 template <int N, bool WIDE = false> void launch_gradient(ptyr_ctx* c, WaveArgs a, int c0, int nc, hipStream_t st) {
     TimedLaunch t(c, PTYR_K_GRADIENT, st, true);
     a.chain0 = c0;
-    const auto kernel = a.keep == KEEP_FULL ? k_gradient<N, KEEP_FULL, WIDE> : k_gradient<N, KEEP_CKPT, false>;
+    const auto kernel = a.keep != KEEP_FULL ? k_gradient<N, KEEP_CKPT, false>
+                        : a.spectra         ? k_gradient<N, KEEP_FULL, WIDE>
+                                            : k_gradient<N, KEEP_PHI, WIDE>;
     hipExtLaunchKernelGGL(kernel, dim3(nc), dim3(N * N / 16), 0, st, t.start(), t.stop(), 0, a);
 }
 // N = 256: forward and gradient as line passes (lines256.hpp)
@@ -1529,7 +1534,11 @@ ptyr_status run_adjoint(ptyr_ctx* c, const float* amp, const float* phase, const
                            at<PosInfo>(c, c->L.pinfo), g.S * obj_modes(g), g.N, g.H, g.W, at<double>(c, c->L.spart));
     const float sp =
         sparse && g_phase ? (float)(g.sparse_w / ((double)B * g.S * obj_modes(g) * g.N * g.N)) : 0.f;
-    const WaveArgs a = wave_args(c, tilt, dz, B);
+    WaveArgs a = wave_args(c, tilt, dz, B);
+    // a step with tilts and dz frozen neither keeps nor reads the spectra Y_s
+    // (their only use is those gradients); no later call may then reuse its
+    // waves.  Other callers' forwards keep everything for a reuse to come.
+    a.spectra = !fuse || g_tilt || g_dz ? 1 : 0;
     const double* scale = at<double>(c, c->L.scal) + 1;     // the batch factor of w (after loss_final)
     // object-gradient scatter of batch rows [j0, j1) on stream st; `last`
     // (the batch's final scatter) runs the fused object Adam when asked
@@ -1660,7 +1669,7 @@ ptyr_status run_adjoint(ptyr_ctx* c, const float* amp, const float* phase, const
         }
         gradient_chains(c, a, 0, BM, c->stream);
     }
-    c->fwd_valid = 1;
+    c->fwd_valid = a.spectra;
     c->fwd_B = B;
     if (!scattered) {
         if (!fold) loss_final(c, 1, B, loss_dev, c->stream, true);
@@ -1898,10 +1907,9 @@ ptyr_status ptyr_step(ptyr_ctx* c, ptyr_params* p, const int* idx, int B, const 
         const size_t sizes[6] = {nobj, nobj, nprb, npos, ntilt, 1};
         A.off[0] = 0;
         for (int k = 0; k < 6; ++k) {
-            // a zero rate leaves the parameter and its moments alone; the
-            // object and probe gradients are then not even accumulated, the
-            // position / tilt / dz ones are and only need clearing.  The
-            // object (k < 2) was updated by the fused scatter.
+            // a zero rate leaves the parameter and its moments alone, and its
+            // gradient is not formed (its buffer stays zero).  The object
+            // (k < 2) is updated by the fused scatter.
             const bool on = rates[k] > 0.f && k >= 2;
             A.p[k] = params[k];
             A.g[k] = grads[k];
@@ -1909,7 +1917,7 @@ ptyr_status ptyr_step(ptyr_ctx* c, ptyr_params* p, const int* idx, int B, const 
             A.v[k] = mv[k][1];
             A.lr[k] = rates[k];
             A.upd[k] = on ? 1 : 0;
-            A.off[k + 1] = A.off[k] + ((on || k >= 3) ? sizes[k] : 0);
+            A.off[k + 1] = A.off[k] + (on ? sizes[k] : 0);
         }
         sa.b1 = lr->beta1;
         sa.b2 = lr->beta2;
@@ -1919,7 +1927,8 @@ ptyr_status ptyr_step(ptyr_ctx* c, ptyr_params* p, const int* idx, int B, const 
     }
     st = run_adjoint(c, p->amp, p->phase, p->probe, p->pos, p->tilt, p->dz, idx, p->n_pos, B, I_meas_all,
                      rates[0] > 0.f ? gamp : nullptr, rates[1] > 0.f ? gphase : nullptr,
-                     rates[2] > 0.f ? gprobe : nullptr, gpos, gtilt, gdz, loss_dev, 0, &oa, &sa);
+                     rates[2] > 0.f ? gprobe : nullptr, rates[3] > 0.f ? gpos : nullptr,
+                     rates[4] > 0.f ? gtilt : nullptr, rates[5] > 0.f ? gdz : nullptr, loss_dev, 0, &oa, &sa);
     if (st != PTYR_OK) return st;
     c->step_grads_clear = 1;
     p->step = t;

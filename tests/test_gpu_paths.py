@@ -2,10 +2,11 @@
 the FP64 oracle, at the sizes where a rule or a remainder changes."""
 import numpy as np
 import pytest
-
-from paper_2505_07814_amd import synth
+import torch
 
 from oracle import constraints as oc
+from paper_2505_07814_amd import synth
+from paper_2505_07814_amd.ptyr import AdamState
 from test_gpu_constraints import T, engine, rz_bound
 from test_gpu_parity import Case, _check_grads
 
@@ -69,3 +70,31 @@ def test_kz_filter_passes(S, H, W):
     for got, field in ((a, amp), (p, ph)):
         ref = oc.kz_filter(field, 0.8, 0.5, 0.2, 5.0)
         assert np.linalg.norm(got.cpu().numpy() - ref) <= 1e-5 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("N,S,M,B", [(64, 3, 2, 5), (64, 3, 5, 110), (128, 3, 2, 3), (256, 2, 2, 2)])
+def test_step_with_frozen_tilt_and_dz(N, S, M, B):
+    """A step with tilts and dz frozen (no Y_s kept, no such sums) updates the
+    other parameters exactly as one that also refines them, leaves tilts, dz
+    and their moments alone, and a later gradient does not reuse its waves."""
+    print(f"frozen tilt / dz N={N} S={S} M={M} B={B}", flush=True)
+    c = Case(synth.small_case(N=N, S=S, M=M, B=B, H=N + 40, W=N + 47, seed=47), perturb=True)
+    full = dict(amp=1e-3, phase=2e-3, probe=1e-2, pos=1e-2, tilt=1e-4, dz=1e-1)
+    out = []
+    for lr in (full, dict(full, tilt=0.0, dz=0.0)):
+        eng = c.engine(n_scan=B)
+        st = AdamState(*c.gpu_args())
+        eng.step(st, T(np.arange(B, dtype=np.int32)), T(c.meas), lr)
+        eng.sync()
+        out.append((eng, st))
+    (_, a), (eng, b) = out
+    for k in ("amp", "phase", "probe", "pos"):
+        assert torch.equal(getattr(a, k), getattr(b, k)), k
+        assert torch.equal(a.m[k], b.m[k]) and torch.equal(a.v[k], b.v[k]), k
+    assert np.array_equal(b.tilt.cpu().numpy(), c.tilt) and float(b.dz) == float(c.dz)
+    assert not b.m["tilt"].any() and not b.v["dz"].any()
+    args = tuple(getattr(b, k) for k in b.NAMES)
+    l0, g0 = eng.adjoint(*args, T(c.meas), reuse=True)
+    l1, g1 = eng.adjoint(*args, T(c.meas))
+    eng.sync()
+    assert all(torch.equal(g0[k], g1[k]) for k in g0) and torch.equal(l0, l1)
