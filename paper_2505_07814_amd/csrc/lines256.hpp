@@ -30,25 +30,40 @@ constexpr int N256 = 256;
 constexpr int LINES256 = 16;                   // lines per workgroup
 constexpr int NBLK256 = N256 / LINES256;       // line blocks per wave
 
+// The exchange of either geometry moves the real parts, then the imaginary
+// parts, through a float buffer (SPLIT): half the LDS, so that five to seven
+// workgroups share a compute unit instead of three and a 2048-workgroup pass
+// does not leave a third of its last round empty.  The paddings keep a wave's
+// 64 accesses in different banks.
 // lanes along the line (row passes): thread = line * 16 + lane
 struct RowGeo256 {
     static constexpr int NL = 256, L = 16, SB = 17, SL = 272;
     static constexpr bool WAVE_LOCAL = true;        // the 16 lanes of a line are in one wave
+    static constexpr bool SPLIT = true;
 };
 // lanes across lines (column passes): thread = lane * 16 + line, so the lanes
 // of a line span all four waves and an exchange needs a workgroup barrier
 struct ColGeo256 {
+    static constexpr int NL = 256, L = 16, SB = 17, SL = 324;
+    static constexpr bool WAVE_LOCAL = false;
+    static constexpr bool SPLIT = true;
+};
+// column passes through the whole-value exchange (two barriers instead of
+// four), for the gradient's, which its registers hold to three workgroups per
+// compute unit anyway (51.6 us a pass; 53.9 with the split exchange)
+struct WideColGeo256 {
     static constexpr int NL = 256, L = 16, SB = 17, SL = 274;
     static constexpr bool WAVE_LOCAL = false;
 };
-constexpr int LDS256 = (LINES256 - 1) * 274 + 15 * 17 + 16;
+// float2 slots of the exchange buffers (16 lines)
+constexpr int ROW_LDS256 = LINES256 * 272 / 2, COL_LDS256 = LINES256 * 324 / 2, WIDE_COL_LDS256 = LINES256 * 274;
 
+// tables of a column pass (a row pass needs the twiddles only)
 struct Tables256 {
     float4 tw[N256];       // tw[b*16 + c] = exp(-2 pi i c b / 256)
-    float4 h[N256];        // propagator factor along the pass direction
-    float2 r[N256];        // shift ramp along the pass direction
-    float4 hl[LINES256];   // propagator factor of each line of the block (column passes)
-    float2 rl[LINES256];   // shift ramp of each line of the block (column passes)
+    float4 h[N256];        // propagator factor along y
+    float4 hl[LINES256];   // propagator factor of each of the block's columns
+    float2 rl[LINES256];   // shift ramp of each of the block's columns
 };
 
 // The factors of one batch position, both axes (0: y, 1: x), all 256
@@ -88,19 +103,17 @@ __global__ __launch_bounds__(256) void k256_tables(WaveArgs a, float4* tw, PosTa
     }
 }
 
-// A workgroup's tables: the twiddles and, for its position, the factors along
-// the pass direction (AXIS 0: y, 1: x) for all 256 frequencies and those of
-// the block's 16 lines along the other axis.
-template <int AXIS>
-__device__ __forceinline__ void load256(Tables256& t, const float4* tw, const PosTab256* tab, int j, int line0) {
+// A column pass's tables: the twiddles and, for its position, the propagator
+// along y and the factors of the block's 16 columns.  (The shift ramp along
+// the lines is used by the first and last passes only, which read it from the
+// position's table.)
+__device__ __forceinline__ void load256(Tables256& t, const float4* tw, const PosTab256& T, int line0) {
     const int n = threadIdx.x;                       // blockDim.x == 256
-    const PosTab256& T = tab[j];
     t.tw[n] = tw[n];
-    t.h[n] = T.h[AXIS][n];
-    t.r[n] = T.r[AXIS][n];
+    t.h[n] = T.h[0][n];
     if (n < LINES256) {
-        t.hl[n] = T.h[1 - AXIS][line0 + n];
-        t.rl[n] = T.r[1 - AXIS][line0 + n];
+        t.hl[n] = T.h[1][line0 + n];
+        t.rl[n] = T.r[1][line0 + n];
     }
     __syncthreads();
 }
@@ -151,33 +164,34 @@ struct Pass256 {
 // pass (for s == 0 the shifted probe still lacking its x ramp); keeps phi_s,
 // transmits by O_s and transforms along x.
 __global__ __launch_bounds__(256) void k256_fwd_row(Pass256 P) {
-    __shared__ float2 lds[LDS256];
-    __shared__ Tables256 tab;
+    __shared__ float2 lds[ROW_LDS256];
+    __shared__ float4 tw[N256];
     const WaveArgs& a = P.a;
     const int ch = a.chain0 + blockIdx.x / NBLK256, blk = blockIdx.x % NBLK256;
     const int j = ch / a.M;
     const PosInfo pi = a.pinfo[j];
     if (pi.ty < 0) return;
     const int l = threadIdx.x / 16, c = threadIdx.x % 16, y = blk * LINES256 + l;
-    load256<1>(tab, P.tw, P.tab, j, blk * LINES256);
+    tw[threadIdx.x] = P.tw[threadIdx.x];
+    __syncthreads();
     float2* w = P.wave + (size_t)ch * N256 * N256;
     const Slots<N256> sl(a, ch);
     const bool full = sl.base && a.keep == KEEP_FULL;
     float2 v[16], ov[16];
     rows_load(v, full ? sl.phi(P.s) : w, y, c);
-    // the object patch is read now, so that its latency overlaps the line DFT
-    // (three workgroups per CU by LDS leave room for the extra registers)
     const float2* Os = chain_object(a, ch % a.M) + (size_t)P.s * a.H * a.W + (size_t)(pi.ty + y) * a.W + pi.tx;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) ov[r] = Os[c + 16 * r];
     if (P.s == 0) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) v[r] = cmul(v[r], tab.r[c + 16 * r]);
+        for (int r = 0; r < 16; ++r) v[r] = cmul(v[r], P.tab[j].r[1][c + 16 * r]);
     }
-    mid2nat<RowGeo256, +1>(v, lds, tab.tw, l, c);                      // phi_s (space)
+    mid2nat<RowGeo256, +1>(v, lds, tw, l, c);                      // phi_s (space)
+    // (read before the DFT the patch's 32 registers cost more in workgroups
+    // per compute unit than its latency: pass 34.2 us, here 32.3)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) ov[r] = Os[c + 16 * r];
 #pragma unroll
     for (int r = 0; r < 16; ++r) v[r] = cmul(v[r], ov[r]);
-    nat2mid<RowGeo256, -1>(v, lds, tab.tw, l, c);
+    nat2mid<RowGeo256, -1>(v, lds, tw, l, c);
     rows_store(v, w, y, c);
 }
 
@@ -185,7 +199,7 @@ __global__ __launch_bounds__(256) void k256_fwd_row(Pass256 P) {
 // Phat R_y / N); 0 <= s < S-1 propagates to slice s+1 (keeping Y'_{s+1});
 // s == S-1 forms the far field and its intensity.
 __global__ __launch_bounds__(256) void k256_fwd_col(Pass256 P) {
-    __shared__ float2 lds[LDS256];
+    __shared__ float2 lds[COL_LDS256];
     __shared__ Tables256 tab;
     const WaveArgs& a = P.a;
     const int ch = a.chain0 + blockIdx.x / NBLK256, blk = blockIdx.x % NBLK256;
@@ -200,7 +214,7 @@ __global__ __launch_bounds__(256) void k256_fwd_col(Pass256 P) {
         }
         return;
     }
-    load256<0>(tab, P.tw, P.tab, j, blk * LINES256);
+    load256(tab, P.tw, P.tab[j], blk * LINES256);
     float2* w = P.wave + (size_t)ch * N256 * N256;
     const Slots<N256> sl(a, ch);
     const bool full = sl.base && a.keep == KEEP_FULL;
@@ -209,7 +223,7 @@ __global__ __launch_bounds__(256) void k256_fwd_col(Pass256 P) {
         cols_load(v, chain_probe(a, m, N256 * N256), x, c);
         const float sc = 1.0f / N256;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) v[r] = cscale(cmul(v[r], tab.r[c + 16 * r]), sc);
+        for (int r = 0; r < 16; ++r) v[r] = cscale(cmul(v[r], P.tab[j].r[0][c + 16 * r]), sc);
         mid2nat<ColGeo256, +1>(v, lds, tab.tw, l, c);
         cols_store(v, full ? sl.phi(0) : w, x, c);                      // Z_0
         return;
@@ -235,8 +249,10 @@ __global__ __launch_bounds__(256) void k256_fwd_col(Pass256 P) {
 // along y.  1 <= s < S: the adjoint of slice s's propagation (after the row
 // pass of slice s): G^ -> dz / tilt partial sums with Y'_s -> conj(H) G^ / N^2
 // -> inverse along y.  s == 0: probe-spectrum and position terms.
+// SPECS: whether Y_s and the dz / tilt sums are wanted.
+template <bool SPECS>
 __global__ __launch_bounds__(256) void k256_grad_col(Pass256 P) {
-    __shared__ float2 lds[LDS256];
+    __shared__ float2 lds[WIDE_COL_LDS256];
     __shared__ Tables256 tab;
     const WaveArgs& a = P.a;
     const int ch = a.chain0 + blockIdx.x / NBLK256, blk = blockIdx.x % NBLK256;
@@ -253,7 +269,7 @@ __global__ __launch_bounds__(256) void k256_grad_col(Pass256 P) {
         }
         return;
     }
-    load256<0>(tab, P.tw, P.tab, j, blk * LINES256);
+    load256(tab, P.tw, P.tab[j], blk * LINES256);
     const Slots<N256> sl(a, ch);
     float2* w = P.wave + (size_t)ch * N256 * N256;
     const float inv_n = 1.0f / N256, inv_n2 = 1.0f / ((float)N256 * N256);
@@ -263,19 +279,18 @@ __global__ __launch_bounds__(256) void k256_grad_col(Pass256 P) {
         const float* wj = a.wgt + (size_t)j * N256 * N256;
 #pragma unroll
         for (int r = 0; r < 16; ++r) v[r] = cscale(v[r], wj[(c + 16 * r) * N256 + x] * inv_n2);
-        mid2nat<ColGeo256, +1>(v, lds, tab.tw, l, c);
+        mid2nat<WideColGeo256, +1>(v, lds, tab.tw, l, c);
         cols_store(v, w, x, c);
         if (threadIdx.x < 8) part[threadIdx.x] = 0.0;
         return;
     }
     cols_load(v, w, x, c);
     float2 yv_[16];                      // Z_s, read now so that its latency overlaps the DFT
-    const bool specs = P.s > 0 && a.spectra;          // Y_s only enters the dz / tilt sums
-    if (specs) cols_load(yv_, sl.phi(P.s), x, c);
-    nat2mid<ColGeo256, -1>(v, lds, tab.tw, l, c);                       // G^ (raw), (k_y, k_x)
-    if (specs) {
+    if (SPECS && P.s > 0) cols_load(yv_, sl.phi(P.s), x, c);
+    nat2mid<WideColGeo256, -1>(v, lds, tab.tw, l, c);                       // G^ (raw), (k_y, k_x)
+    if (SPECS && P.s > 0) {
         // Y'_s = F_y[Z_s] / N: the forward's inverse along y undone (1/N is exact)
-        nat2mid<ColGeo256, -1>(yv_, lds, tab.tw, l, c);
+        nat2mid<WideColGeo256, -1>(yv_, lds, tab.tw, l, c);
 #pragma unroll
         for (int r = 0; r < 16; ++r) yv_[r] = cscale(yv_[r], inv_n);
     }
@@ -288,7 +303,7 @@ __global__ __launch_bounds__(256) void k256_grad_col(Pass256 P) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int ky_i = c + 16 * r;
-            if (specs) {
+            if constexpr (SPECS) {
                 const float2 yv = yv_[r];
                 const double e = fma((double)v[r].y, (double)yv.x, -((double)v[r].x * (double)yv.y));   // Im(G^ conj(Y))
                 const double ky = sfreq<N256>(ky_i) * dk;
@@ -298,7 +313,7 @@ __global__ __launch_bounds__(256) void k256_grad_col(Pass256 P) {
             }
             v[r] = cscale(tmul<true>(tmul<true>(v[r], tab.h[ky_i]), hx), inv_n2);
         }
-        mid2nat<ColGeo256, +1>(v, lds, tab.tw, l, c);
+        mid2nat<WideColGeo256, +1>(v, lds, tab.tw, l, c);
         cols_store(v, w, x, c);
     } else {
         const float2* Pm = chain_probe(a, m, N256 * N256);
@@ -309,14 +324,14 @@ __global__ __launch_bounds__(256) void k256_grad_col(Pass256 P) {
         for (int r = 0; r < 16; ++r) {
             const int ky_i = c + 16 * r;
             const float2 G0 = cscale(v[r], inv_n);
-            const float2 R = cmul(tab.r[ky_i], rx);
+            const float2 R = cmul(P.tab[j].r[0][ky_i], rx);
             gP[ky_i * N256 + x] = cmulc(G0, R);                          // conj(R) G^_0
             const float2 z = cmulc(cmul(Pm[ky_i * N256 + x], R), G0);    // Phat R conj(G^_0)
             acc[3] = fma((double)z.y, (double)sfreq<N256>(ky_i) / N256, acc[3]);
             acc[4] = fma((double)z.y, qx, acc[4]);
         }
     }
-    if (P.s > 0 && !specs) return;                      // nothing to add to the partial sums
+    if (P.s > 0 && !SPECS) return;                      // nothing to add to the partial sums
     block_sum<5>(acc, reinterpret_cast<double*>(lds));
     if (threadIdx.x == 0)
         for (int k = 0; k < 5; ++k) part[k] += acc[k];
@@ -326,25 +341,32 @@ __global__ __launch_bounds__(256) void k256_grad_col(Pass256 P) {
 // and object mode (probe modes p0 .. p0 + mg - 1): per chain the wave holds
 // (y, k_x) of G after the inverse along y; the inverse along x gives
 // G_chi_s, phi_s is rebuilt from the kept Z_s as the forward row pass formed
-// it, the group's patch gradient sum_p conj(phi_s) G_chi (in probe-mode
-// order) is summed in registers, and G_phi = conj(O_s) G_chi is transformed
-// along x.  The object patch is read once for the group and the summed patch
-// gradient written once, mg times less patch-gradient traffic (written here,
-// read by the object scatter) than one per chain.  The next chain's phi_s is
-// read while the current chain's line DFT runs.
-__global__ __launch_bounds__(256) void k256_grad_row(Pass256 P) {
-    __shared__ float2 lds[LDS256];
-    __shared__ Tables256 tab;
+// it, the group's patch gradient sum_p conj(phi_s) G_chi is summed in
+// registers, and G_phi = conj(O_s) G_chi is transformed along x.  The object
+// patch is read once for the group and the summed patch gradient written
+// once, mg times less patch-gradient traffic (written here, read by the object
+// scatter) than one per chain.  The next chain's phi_s is read while the
+// current chain's line DFT runs.
+// HV: 256-thread halves of the workgroup, of which half h takes the chains p =
+// h, h + HV, ...; their patch gradients are added in half order at the end.
+// With one half and one workgroup per compute unit (256 workgroups at 16
+// positions) each SIMD holds a single wave, whose latencies nothing hides.
+template <int HV>
+__global__ __launch_bounds__(256 * HV, 2) void k256_grad_row(Pass256 P) {
+    __shared__ float2 lds[HV * ROW_LDS256];
+    __shared__ float4 tw[N256];
     const WaveArgs& a = P.a;
     const int mg = P.mg, grp = a.chain0 / mg + blockIdx.x / NBLK256, blk = blockIdx.x % NBLK256;
     const int ch0 = grp * mg, j = ch0 / a.M;
     const PosInfo pi = a.pinfo[j];
     if (pi.ty < 0) return;
-    const int l = threadIdx.x / 16, c = threadIdx.x % 16, y = blk * LINES256 + l;
-    load256<1>(tab, P.tw, P.tab, j, blk * LINES256);
+    const int half = threadIdx.x / 256;
+    const int ll = threadIdx.x / 16, l = ll % LINES256, c = threadIdx.x % 16, y = blk * LINES256 + l;   // ll: LDS line
+    if (threadIdx.x < N256) tw[threadIdx.x] = P.tw[threadIdx.x];
+    __syncthreads();
     float2 v[16], ph[16], ov[16], acc[16];
-    rows_load(v, P.wave + (size_t)ch0 * N256 * N256, y, c);
-    rows_load(ph, Slots<N256>(a, ch0).phi(P.s), y, c);
+    rows_load(v, P.wave + (size_t)(ch0 + half) * N256 * N256, y, c);
+    rows_load(ph, Slots<N256>(a, ch0 + half).phi(P.s), y, c);
     // the object patch (the same for the group's chains) and the first
     // chain's G and phi_s are read now, so that their latency overlaps the
     // line DFT
@@ -354,23 +376,36 @@ __global__ __launch_bounds__(256) void k256_grad_row(Pass256 P) {
         ov[r] = Os[c + 16 * r];
         acc[r] = make_float2(0.f, 0.f);
     }
-    for (int p = 0; p < mg; ++p) {
+    for (int p = half; p < mg; p += HV) {                              // exchanges are within a wave: no barriers
         const int ch = ch0 + p;
         if (P.s == 0) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) ph[r] = cmul(ph[r], tab.r[c + 16 * r]);
+            for (int r = 0; r < 16; ++r) ph[r] = cmul(ph[r], P.tab[j].r[1][c + 16 * r]);
         }
-        mid2nat<RowGeo256, +1>(ph, lds, tab.tw, l, c);                 // phi_s (space)
-        mid2nat<RowGeo256, +1>(v, lds, tab.tw, l, c);                  // G_chi_s (space)
+        mid2nat<RowGeo256, +1>(ph, lds, tw, ll, c);                    // phi_s (space)
+        mid2nat<RowGeo256, +1>(v, lds, tw, ll, c);                     // G_chi_s (space)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             acc[r] = cadd(acc[r], cmulc(v[r], ph[r]));                  // conj(phi) G_chi
             v[r] = cmulc(v[r], ov[r]);                                  // conj(O) G_chi
         }
-        if (p + 1 < mg) rows_load(ph, Slots<N256>(a, ch + 1).phi(P.s), y, c);
-        nat2mid<RowGeo256, -1>(v, lds, tab.tw, l, c);
+        if (p + HV < mg) rows_load(ph, Slots<N256>(a, ch + HV).phi(P.s), y, c);
+        nat2mid<RowGeo256, -1>(v, lds, tw, ll, c);
         rows_store(v, P.wave + (size_t)ch * N256 * N256, y, c);
-        if (p + 1 < mg) rows_load(v, P.wave + (size_t)(ch + 1) * N256 * N256, y, c);
+        if (p + HV < mg) rows_load(v, P.wave + (size_t)(ch + HV) * N256 * N256, y, c);
+    }
+    if constexpr (HV == 2) {
+        // 16 x 256 float2, thread-major per register: fits the two halves' buffers
+        static_assert(HV * ROW_LDS256 >= 16 * 256, "patch gradient of one half");
+        __syncthreads();
+        if (half == 1) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) lds[r * 256 + threadIdx.x % 256] = acc[r];
+        }
+        __syncthreads();
+        if (half == 1) return;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = cadd(acc[r], lds[r * 256 + threadIdx.x]);
     }
     float2* go = a.gO + (((size_t)grp * a.S + P.s) * N256 + y) * N256;
 #pragma unroll
@@ -382,7 +417,7 @@ __global__ __launch_bounds__(256) void k256_grad_row(Pass256 P) {
 // stores or accumulates.
 template <int SG, bool ROWS, bool ACC>
 __global__ __launch_bounds__(256) void k256_fft(const float2* in, float2* out) {
-    __shared__ float2 lds[LDS256];
+    __shared__ float2 lds[COL_LDS256];
     __shared__ float4 tw[N256];
     const int wv = blockIdx.x / NBLK256, blk = blockIdx.x % NBLK256;
     {

@@ -1242,13 +1242,15 @@ void tables256(ptyr_ctx* c, const WaveArgs& a, hipStream_t st) {
                        reinterpret_cast<PosTab256*>(at<float4>(c, c->L.tab256) + N256));
 }
 // probe modes whose patch gradients the N = 256 gradient row pass sums per
-// workgroup: the largest divisor of the probe modes up to 8 (measured at the
-// 16-position, 8-mode batch: groups of 8, 4 and 2 give 6.65, 6.76 and
-// 7.08 ms per step); 1 for N = 64 and 128
-int row_group(const ptyr_geom& g) {
+// workgroup: the largest divisor of the probe modes up to 8 that leaves a
+// workgroup per compute unit (measured at the 16-position, 8-mode batch, 256
+// workgroups in groups of 8: groups of 8, 4 and 2 gave 6.65, 6.76 and 7.08 ms
+// per step, the scatter reading more patch gradients); 1 for N = 64 and 128
+int row_group(const ptyr_ctx* c, int B) {
+    const ptyr_geom& g = c->g;
     if (g.N != 256) return 1;
     for (int d = 8; d > 1; --d)
-        if (g.M % d == 0) return d;
+        if (g.M % d == 0 && (size_t)B * (chain_modes(g) / d) * NBLK256 >= (size_t)c->n_cu) return d;
     return 1;
 }
 void forward256(ptyr_ctx* c, WaveArgs a, int c0, int nc, hipStream_t st) {
@@ -1267,16 +1269,19 @@ void gradient256(ptyr_ctx* c, WaveArgs a, int c0, int nc, hipStream_t st) {
     a.chain0 = c0;
     const dim3 grid(nc * NBLK256), blk(256);
     tables256(c, a, st);
-    hipLaunchKernelGGL(k256_grad_col, grid, blk, 0, st, pass256(c, a, a.S));
-    // the row pass takes row_group(g) chains per workgroup (c0 and nc are
+    const auto grad_col = a.spectra ? k256_grad_col<true> : k256_grad_col<false>;
+    hipLaunchKernelGGL(grad_col, grid, blk, 0, st, pass256(c, a, a.S));
+    // the row pass takes row_group(c, B) chains per workgroup (c0 and nc are
     // multiples of it: N = 256 batches are not split)
-    const int mg = row_group(c->g);
+    const int mg = row_group(c, a.B);
     const dim3 rgrid(nc / mg * NBLK256);
+    const bool two = mg > 1 && rgrid.x < 2 * (unsigned)c->n_cu;      // two halves per workgroup (k256_grad_row)
     for (int s = a.S - 1; s >= 0; --s) {
         Pass256 P = pass256(c, a, s);
         P.mg = mg;
-        hipLaunchKernelGGL(k256_grad_row, rgrid, blk, 0, st, P);
-        hipLaunchKernelGGL(k256_grad_col, grid, blk, 0, st, pass256(c, a, s));
+        if (two) hipLaunchKernelGGL(k256_grad_row<2>, rgrid, dim3(512), 0, st, P);
+        else hipLaunchKernelGGL(k256_grad_row<1>, rgrid, blk, 0, st, P);
+        hipLaunchKernelGGL(grad_col, grid, blk, 0, st, pass256(c, a, s));
     }
 }
 // N = 64 with at most two chains per compute unit: the fused kernels run with
@@ -1557,8 +1562,8 @@ ptyr_status run_adjoint(ptyr_ctx* c, const float* amp, const float* phase, const
             ad.assign = fuse && j0 == 0 ? 1 : 0;
         }
         // patch gradients per position and object mode: one per group of
-        // row_group(g) probe modes (the N = 256 row pass sums each group)
-        const int mg = row_group(g), Mg = g.M / mg, Mcg = M / mg;
+        // row_group(c, B) probe modes (the N = 256 row pass sums each group)
+        const int mg = row_group(c, B), Mg = g.M / mg, Mcg = M / mg;
         const int rows = scatter_rows(c);
         const dim3 grid(((g.H + 8 * rows - 1) / (8 * rows)) * ((g.W + 31) / 32), g.S * obj_modes(g));
         const bool mb8 = Mg % 8 == 0;

@@ -216,6 +216,13 @@ template <class GEO> struct XLaneX<GEO, decltype(void(GEO::XLANE))> {
     static constexpr bool value = GEO::XLANE;
 };
 
+template <class GEO, class = void> struct SplitX {
+    static constexpr bool value = false;
+};
+template <class GEO> struct SplitX<GEO, decltype(void(GEO::SPLIT))> {
+    static constexpr bool value = GEO::SPLIT;
+};
+
 // position along the line of register r
 template <int N, int K> __device__ __forceinline__ int line_pos(int c, int r) {
     constexpr int L = N / 16;
@@ -422,6 +429,21 @@ __device__ __forceinline__ void nat2mid(float2 (&v)[16], float2* lds, const TW& 
         for (int be = 0; be < G; ++be) dftL<L, SG>(&v[be * L]);
         return;
     }
+    if constexpr (SplitX<GEO>::value) {
+        static_assert(L == 16, "one block per line");
+        float* f = reinterpret_cast<float*>(lds);
+#pragma unroll
+        for (int part = 0; part < 2; ++part) {
+#pragma unroll
+            for (int b = 0; b < 16; ++b) f[slot_x<GEO>(l, b, c)] = part ? v[b].y : v[b].x;
+            exchange_sync<GEO>();
+#pragma unroll
+            for (int a = 0; a < 16; ++a) (part ? v[a].y : v[a].x) = f[slot_x<GEO>(l, c, a)];
+            exchange_sync<GEO>();
+        }
+        dftL<L, SG>(v);
+        return;
+    }
 #pragma unroll
     for (int h = 0; h < R; ++h) {
         constexpr int NB = 16 / R, NBE = G / R;
@@ -447,6 +469,21 @@ __device__ __forceinline__ void mid2nat(float2 (&v)[16], float2* lds, const TW& 
     for (int be = 0; be < G; ++be) dftL<L, SG>(&v[be * L]);
     if constexpr (XLaneX<GEO>::value) {
         xlane_transpose<L>(v);
+        twiddles<L, SG>(v, tw, c);
+        dft16<SG>(v);
+        return;
+    }
+    if constexpr (SplitX<GEO>::value) {
+        float* f = reinterpret_cast<float*>(lds);
+#pragma unroll
+        for (int part = 0; part < 2; ++part) {
+#pragma unroll
+            for (int a = 0; a < 16; ++a) f[slot_x<GEO>(l, c, a)] = part ? v[a].y : v[a].x;
+            exchange_sync<GEO>();
+#pragma unroll
+            for (int b = 0; b < 16; ++b) (part ? v[b].y : v[b].x) = f[slot_x<GEO>(l, b, c)];
+            exchange_sync<GEO>();
+        }
         twiddles<L, SG>(v, tw, c);
         dft16<SG>(v);
         return;

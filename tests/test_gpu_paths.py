@@ -98,3 +98,12 @@ def test_step_with_frozen_tilt_and_dz(N, S, M, B):
     l1, g1 = eng.adjoint(*args, T(c.meas))
     eng.sync()
     assert all(torch.equal(g0[k], g1[k]) for k in g0) and torch.equal(l0, l1)
+
+
+@pytest.mark.parametrize("M,B", [(8, 3), (3, 11), (5, 4), (8, 20)])
+def test_gradient_256_row_groups(M, B):
+    """N = 256 row pass: modes in groups of what leaves each compute unit a
+    workgroup, by two halves of a workgroup (odd groups too) or by one."""
+    print(f"gradient N=256 S=2 M={M} B={B}", flush=True)
+    c = Case(synth.small_case(N=256, S=2, M=M, B=B, H=300, W=310, seed=53))
+    _check_grads(c, c.engine())
