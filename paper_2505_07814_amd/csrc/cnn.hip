@@ -3,6 +3,7 @@
 // training gradients, Adam and patch stitching.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <new>
 
@@ -15,7 +16,8 @@ struct ptyr_cnn {
     int B_max;
     char* ws;
     hipStream_t stream;
-    size_t X[NLAYER], G[NLAYER], out, wbf, wt, wpart, lpart, loss, err, total;
+    size_t X[NLAYER], G[NLAYER], out, wbf, wt, wpart[NLAYER], lpart, loss, err, total;
+    int n_cu;
 };
 
 namespace {
@@ -24,14 +26,9 @@ constexpr int LOSS_BLOCKS = 256;
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-size_t wpart_floats(int B) {
-    size_t m = 0;
-    for (int l = 0; l < NLAYER; ++l) {
-        const size_t nchunk = ((size_t)B * HOUT[l] * HOUT[l] + WCHUNK - 1) / WCHUNK;
-        const size_t f = nchunk * (w_size(l) + COUTP[l]);
-        if (f > m) m = f;
-    }
-    return m;
+// workgroups (partial sums) of layer l's weight gradient for B samples
+template <int L> int wgrad_parts(int B) {
+    return (int)std::min<long>((long)B * WGrad<L>::TPS, WPARTS);
 }
 
 // workspace offsets for batches of up to B neighbourhoods
@@ -47,7 +44,9 @@ void layout(ptyr_cnn* c, int B) {
     c->out = take((size_t)B * OUT * OUT * 4);
     c->wbf = take((size_t)NPARAM * 2);
     c->wt = take((size_t)WT_TOTAL * 2);
-    c->wpart = take(wpart_floats(B) * 4);
+    const int nw[NLAYER] = {wgrad_parts<0>(B), wgrad_parts<1>(B), wgrad_parts<2>(B), wgrad_parts<3>(B),
+                            wgrad_parts<4>(B)};
+    for (int l = 0; l < NLAYER; ++l) c->wpart[l] = take((size_t)nw[l] * (w_size(l) + COUTP[l]) * 4);
     c->lpart = take(LOSS_BLOCKS * 8);
     c->loss = take(8);
     c->err = take(4);
@@ -66,37 +65,44 @@ int blocks_for(size_t n, int per = 256) {
 
 ptyr_status launched() { return hipGetLastError() == hipSuccess ? PTYR_OK : PTYR_E_DEVICE; }
 
-template <int L>
-void fwd_layer(ptyr_cnn* c, const float* params, int B, float* out) {
-    const int nblk = (B * HOUT[L] * HOUT[L] + 63) / 64;
-    __bf16* Y = L < NLAYER - 1 ? at<__bf16>(c, c->X[L + 1]) : nullptr;
-    hipLaunchKernelGGL(k_fwd<L>, dim3(nblk), dim3(256), 0, c->stream, at<__bf16>(c, c->X[L]),
-                       at<__bf16>(c, c->wbf) + w_off(L), params + b_off(L), Y, out, B);
+// Groups of 16 pixels per wave, and the workgroups for them: about twelve waves
+// per compute unit (what the weights' registers leave room for), each walking
+// its share; at least one group.
+struct GroupPlan {
+    int per, blocks;
+};
+GroupPlan group_plan(const ptyr_cnn* c, long groups) {
+    const long waves = 12L * c->n_cu;
+    const int per = (int)std::max(1L, (groups + waves - 1) / waves);
+    return {per, (int)((groups + 4L * per - 1) / (4L * per))};
 }
 
 template <int L>
-void bwd_layer(ptyr_cnn* c, int B, float* grad) {
-    constexpr int NT = kp(L) / 16, PW = w_size(L) + COUTP[L];
-    const int nchunk = (B * HOUT[L] * HOUT[L] + WCHUNK - 1) / WCHUNK;
-    hipLaunchKernelGGL(k_wgrad<L>, dim3(nchunk, (NT + wg_nt<L>() - 1) / wg_nt<L>()), dim3(256), 0, c->stream,
-                       at<__bf16>(c, c->G[L]), at<__bf16>(c, c->X[L]), at<float>(c, c->wpart), B);
-    // weights and bias are contiguous in the parameter vector: one reduction
-    hipLaunchKernelGGL(k_wreduce, dim3((PW + 31) / 32), dim3(256), 0, c->stream, at<float>(c, c->wpart), nchunk, PW,
-                       grad + w_off(L));
-    if constexpr (L > 0) {
-        const int nblk = (B * HIN[L] * HIN[L] + 63) / 64;
-        hipLaunchKernelGGL(k_dgrad<L>, dim3(nblk), dim3(256), 0, c->stream, at<__bf16>(c, c->G[L]),
-                           at<__bf16>(c, c->wt) + wt_off(L), at<__bf16>(c, c->X[L]), at<__bf16>(c, c->G[L - 1]), B);
-    }
+void fwd_layer(ptyr_cnn* c, const float* params, int B, float* out) {
+    const GroupPlan q = group_plan(c, (long)B * HOUT[L] * HOUT[L] / 16);
+    __bf16* Y = L < NLAYER - 1 ? at<__bf16>(c, c->X[L + 1]) : nullptr;
+    hipLaunchKernelGGL(k_fwd<L>, dim3(q.blocks), dim3(256), 0, c->stream, at<__bf16>(c, c->X[L]),
+                       at<__bf16>(c, c->wbf) + w_off(L), params + b_off(L), Y, out, B, q.per);
+}
+
+// dL/dz of layer L - 1 from that of layer L.  Stride 2: the four waves of a
+// workgroup take the four parity classes of the same rows.
+template <int L>
+void input_grad(ptyr_cnn* c, int B) {
+    const long groups = STRIDE[L] == 2 ? (long)B * HIN[L] : (long)B * HIN[L] * HIN[L] / 16;
+    GroupPlan q = group_plan(c, STRIDE[L] == 2 ? 4 * groups : groups);
+    if (STRIDE[L] == 2) q.blocks = (int)((groups + q.per - 1) / q.per);
+    hipLaunchKernelGGL(k_dgrad<L>, dim3(q.blocks), dim3(256), 0, c->stream, at<__bf16>(c, c->G[L]),
+                       at<__bf16>(c, c->wt) + wt_off(L), at<__bf16>(c, c->X[L]), at<__bf16>(c, c->G[L - 1]), B, q.per);
 }
 
 // weights to BF16, gathered log input, the five layers; output to `out`
 void run_forward(ptyr_cnn* c, const float* params, const float* pat, int n_pat, const int* nbr, int B, float* out) {
     const int nprep = NPARAM > WT_TOTAL ? NPARAM : WT_TOTAL;
-    hipLaunchKernelGGL(k_prep, dim3((nprep + 255) / 256), dim3(256), 0, c->stream, params, at<__bf16>(c, c->wbf),
-                       at<__bf16>(c, c->wt));
-    hipLaunchKernelGGL(k_input, dim3(blocks_for((size_t)B * IN * IN)), dim3(256), 0, c->stream, pat, n_pat, nbr, B,
-                       at<__bf16>(c, c->X[0]), at<int>(c, c->err));
+    const int np = (nprep + 255) / 256;
+    hipLaunchKernelGGL(k_input, dim3(np + blocks_for((size_t)B * IN * IN / 4)), dim3(256), 0, c->stream, pat, n_pat, nbr,
+                       B, at<__bf16>(c, c->X[0]), at<int>(c, c->err), params, at<__bf16>(c, c->wbf),
+                       at<__bf16>(c, c->wt), np);
     fwd_layer<0>(c, params, B, nullptr);
     fwd_layer<1>(c, params, B, nullptr);
     fwd_layer<2>(c, params, B, nullptr);
@@ -136,6 +142,12 @@ ptyr_status ptyr_cnn_create(int B_max, void* workspace, size_t ws_bytes, void* s
     if (ws_bytes < c->total) {
         delete c;
         return PTYR_E_NOMEM;
+    }
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || c->n_cu < 1) {
+        delete c;
+        return PTYR_E_DEVICE;
     }
     if (hipMemsetAsync(at<int>(c, c->err), 0, sizeof(int), c->stream) != hipSuccess) {
         delete c;
@@ -178,16 +190,34 @@ ptyr_status ptyr_cnn_gradient(ptyr_cnn* c, const float* params, const float* pat
     run_forward(c, params, patterns, n_pat, nbr, B, out);
     const int n = B * OUT * OUT;
     const int nblk = blocks_for(n) < LOSS_BLOCKS ? blocks_for(n) : LOSS_BLOCKS;
-    hipLaunchKernelGGL(k_mse_partial, dim3(nblk), dim3(256), 0, c->stream, out, target, n, at<double>(c, c->lpart));
-    hipLaunchKernelGGL(k_mse_final, dim3(1), dim3(64), 0, c->stream, at<double>(c, c->lpart), nblk, n,
-                       loss_dev ? loss_dev : at<double>(c, c->loss));
-    hipLaunchKernelGGL(k_mse_grad, dim3(blocks_for(n)), dim3(256), 0, c->stream, out, target, n,
+    hipLaunchKernelGGL(k_mse, dim3(nblk), dim3(256), 0, c->stream, out, target, n, at<double>(c, c->lpart),
                        at<__bf16>(c, c->G[NLAYER - 1]));
-    bwd_layer<4>(c, B, grad);
-    bwd_layer<3>(c, B, grad);
-    bwd_layer<2>(c, B, grad);
-    bwd_layer<1>(c, B, grad);
-    bwd_layer<0>(c, B, grad);
+    input_grad<4>(c, B);
+    input_grad<3>(c, B);
+    input_grad<2>(c, B);
+    input_grad<1>(c, B);
+    // every layer's weight gradient at once, then every layer's sum
+    WGradArgs wg{};
+    WReduceArgs wr{};
+    const int nw[NLAYER] = {wgrad_parts<0>(B), wgrad_parts<1>(B), wgrad_parts<2>(B), wgrad_parts<3>(B),
+                            wgrad_parts<4>(B)};
+    int most = 0, blocks = 1;
+    for (int l = 0; l < NLAYER; ++l) {
+        wg.G[l] = at<__bf16>(c, c->G[l]);
+        wg.X[l] = at<__bf16>(c, c->X[l]);
+        wg.part[l] = at<float>(c, c->wpart[l]);
+        wr.part[l] = wg.part[l];
+        wg.nw[l] = wr.nw[l] = nw[l];
+        most = std::max(most, nw[l]);
+        blocks += wreduce_blocks(l);
+    }
+    wg.B = B;
+    wr.loss_part = at<double>(c, c->lpart);
+    wr.nblk = nblk;
+    wr.n = n;
+    wr.loss = loss_dev ? loss_dev : at<double>(c, c->loss);
+    hipLaunchKernelGGL(k_wgrad, dim3(most, NLAYER), dim3(512), 0, c->stream, wg);
+    hipLaunchKernelGGL(k_wreduce, dim3(blocks), dim3(256), 0, c->stream, wr, grad);
     return launched();
 }
 
@@ -204,8 +234,8 @@ ptyr_status ptyr_cnn_adam(ptyr_cnn* c, float* params, const float* grad, float* 
 ptyr_status ptyr_cnn_stitch(ptyr_cnn* c, const float* patches, const float* centres, int P, int H, int W, float* img) {
     if (!c || !img || H < 1 || W < 1 || P < 0) return PTYR_E_ARG;
     if (P > 0 && (!patches || !centres)) return PTYR_E_ARG;
-    hipLaunchKernelGGL(k_stitch, dim3(blocks_for((size_t)H * W)), dim3(256), 0, c->stream, patches, centres, P, H, W,
-                       img);
+    hipLaunchKernelGGL(k_stitch, dim3((unsigned)(((H + 15) / 16) * ((W + 15) / 16))), dim3(256), 0, c->stream, patches,
+                       centres, P, H, W, img);
     return launched();
 }
 
