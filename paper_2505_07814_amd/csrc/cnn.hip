@@ -100,7 +100,7 @@ void input_grad(ptyr_cnn* c, int B) {
 void run_forward(ptyr_cnn* c, const float* params, const float* pat, int n_pat, const int* nbr, int B, float* out) {
     const int nprep = NPARAM > WT_TOTAL ? NPARAM : WT_TOTAL;
     const int np = (nprep + 255) / 256;
-    hipLaunchKernelGGL(k_input, dim3(np + blocks_for((size_t)B * IN * IN / 4)), dim3(256), 0, c->stream, pat, n_pat, nbr,
+    hipLaunchKernelGGL(k_input, dim3(np + blocks_for((size_t)B * IN * IN / 2)), dim3(256), 0, c->stream, pat, n_pat, nbr,
                        B, at<__bf16>(c, c->X[0]), at<int>(c, c->err), params, at<__bf16>(c, c->wbf),
                        at<__bf16>(c, c->wt), np);
     fwd_layer<0>(c, params, B, nullptr);

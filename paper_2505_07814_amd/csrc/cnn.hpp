@@ -98,44 +98,35 @@ __device__ __forceinline__ void prep_weights(const float* p, __bf16* wbf, __bf16
 // Gather the 9 patterns of each neighbourhood (nbr: B x 9 indices into the
 // n_pat patterns of 64 x 64) and store log(1 + max(I, 0)) as BF16 NHWC with 16
 // channels (9 used).  An index outside [0, n_pat) raises ERR_INDEX and reads
-// as an all-zero pattern.  Four consecutive pixels per thread, 16-byte reads
-// where the patterns are 16-byte aligned.  Workgroups before the nin last
-// convert the parameters (k_prep's work: see prep_weights), which needs
-// nothing of the input.
+// as an all-zero pattern.  A thread takes two pixels half a pattern apart, 18
+// reads in flight.  The nprep first workgroups convert the parameters
+// (prep_weights), which needs nothing of the input.
 __global__ __launch_bounds__(256) void k_input(const float* pat, int n_pat, const int* nbr, int B, __bf16* X0,
                                                int* err, const float* params, __bf16* wbf, __bf16* wt, int nprep) {
     if ((int)blockIdx.x < nprep) {
         prep_weights(params, wbf, wt, blockIdx.x * blockDim.x + threadIdx.x);
         return;
     }
-    const int n = B * IN * IN / 4;
-    const bool vec = (reinterpret_cast<uintptr_t>(pat) & 15) == 0;
+    constexpr int HALF = IN * IN / 2;
+    const int n = B * HALF;
     for (int q = (blockIdx.x - nprep) * blockDim.x + threadIdx.x; q < n; q += (gridDim.x - nprep) * blockDim.x) {
-        const int b = q / (IN * IN / 4), yx = 4 * (q % (IN * IN / 4));
-        float v[NB][4];
+        const int b = q / HALF, yx = q % HALF;                 // HALF is a multiple of the block: b is uniform
+        float v[2][NB];
 #pragma unroll
         for (int c = 0; c < NB; ++c) {
             const int j = nbr[b * NB + c];
             const bool ok = j >= 0 && j < n_pat;
             if (!ok && yx == 0) atomicOr(err, ERR_INDEX);
-            const float* src = pat + (size_t)(ok ? j : 0) * IN * IN + yx;
-            if (vec) {
-                const float4 t = *reinterpret_cast<const float4*>(src);
-                v[c][0] = t.x; v[c][1] = t.y; v[c][2] = t.z; v[c][3] = t.w;
-            } else {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[c][i] = src[i];
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[c][i] = ok ? log1pf(fmaxf(v[c][i], 0.f)) : 0.f;
+            for (int h = 0; h < 2; ++h) v[h][c] = ok ? pat[(size_t)j * IN * IN + yx + h * HALF] : 0.f;
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int h = 0; h < 2; ++h) {
             bf16x8 lo, hi = zero8();
 #pragma unroll
-            for (int c = 0; c < 8; ++c) lo[c] = (__bf16)v[c][i];
-            hi[0] = (__bf16)v[8][i];
-            bf16x8* dst = reinterpret_cast<bf16x8*>(X0 + ((size_t)4 * q + i) * 16);
+            for (int c = 0; c < 8; ++c) lo[c] = (__bf16)log1pf(fmaxf(v[h][c], 0.f));
+            hi[0] = (__bf16)log1pf(fmaxf(v[h][8], 0.f));
+            bf16x8* dst = reinterpret_cast<bf16x8*>(X0 + ((size_t)b * IN * IN + yx + h * HALF) * 16);
             dst[0] = lo;
             dst[1] = hi;
         }
@@ -594,7 +585,7 @@ __global__ void k_adam(float* p, const float* gr, float* m, float* v, int n, flo
 // of each wave tests one patch against the tile, 64 at a time, and the wave
 // walks the ballot, so the patches are visited in order and only those near
 // the tile by each pixel (with every pixel reading every centre, 64 patches on
-// a 144 x 144 image took 18 us).
+// a 144 x 144 image took 18 us; 6 us this way).
 __global__ __launch_bounds__(256) void k_stitch(const float* patches, const float* centres, int P, int H, int W,
                                                 float* img) {
     const int ntx = (W + 15) / 16, ty = ((int)blockIdx.x / ntx) * 16, tx = ((int)blockIdx.x % ntx) * 16;
@@ -610,13 +601,25 @@ __global__ __launch_bounds__(256) void k_stitch(const float* patches, const floa
             x0 = (int)rintf(centres[2 * q + 1]) - OUT / 2;
             near = ty + 16 > y0 && ty < y0 + OUT && tx + 16 > x0 && tx < x0 + OUT;
         }
-        for (unsigned long long m = __ballot(near); m; m &= m - 1) {
-            const int k = __builtin_ctzll(m);
-            const int py = y - __builtin_amdgcn_readlane(y0, k), px = x - __builtin_amdgcn_readlane(x0, k);
-            if (py >= 0 && py < OUT && px >= 0 && px < OUT) {
-                s += patches[(size_t)(p0 + k) * OUT * OUT + py * OUT + px];
-                ++cnt;
+        // eight patches' reads in flight, added in order
+        for (unsigned long long m = __ballot(near); m;) {
+            float v[8];
+            bool in[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const bool live = m != 0;
+                const int k = live ? __builtin_ctzll(m) : 0;
+                const int py = y - __builtin_amdgcn_readlane(y0, k), px = x - __builtin_amdgcn_readlane(x0, k);
+                in[u] = live && py >= 0 && py < OUT && px >= 0 && px < OUT;
+                v[u] = in[u] ? patches[(size_t)(p0 + k) * OUT * OUT + py * OUT + px] : 0.f;
+                m &= m - 1;
             }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (in[u]) {
+                    s += v[u];
+                    ++cnt;
+                }
         }
     }
     if (cnt && y < H && x < W) img[(size_t)y * W + x] = s / (float)cnt;

@@ -5,8 +5,9 @@ import pytest
 import torch
 
 from oracle import constraints as oc
-from paper_2505_07814_amd import synth
+from paper_2505_07814_amd import cnn, synth
 from paper_2505_07814_amd.ptyr import AdamState
+from test_gpu_cnn import make_case
 from test_gpu_constraints import T, engine, rz_bound
 from test_gpu_parity import Case, _check_grads
 
@@ -107,3 +108,48 @@ def test_gradient_256_row_groups(M, B):
     print(f"gradient N=256 S=2 M={M} B={B}", flush=True)
     c = Case(synth.small_case(N=256, S=2, M=M, B=B, H=300, W=310, seed=53))
     _check_grads(c, c.engine())
+
+
+@pytest.mark.parametrize("B", [2, 36])
+def test_conv_net_gradient_is_the_mean_of_its_halves(B):
+    """Weight gradients over fewer tiles than workgroups and (36 samples of 8
+    tiles over 256 workgroups) over uneven shares: the gradient of a batch is
+    the mean of those of its halves.  The output gradient differs by the exact
+    factor 2, so every stored BF16 value scales exactly and only the order of
+    float32 sums differs."""
+    print(f"conv net gradient B={B}", flush=True)
+    _, vec, pats, nbr, target = make_case(B, 40, 60 + B)
+    net = cnn.ConvInit(B)
+    V, P = T(vec), T(pats)
+
+    def grad(sel):
+        g = torch.zeros(cnn.param_count(), dtype=torch.float32, device=V.device)
+        net.gradient(V, P, T(nbr[sel]), T(target[sel]), g)
+        return g
+
+    whole = grad(slice(0, B))
+    halves = 0.5 * (grad(slice(0, B // 2)) + grad(slice(B // 2, B)))
+    net.sync()
+    assert float(torch.linalg.norm(whole - halves)) <= 1e-5 * float(torch.linalg.norm(halves))
+
+
+@pytest.mark.parametrize("P,H,W", [(0, 40, 33), (1, 32, 32), (70, 100, 90)])
+def test_stitch_tiles(P, H, W):
+    """Patches over image edges, more than 64 of them, ragged tiles; the sum
+    runs in patch order in float32 as the reference's."""
+    rng = np.random.default_rng(P + H)
+    patches = rng.standard_normal((P, 32, 32)).astype(np.float32)
+    centres = np.stack([rng.uniform(-10, H + 10, P), rng.uniform(-10, W + 10, P)], 1).astype(np.float32)
+    img = rng.standard_normal((H, W)).astype(np.float32)
+    total, hits = np.zeros((H, W), np.float32), np.zeros((H, W), np.float32)
+    for q in range(P):
+        y0, x0 = int(np.rint(centres[q, 0])) - 16, int(np.rint(centres[q, 1])) - 16
+        ya, yb, xa, xb = max(y0, 0), min(y0 + 32, H), max(x0, 0), min(x0 + 32, W)
+        if ya < yb and xa < xb:
+            total[ya:yb, xa:xb] += patches[q, ya - y0:yb - y0, xa - x0:xb - x0]
+            hits[ya:yb, xa:xb] += 1
+    ref = np.where(hits > 0, total / np.maximum(hits, 1), img)
+    out = T(img)
+    cnn.ConvInit(1).stitch(T(patches), T(centres), out)
+    # one float division apart: at most one unit in the last place
+    assert np.max(np.abs(out.cpu().numpy() - ref)) <= 2.0 ** -23 * np.max(np.abs(ref))
