@@ -1242,15 +1242,18 @@ void tables256(ptyr_ctx* c, const WaveArgs& a, hipStream_t st) {
                        reinterpret_cast<PosTab256*>(at<float4>(c, c->L.tab256) + N256));
 }
 // probe modes whose patch gradients the N = 256 gradient row pass sums per
-// workgroup: the largest divisor of the probe modes up to 8 that leaves a
-// workgroup per compute unit (measured at the 16-position, 8-mode batch, 256
-// workgroups in groups of 8: groups of 8, 4 and 2 gave 6.65, 6.76 and 7.08 ms
-// per step, the scatter reading more patch gradients); 1 for N = 64 and 128
+// workgroup: the largest divisor of the probe modes up to 8 that leaves half
+// of the compute units a workgroup; 1 for N = 64 and 128.  Larger groups write
+// and scatter fewer patch gradients (16 positions, 8 modes: groups of 8, 4 and
+// 2 gave 6.65, 6.76 and 7.08 ms per step), smaller ones fill the chip: with a
+// workgroup for every unit, half of them, and groups of 8 always, 12
+// positions of 4 modes and 30 slices took 2.83, 2.60 and 2.76 ms, 6 positions
+// of 8 modes and 10 slices 1.03, 0.95 and 1.17 ms.
 int row_group(const ptyr_ctx* c, int B) {
     const ptyr_geom& g = c->g;
     if (g.N != 256) return 1;
     for (int d = 8; d > 1; --d)
-        if (g.M % d == 0 && (size_t)B * (chain_modes(g) / d) * NBLK256 >= (size_t)c->n_cu) return d;
+        if (g.M % d == 0 && (size_t)B * (chain_modes(g) / d) * NBLK256 * 2 >= (size_t)c->n_cu) return d;
     return 1;
 }
 void forward256(ptyr_ctx* c, WaveArgs a, int c0, int nc, hipStream_t st) {
