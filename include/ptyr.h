@@ -169,8 +169,8 @@ ptyr_status ptyr_checkpoint_plan(const ptyr_geom* g, int* stride);
  * stream), on the current device.  Besides pointers the context owns one
  * extra stream of default priority and seven events: a batch with more
  * (row, mode) chains than the device has compute units runs part of its
- * chains on that stream, joined back to the caller's stream before
- * ptyr_adjoint / ptyr_step return, so callers only ever order work against
+ * chains on that stream, and a step may run its object scatter there, joined
+ * back to the caller's stream before ptyr_adjoint / ptyr_step return, so callers only ever order work against
  * their own stream.  PTYR_E_DEVICE if the stream or events cannot be made. */
 ptyr_status ptyr_create(const ptyr_geom* g, void* workspace, size_t ws_bytes,
                         void* stream, ptyr_ctx** out);

@@ -16,11 +16,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "loss.hpp"
 #include "wave.hpp"
 
 namespace ptyr {
-
-enum : int { ERR_BOUNDS = 1, ERR_NONFINITE = 2, ERR_ZERO_MEAN = 4, ERR_INDEX = 8 };
 
 struct PosInfo {      // integer crop corner and sub-pixel shift of one batch row
     int ty, tx;       // ty < 0 marks a row that is skipped (patch out of bounds / bad index)
@@ -53,6 +52,7 @@ struct WaveArgs {
     int Mp;                // probe modes: chain mode e uses probe mode e % Mp and object mode e / Mp
     size_t ostride;        // object-mode stride of Oc (S x H x W)
     int chain0;            // first chain (row * M + mode) of this launch; block b handles chain0 + b
+    int nc;                // chains of a gradient launch (its block nc, if any, ends the batch's loss)
     double dx, lam;
     int global_tilt;
     float* Imode;          // B x M x N x N, zero frequency at (0, 0)
@@ -387,13 +387,20 @@ __device__ __forceinline__ void recompute_phi(float2 (&v)[16], int s, const Wave
 // probe-spectrum gradient conj(R) G^_0 and partial sums for the position,
 // tilt and dz gradients.
 template <int N, int KEEP, bool WIDE>
-__global__ __launch_bounds__(N * N / 16) void k_gradient(WaveArgs a) {
+__global__ __launch_bounds__(N * N / 16) void k_gradient(WaveArgs a, LossFinalArgs lf) {
     constexpr int T = N * N / 16;
     __shared__ float2 lds[WaveGeo<N>::LDS_SLOTS];
     __shared__ Tables<N> tab;
+    if ((int)blockIdx.x == a.nc) {
+        // the batch's loss and its factor, which only the reductions after
+        // this launch read: its serial tail costs no launch of its own
+        static_assert(LOSS_FINAL_LDS * sizeof(double) <= sizeof(lds), "the loss's sums fit the transposes' buffer");
+        loss_final_block(lf, reinterpret_cast<double*>(lds));
+        return;
+    }
     int l, c;
     line_of<N>(threadIdx.x, l, c);
-    const int wg = a.chain0 + xcd_remap(blockIdx.x, gridDim.x);
+    const int wg = a.chain0 + xcd_remap(blockIdx.x, a.nc);
     const int j = wg / a.M, m = wg % a.M;
     const PosInfo pi = a.pinfo[j];
     double* part = a.part + (size_t)(j * a.M + m) * 8;

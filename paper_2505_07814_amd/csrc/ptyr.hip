@@ -208,14 +208,6 @@ __device__ __forceinline__ double powm1(double v, double p) {
     return pow(v, p - 1.0);
 }
 
-// The data terms of the loss (Eq. 5 / Eq. 6, or their weighted sum of
-// Eq. 9): term t has kind k[t], power p[t] and weight w[t]; n = 1 or 2.
-struct LossTerms {
-    int n;
-    int k[2];
-    double p[2], w[2];
-};
-
 // per-pixel pieces of data term (kind, p) at model value I and measured value
 // Em (both clamped at 0): the summand of the term's mean, dL/dA without the
 // batch factor, and dL/dI without it
@@ -252,10 +244,6 @@ __device__ __forceinline__ void block_partials(double (&v)[NP], double* part) {
     if (threadIdx.x == 0)
         for (int k = 0; k < NP; ++k) part[NP * blockIdx.x + k] = sh[k * 256];
 }
-
-// loss partial sums per block: E_0, R_0, E_1, R_1 (term means' summands) and
-// the count of non-finite inputs
-constexpr int NLP = 5;
 
 // pass 1 of the loss: per-block partial sums (ptyr_loss; inside the step
 // k_loss_rows does this per row range)
@@ -336,6 +324,11 @@ __global__ void k_loss_final(const double* part, int nblk, double K, LossTerms l
         scal[6] = c[1];
         if (loss_out) *loss_out = L;
     }
+}
+
+__global__ __launch_bounds__(256) void k_loss_final(LossFinalArgs a) {
+    __shared__ double sh[LOSS_FINAL_LDS];
+    loss_final_block(a, sh);
 }
 
 // dL/dI per value, in the layout of I_model (ptyr_loss)
@@ -705,10 +698,11 @@ __global__ __launch_bounds__(256) void k_sparse_partial(const float* phase, cons
 
 // sum over batch rows of the probe-spectrum gradients (fixed order), times
 // the batch factor
-__global__ void k_sum_rows(const float2* src, float2* dst, int B, int M, int NN, const double* scale) {
+__device__ __forceinline__ void sum_rows(const float2* src, float2* dst, int B, int M, int NN, const double* scale,
+                                         int block, int nblocks) {
     size_t n = (size_t)M * NN;
     const float sc = (float)*scale;
-    for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < n; e += (size_t)gridDim.x * blockDim.x) {
+    for (size_t e = block * (size_t)blockDim.x + threadIdx.x; e < n; e += (size_t)nblocks * blockDim.x) {
         float2 s = make_float2(0.f, 0.f);
         int j = 0;
         for (; j + 8 <= B; j += 8) {         // eight loads in flight, added in row order
@@ -727,23 +721,32 @@ __global__ void k_sum_rows(const float2* src, float2* dst, int B, int M, int NN,
 //   g_rho   = 2 pi sum_m sum_k q Im(Phat R conj(G^_0))
 //   g_th    = 2 pi dz sec^2(th) sum_s,m,k k Im(G^ conj(Y))
 //   g_dz    = sum [-pi lam |k|^2 + 2 pi (k_x tan th_x + k_y tan th_y)] Im(G^ conj(Y))
-// One workgroup of up to 1024 threads, 16 lanes per batch row (rows of a batch are
+// One workgroup of 256 threads, 16 lanes per batch row (rows of a batch are
 // distinct, so the row updates do not collide), which add the row's partial
 // sums in a fixed order; dz and a global tilt are summed over rows in fixed
 // order by a block tree.  (With one thread per row the chain of dependent
 // reads took 34 us for 8 modes at N = 256, 10 us for 12 at N = 128.)
-__global__ __launch_bounds__(1024) void k_param_grads(const double* part, int nblk, const PosInfo* pinfo, int B, int M,
-                                                      const float* tilt, int global_tilt, const float* dzp,
-                                                      double lam, const double* scale, float* g_pos, float* g_tilt,
-                                                      float* g_dz) {
-    __shared__ double sh[3][64];
+struct ParamGradArgs {
+    const double* part;
+    const PosInfo* pinfo;
+    const float *tilt, *dzp;
+    float *g_pos, *g_tilt, *g_dz;
+    double lam;
+    int nblk, B, M, global_tilt;
+};
+__device__ __forceinline__ void param_grads(const ParamGradArgs& a, const double* scale) {
+    __shared__ double sh[3][16];
+    const double* part = a.part;
+    const PosInfo* pinfo = a.pinfo;
+    const float *tilt = a.tilt, *dzp = a.dzp;
+    float *g_pos = a.g_pos, *g_tilt = a.g_tilt, *g_dz = a.g_dz;
+    const double lam = a.lam;
+    const int nblk = a.nblk, B = a.B, M = a.M, global_tilt = a.global_tilt;
     const double two_pi = 6.283185307179586;
     const double sc = *scale;                 // batch factor of the loss gradient
     const double dz = *dzp;
     const int slot = threadIdx.x / 16, lane = threadIdx.x % 16, n = M * nblk;
     double sdz = 0.0, sty = 0.0, stx = 0.0;
-    if (threadIdx.x < 64) sh[0][threadIdx.x] = sh[1][threadIdx.x] = sh[2][threadIdx.x] = 0.0;
-    __syncthreads();
     for (int j0 = 0; j0 < B; j0 += blockDim.x / 16) {
         const int j = j0 + slot;
         const bool live = j < B && pinfo[j].ty >= 0;
@@ -772,7 +775,7 @@ __global__ __launch_bounds__(1024) void k_param_grads(const double* part, int nb
     }
     if (lane == 0) { sh[0][slot] = sdz; sh[1][slot] = sty; sh[2][slot] = stx; }
     __syncthreads();
-    for (int o = 32; o > 0; o >>= 1) {
+    for (int o = 8; o > 0; o >>= 1) {
         if ((int)threadIdx.x < o)
             for (int k = 0; k < 3; ++k) sh[k][threadIdx.x] += sh[k][threadIdx.x + o];
         __syncthreads();
@@ -781,6 +784,15 @@ __global__ __launch_bounds__(1024) void k_param_grads(const double* part, int nb
         if (global_tilt && g_tilt) { g_tilt[0] += (float)sh[1][0]; g_tilt[1] += (float)sh[2][0]; }
         if (g_dz) g_dz[0] += (float)sh[0][0];
     }
+}
+
+// The reductions of a batch that need no transform, in one launch: the
+// probe-spectrum sum (blocks 0 .. nsum - 1) and, in the last block (with
+// params), the position, tilt and dz gradients.
+__global__ __launch_bounds__(256) void k_reduce(const float2* src, float2* dst, int rows, int M, int NN,
+                                                const double* scale, int nsum, ParamGradArgs pg, int params) {
+    if ((int)blockIdx.x < nsum) sum_rows(src, dst, rows, M, NN, scale, blockIdx.x, nsum);
+    else if (params) param_grads(pg, scale);
 }
 
 // Adam (PyTorch's form): m = b1 m + (1-b1) g; v = b2 v + (1-b2) g^2;
@@ -1099,6 +1111,10 @@ ptyr_status ptyr_create(const ptyr_geom* g, void* workspace, size_t ws_bytes, vo
         return PTYR_E_DEVICE;
     }
     hipLaunchKernelGGL(k_zero, dim3(1), dim3(64), 0, c->stream, at<float>(c, L.err), (size_t)1);
+    // twiddles of the k_z filter's lines, where its lengths are allowed (k_kz_twiddles: 5 us of a 104 us call)
+    if (std::max(g->S, std::max(g->H, g->W)) <= KZ_MAX_SIDE)
+        hipLaunchKernelGGL(k_kz_twiddles, dim3(grid_for(g->W + g->H + g->S)), dim3(256), 0, c->stream,
+                           at<float2>(c, L.kz) + (size_t)g->S * g->H * g->W, g->W, g->H, g->S);
     if (g->N == 64) hipLaunchKernelGGL(k_twiddles<64>, dim3(1), dim3(64), 0, c->stream, at<float4>(c, L.tw));
     if (g->N == 128) hipLaunchKernelGGL(k_twiddles<128>, dim3(1), dim3(128), 0, c->stream, at<float4>(c, L.tw));
     if (hipGetLastError() != hipSuccess) { (void)ptyr_destroy(c); return PTYR_E_DEVICE; }
@@ -1217,13 +1233,17 @@ template <int N, bool WIDE = false> void launch_forward(ptyr_ctx* c, WaveArgs a,
                                             : k_forward<N, KEEP_PHI, WIDE>;
     hipExtLaunchKernelGGL(kernel, dim3(nc), dim3(N * N / 16), 0, st, t.start(), t.stop(), 0, a);
 }
-template <int N, bool WIDE = false> void launch_gradient(ptyr_ctx* c, WaveArgs a, int c0, int nc, hipStream_t st) {
+// lf (nullable): the end of the batch's loss, as one more workgroup
+template <int N, bool WIDE = false>
+void launch_gradient(ptyr_ctx* c, WaveArgs a, int c0, int nc, hipStream_t st, const LossFinalArgs* lf) {
     TimedLaunch t(c, PTYR_K_GRADIENT, st, true);
     a.chain0 = c0;
+    a.nc = nc;
     const auto kernel = a.keep != KEEP_FULL ? k_gradient<N, KEEP_CKPT, false>
                         : a.spectra         ? k_gradient<N, KEEP_FULL, WIDE>
                                             : k_gradient<N, KEEP_PHI, WIDE>;
-    hipExtLaunchKernelGGL(kernel, dim3(nc), dim3(N * N / 16), 0, st, t.start(), t.stop(), 0, a);
+    hipExtLaunchKernelGGL(kernel, dim3(nc + (lf ? 1 : 0)), dim3(N * N / 16), 0, st, t.start(), t.stop(), 0, a,
+                          lf ? *lf : LossFinalArgs{});
 }
 // N = 256: forward and gradient as line passes (lines256.hpp)
 Pass256 pass256(ptyr_ctx* c, const WaveArgs& a, int s) {
@@ -1301,10 +1321,12 @@ void forward_chains(ptyr_ctx* c, const WaveArgs& a, int c0, int nc, hipStream_t 
     else if (c->g.N == 128) launch_forward<128>(c, a, c0, nc, st);
     else forward256(c, a, c0, nc, st);
 }
-void gradient_chains(ptyr_ctx* c, const WaveArgs& a, int c0, int nc, hipStream_t st) {
-    if (c->g.N == 64 && wide_chains(c, a)) launch_gradient<64, true>(c, a, c0, nc, st);
-    else if (c->g.N == 64) launch_gradient<64>(c, a, c0, nc, st);
-    else if (c->g.N == 128) launch_gradient<128>(c, a, c0, nc, st);
+// lf: N = 64 and 128 only
+void gradient_chains(ptyr_ctx* c, const WaveArgs& a, int c0, int nc, hipStream_t st,
+                     const LossFinalArgs* lf = nullptr) {
+    if (c->g.N == 64 && wide_chains(c, a)) launch_gradient<64, true>(c, a, c0, nc, st, lf);
+    else if (c->g.N == 64) launch_gradient<64>(c, a, c0, nc, st, lf);
+    else if (c->g.N == 128) launch_gradient<128>(c, a, c0, nc, st, lf);
     else gradient256(c, a, c0, nc, st);
 }
 
@@ -1400,14 +1422,27 @@ LossBufs loss_bufs(ptyr_ctx* c) {
 
 // with_sparse: add the sparsity term of the batch (its partial sums come
 // from k_sparse_partial) to the loss
+LossFinalArgs loss_final_args(const ptyr_geom& g, const LossBufs& b, int nslots, int B, double* loss_dev,
+                              bool with_sparse) {
+    const bool sp = with_sparse && g.sparse_w > 0.0 && b.spart;
+    LossFinalArgs a{};
+    a.part = b.lpart;
+    a.nblk = nslots * NPART;
+    a.K = (double)B * g.N * g.N;
+    a.lt = loss_terms(g);
+    a.check = (g.flags & PTYR_CHECK_FINITE) ? 1 : 0;
+    a.scal = b.scal;
+    a.loss_out = loss_dev;
+    a.err = b.err;
+    a.spart = b.spart;
+    a.nsp = sp ? B * g.S * obj_modes(g) : 0;
+    a.spw = sp ? g.sparse_w / ((double)B * g.S * obj_modes(g) * g.N * g.N) : 0.0;
+    return a;
+}
 void loss_final_with(const ptyr_geom& g, const LossBufs& b, int nslots, int B, double* loss_dev, hipStream_t st,
                      bool with_sparse) {
-    const double n = (double)B * g.N * g.N;
-    const bool sp = with_sparse && g.sparse_w > 0.0 && b.spart;
-    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(256), 0, st, b.lpart, nslots * NPART, n, loss_terms(g),
-                       (g.flags & PTYR_CHECK_FINITE) ? 1 : 0, b.scal, loss_dev, b.err, b.spart,
-                       sp ? B * g.S * obj_modes(g) : 0,
-                       sp ? g.sparse_w / ((double)B * g.S * obj_modes(g) * g.N * g.N) : 0.0);
+    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(256), 0, st,
+                       loss_final_args(g, b, nslots, B, loss_dev, with_sparse));
 }
 void loss_final(ptyr_ctx* c, int nslots, int B, double* loss_dev, hipStream_t st, bool with_sparse) {
     loss_final_with(c->g, loss_bufs(c), nslots, B, loss_dev, st, with_sparse);
@@ -1580,10 +1615,14 @@ ptyr_status run_adjoint(ptyr_ctx* c, const float* amp, const float* phase, const
     };
     // probe-spectrum sum and inverse transform, position / tilt / dz partials
     auto reductions = [&](hipStream_t st) {
+        const int NN = g.N * g.N, nsum = g_probe ? grid_for((size_t)g.M * NN) : 0;
+        const int params = g_pos || g_tilt || g_dz ? 1 : 0;
+        const ParamGradArgs pg{at<double>(c, c->L.part), at<PosInfo>(c, c->L.pinfo), tilt, dz, g_pos, g_tilt, g_dz,
+                               g.lambda, g.N == 256 ? NBLK256 : 1, B, M, a.global_tilt};
+        if (nsum + params)
+            hipLaunchKernelGGL(k_reduce, dim3(nsum + params), dim3(256), 0, st, at<float2>(c, c->L.gPhat),
+                               at<float2>(c, c->L.gPsum), B * obj_modes(g), g.M, NN, scale, nsum, pg, params);
         if (g_probe) {
-            int NN = g.N * g.N;
-            hipLaunchKernelGGL(k_sum_rows, dim3(grid_for((size_t)g.M * NN)), dim3(256), 0, st,
-                               at<float2>(c, c->L.gPhat), at<float2>(c, c->L.gPsum), B * obj_modes(g), g.M, NN, scale);
             if (g.N == 64) launch_probe_ifft_acc<64>(c, g_probe, st);
             else if (g.N == 128) launch_probe_ifft_acc<128>(c, g_probe, st);
             else {
@@ -1594,10 +1633,6 @@ ptyr_status run_adjoint(ptyr_ctx* c, const float* amp, const float* phase, const
                                    reinterpret_cast<float2*>(g_probe));
             }
         }
-        if (g_pos || g_tilt || g_dz)
-            hipLaunchKernelGGL(k_param_grads, dim3(1), dim3(std::min(1024, (B * 16 + 63) / 64 * 64)), 0, st, at<double>(c, c->L.part),
-                               g.N == 256 ? NBLK256 : 1, at<PosInfo>(c, c->L.pinfo), B, M, tilt, a.global_tilt, dz,
-                               g.lambda, scale, g_pos, g_tilt, g_dz);
     };
     // ptyr_step: Adam of the probe, positions, tilts and dz, whose gradients
     // are complete once the reductions are; on the main stream right after
@@ -1675,15 +1710,35 @@ ptyr_status run_adjoint(ptyr_ctx* c, const float* amp, const float* phase, const
                 pacbed(c, at<float>(c, c->L.Ibuf), I_meas, idx, nm, 0, B, loss_dev, at<float>(c, c->L.wbuf), true,
                        c->stream);
         }
-        gradient_chains(c, a, 0, BM, c->stream);
+        // the loss's last pass rides with the gradient's launch where nothing
+        // before the reductions needs it
+        const LossFinalArgs lf = loss_final_args(g, loss_bufs(c), 1, B, loss_dev, true);
+        const bool ride = !fold && g.N < 256;
+        gradient_chains(c, a, 0, BM, c->stream, ride ? &lf : nullptr);
+        if (!fold && !ride) loss_final(c, 1, B, loss_dev, c->stream, true);
     }
     c->fwd_valid = a.spectra;
     c->fwd_B = B;
     if (!scattered) {
-        if (!fold) loss_final(c, 1, B, loss_dev, c->stream, true);
+        // The probe's sum, transform and Adam are short launches in a row, one
+        // or a few workgroups long each (about 40 us at N = 128).  Where the
+        // object scatter of a step is at least as long (some 3 TB/s over the
+        // patch gradients and the object's Adam) it runs beside them on the
+        // other stream: 12 modes, 6 slices, 270 MB: step 439 -> 423 us.  The
+        // fork and join cost about 10 us, which the shorter reductions at
+        // N = 64 do not repay (395 -> 402 us), and at N = 256 the scatter
+        // fills the memory either way (5450 -> 5474 us).
+        const size_t scatter_bytes = ((size_t)BM * g.S * g.N * g.N * 8) + (size_t)obj_modes(g) * g.S * g.H * g.W * 48;
+        const bool beside = fuse && g.N == 128 && g_probe && (g_amp || g_phase) && scatter_bytes >= 128e6;
+        if (beside && (hipEventRecord(c->ev_gdone, c->stream) != hipSuccess ||
+                       hipStreamWaitEvent(c->side, c->ev_gdone, 0) != hipSuccess))
+            return PTYR_E_DEVICE;
         reductions(c->stream);
         seg_adam();
-        scatter(0, B, c->stream, true);
+        scatter(0, B, beside ? c->side : c->stream, true);
+        if (beside && (hipEventRecord(c->ev_join, c->side) != hipSuccess ||
+                       hipStreamWaitEvent(c->stream, c->ev_join, 0) != hipSuccess))
+            return PTYR_E_DEVICE;
     }
     return hipGetLastError() == hipSuccess ? PTYR_OK : PTYR_E_DEVICE;
 }
@@ -1810,8 +1865,6 @@ ptyr_status ptyr_constrain(ptyr_ctx* c, float* amp, float* phase, float* probe, 
             float2* twy = twx + g.W;
             float2* twz = twy + g.H;
             float2* wtab = twz + g.S;
-            if (ob == 0)
-                hipLaunchKernelGGL(k_kz_twiddles, dim3(grid_for(g.W + g.H + g.S)), dim3(256), 0, st, twx, g.W, g.H, g.S);
             KzPlan plans[5];
             const int np = kz_plan(g.S, g.H, g.W, rad[0], nrad[0], rad[1], nrad[1], rad[2], nrad[2], twx, twy, twz,
                                    (float)(1.0 / (g.S * (double)cfg->kz_dz)), plans);
