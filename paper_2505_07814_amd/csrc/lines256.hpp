@@ -341,32 +341,39 @@ __global__ __launch_bounds__(256) void k256_grad_col(Pass256 P) {
 // and object mode (probe modes p0 .. p0 + mg - 1): per chain the wave holds
 // (y, k_x) of G after the inverse along y; the inverse along x gives
 // G_chi_s, phi_s is rebuilt from the kept Z_s as the forward row pass formed
-// it, the group's patch gradient sum_p conj(phi_s) G_chi is summed in
-// registers, and G_phi = conj(O_s) G_chi is transformed along x.  The object
-// patch is read once for the group and the summed patch gradient written
-// once, mg times less patch-gradient traffic (written here, read by the object
-// scatter) than one per chain.  The next chain's phi_s is read while the
-// current chain's line DFT runs.
-// HV: 256-thread halves of the workgroup, of which half h takes the chains p =
-// h, h + HV, ...; their patch gradients are added in half order at the end.
-// With one half and one workgroup per compute unit (256 workgroups at 16
-// positions) each SIMD holds a single wave, whose latencies nothing hides.
-template <int HV>
-__global__ __launch_bounds__(256 * HV, 2) void k256_grad_row(Pass256 P) {
-    __shared__ float2 lds[HV * ROW_LDS256];
+// it, the group's patch gradient sum_p conj(phi_s) G_chi (in probe-mode
+// order) is summed in registers, and G_phi = conj(O_s) G_chi is transformed
+// along x.  The object patch is read once for the group and the summed patch
+// gradient written once, mg times less patch-gradient traffic (written here,
+// read by the object scatter) than one per chain.  The next chain's phi_s is
+// read while the current chain's line DFT runs.
+// The workgroup takes NL lines, and its HV halves of 16 NL threads take the
+// chains in turn (half h: p = h, h + HV, ...): with one half and one workgroup
+// of 16 lines per compute unit each SIMD holds a single wave, whose latencies
+// nothing hides; two halves of 4 lines put two waves there and spread fewer
+// groups over more units.  The sum stays in probe-mode order, the same bits whatever HV and NL:
+// half 1 hands its product over in LDS and half 0 adds the two, its own first,
+// one barrier later (two buffers, so one barrier per pair of chains).
+template <int HV, int NL>
+__global__ __launch_bounds__(16 * NL * HV, 2) void k256_grad_row(Pass256 P) {
+    constexpr int T = 16 * NL, NBLK = N256 / NL;
+    __shared__ float2 lds[HV * NL * RowGeo256::SL / 2];
     __shared__ float4 tw[N256];
+    __shared__ float2 hand[HV == 2 ? 2 * 16 * T : 1];
     const WaveArgs& a = P.a;
-    const int mg = P.mg, grp = a.chain0 / mg + blockIdx.x / NBLK256, blk = blockIdx.x % NBLK256;
+    const int mg = P.mg, grp = a.chain0 / mg + blockIdx.x / NBLK, blk = blockIdx.x % NBLK;
     const int ch0 = grp * mg, j = ch0 / a.M;
     const PosInfo pi = a.pinfo[j];
     if (pi.ty < 0) return;
-    const int half = threadIdx.x / 256;
-    const int ll = threadIdx.x / 16, l = ll % LINES256, c = threadIdx.x % 16, y = blk * LINES256 + l;   // ll: LDS line
-    if (threadIdx.x < N256) tw[threadIdx.x] = P.tw[threadIdx.x];
+    const int half = threadIdx.x / T, t = threadIdx.x % T;
+    const int ll = threadIdx.x / 16, c = threadIdx.x % 16, y = blk * NL + ll % NL;   // ll: LDS line
+    for (int i = threadIdx.x; i < N256; i += HV * T) tw[i] = P.tw[i];
     __syncthreads();
     float2 v[16], ph[16], ov[16], acc[16];
-    rows_load(v, P.wave + (size_t)(ch0 + half) * N256 * N256, y, c);
-    rows_load(ph, Slots<N256>(a, ch0 + half).phi(P.s), y, c);
+    if (half < mg) {
+        rows_load(v, P.wave + (size_t)(ch0 + half) * N256 * N256, y, c);
+        rows_load(ph, Slots<N256>(a, ch0 + half).phi(P.s), y, c);
+    }
     // the object patch (the same for the group's chains) and the first
     // chain's G and phi_s are read now, so that their latency overlaps the
     // line DFT
@@ -376,37 +383,37 @@ __global__ __launch_bounds__(256 * HV, 2) void k256_grad_row(Pass256 P) {
         ov[r] = Os[c + 16 * r];
         acc[r] = make_float2(0.f, 0.f);
     }
-    for (int p = half; p < mg; p += HV) {                              // exchanges are within a wave: no barriers
-        const int ch = ch0 + p;
-        if (P.s == 0) {
+    int buf = 0;
+    for (int p0 = 0; p0 < mg; p0 += HV, buf ^= 1) {
+        const int p = p0 + half, ch = ch0 + p;
+        if (HV == 1 || p < mg) {                                           // exchanges are within a wave: no barriers
+            if (P.s == 0) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) ph[r] = cmul(ph[r], P.tab[j].r[1][c + 16 * r]);
-        }
-        mid2nat<RowGeo256, +1>(ph, lds, tw, ll, c);                    // phi_s (space)
-        mid2nat<RowGeo256, +1>(v, lds, tw, ll, c);                     // G_chi_s (space)
+                for (int r = 0; r < 16; ++r) ph[r] = cmul(ph[r], P.tab[j].r[1][c + 16 * r]);
+            }
+            mid2nat<RowGeo256, +1>(ph, lds, tw, ll, c);                    // phi_s (space)
+            mid2nat<RowGeo256, +1>(v, lds, tw, ll, c);                     // G_chi_s (space)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            acc[r] = cadd(acc[r], cmulc(v[r], ph[r]));                  // conj(phi) G_chi
-            v[r] = cmulc(v[r], ov[r]);                                  // conj(O) G_chi
+            for (int r = 0; r < 16; ++r) {
+                const float2 q = cmulc(v[r], ph[r]);                       // conj(phi) G_chi
+                if (half == 0) acc[r] = cadd(acc[r], q);
+                else hand[(buf * 16 + r) * T + t] = q;
+                v[r] = cmulc(v[r], ov[r]);                                 // conj(O) G_chi
+            }
+            if (p + HV < mg) rows_load(ph, Slots<N256>(a, ch + HV).phi(P.s), y, c);
+            nat2mid<RowGeo256, -1>(v, lds, tw, ll, c);
+            rows_store(v, P.wave + (size_t)ch * N256 * N256, y, c);
+            if (p + HV < mg) rows_load(v, P.wave + (size_t)(ch + HV) * N256 * N256, y, c);
         }
-        if (p + HV < mg) rows_load(ph, Slots<N256>(a, ch + HV).phi(P.s), y, c);
-        nat2mid<RowGeo256, -1>(v, lds, tw, ll, c);
-        rows_store(v, P.wave + (size_t)ch * N256 * N256, y, c);
-        if (p + HV < mg) rows_load(v, P.wave + (size_t)(ch + HV) * N256 * N256, y, c);
+        if constexpr (HV == 2) {
+            __syncthreads();
+            if (half == 0 && p0 + 1 < mg) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[r] = cadd(acc[r], hand[(buf * 16 + r) * T + t]);
+            }
+        }
     }
-    if constexpr (HV == 2) {
-        // 16 x 256 float2, thread-major per register: fits the two halves' buffers
-        static_assert(HV * ROW_LDS256 >= 16 * 256, "patch gradient of one half");
-        __syncthreads();
-        if (half == 1) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) lds[r * 256 + threadIdx.x % 256] = acc[r];
-        }
-        __syncthreads();
-        if (half == 1) return;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = cadd(acc[r], lds[r * 256 + threadIdx.x]);
-    }
+    if (half != 0) return;
     float2* go = a.gO + (((size_t)grp * a.S + P.s) * N256 + y) * N256;
 #pragma unroll
     for (int r = 0; r < 16; ++r) go[c + 16 * r] = acc[r];

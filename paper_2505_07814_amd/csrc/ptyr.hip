@@ -1262,18 +1262,15 @@ void tables256(ptyr_ctx* c, const WaveArgs& a, hipStream_t st) {
                        reinterpret_cast<PosTab256*>(at<float4>(c, c->L.tab256) + N256));
 }
 // probe modes whose patch gradients the N = 256 gradient row pass sums per
-// workgroup: the largest divisor of the probe modes up to 8 that leaves half
-// of the compute units a workgroup; 1 for N = 64 and 128.  Larger groups write
-// and scatter fewer patch gradients (16 positions, 8 modes: groups of 8, 4 and
-// 2 gave 6.65, 6.76 and 7.08 ms per step), smaller ones fill the chip: with a
-// workgroup for every unit, half of them, and groups of 8 always, 12
-// positions of 4 modes and 30 slices took 2.83, 2.60 and 2.76 ms, 6 positions
-// of 8 modes and 10 slices 1.03, 0.95 and 1.17 ms.
-int row_group(const ptyr_ctx* c, int B) {
-    const ptyr_geom& g = c->g;
+// workgroup: the largest divisor of the probe modes up to 8 (measured at the
+// 16-position, 8-mode batch: groups of 8, 4 and 2 give 6.65, 6.76 and
+// 7.08 ms per step); 1 for N = 64 and 128.  By the modes alone: the group sets
+// the order in which the object gradient's sum over modes and positions is
+// rounded, which neither the batch nor the device may change.
+int row_group(const ptyr_geom& g) {
     if (g.N != 256) return 1;
     for (int d = 8; d > 1; --d)
-        if (g.M % d == 0 && (size_t)B * (chain_modes(g) / d) * NBLK256 * 2 >= (size_t)c->n_cu) return d;
+        if (g.M % d == 0) return d;
     return 1;
 }
 void forward256(ptyr_ctx* c, WaveArgs a, int c0, int nc, hipStream_t st) {
@@ -1294,16 +1291,20 @@ void gradient256(ptyr_ctx* c, WaveArgs a, int c0, int nc, hipStream_t st) {
     tables256(c, a, st);
     const auto grad_col = a.spectra ? k256_grad_col<true> : k256_grad_col<false>;
     hipLaunchKernelGGL(grad_col, grid, blk, 0, st, pass256(c, a, a.S));
-    // the row pass takes row_group(c, B) chains per workgroup (c0 and nc are
+    // the row pass takes row_group(g) chains per workgroup (c0 and nc are
     // multiples of it: N = 256 batches are not split)
-    const int mg = row_group(c, a.B);
-    const dim3 rgrid(nc / mg * NBLK256);
-    const bool two = mg > 1 && rgrid.x < 2 * (unsigned)c->n_cu;      // two halves per workgroup (k256_grad_row)
+    const int mg = row_group(c->g), groups = nc / mg;
+    // Two halves and 4 lines per workgroup (k256_grad_row) where one half and
+    // 16 lines give less than two workgroups per compute unit.  Step times,
+    // one half / two: 8 modes, 16 positions, 30 slices (256 workgroups of 16
+    // lines) 5684 / 5341 us, 20 positions, 6 slices (320) 1475 / 1458; from
+    // 512 on (8 modes, 32 positions, 4 slices) 1491 / 1542.
+    const bool two = mg > 1 && groups * NBLK256 < 2 * c->n_cu;
     for (int s = a.S - 1; s >= 0; --s) {
         Pass256 P = pass256(c, a, s);
         P.mg = mg;
-        if (two) hipLaunchKernelGGL(k256_grad_row<2>, rgrid, dim3(512), 0, st, P);
-        else hipLaunchKernelGGL(k256_grad_row<1>, rgrid, blk, 0, st, P);
+        if (two) hipLaunchKernelGGL((k256_grad_row<2, 4>), dim3(groups * (N256 / 4)), dim3(128), 0, st, P);
+        else hipLaunchKernelGGL((k256_grad_row<1, 16>), dim3(groups * NBLK256), blk, 0, st, P);
         hipLaunchKernelGGL(grad_col, grid, blk, 0, st, pass256(c, a, s));
     }
 }
@@ -1600,8 +1601,8 @@ ptyr_status run_adjoint(ptyr_ctx* c, const float* amp, const float* phase, const
             ad.assign = fuse && j0 == 0 ? 1 : 0;
         }
         // patch gradients per position and object mode: one per group of
-        // row_group(c, B) probe modes (the N = 256 row pass sums each group)
-        const int mg = row_group(c, B), Mg = g.M / mg, Mcg = M / mg;
+        // row_group(g) probe modes (the N = 256 row pass sums each group)
+        const int mg = row_group(g), Mg = g.M / mg, Mcg = M / mg;
         const int rows = scatter_rows(c);
         const dim3 grid(((g.H + 8 * rows - 1) / (8 * rows)) * ((g.W + 31) / 32), g.S * obj_modes(g));
         const bool mb8 = Mg % 8 == 0;

@@ -6,7 +6,7 @@ import torch
 
 from oracle import constraints as oc
 from paper_2505_07814_amd import cnn, synth
-from paper_2505_07814_amd.ptyr import AdamState
+from paper_2505_07814_amd.ptyr import AdamState, Engine
 from test_gpu_cnn import make_case
 from test_gpu_constraints import T, engine, rz_bound
 from test_gpu_parity import Case, _check_grads
@@ -108,6 +108,29 @@ def test_gradient_256_row_groups(M, B):
     print(f"gradient N=256 S=2 M={M} B={B}", flush=True)
     c = Case(synth.small_case(N=256, S=2, M=M, B=B, H=300, W=310, seed=53))
     _check_grads(c, c.engine())
+
+
+@pytest.mark.parametrize("B", [1, 2, 16, 32])
+def test_object_gradient_256_adds_modes_in_order(B):
+    """N = 256: the object gradient adds the probe modes of a group in mode
+    order whatever the batch, and so whatever share of the chip the row pass
+    has.  Modes 1 to 7 are the first times 2^-13, so every product of theirs is
+    the first mode's times 2^-26 exactly and, added one by one, below a quarter
+    unit in the last place: the intensities, the loss and the object gradient
+    are bitwise those of the first mode alone.  Any partial sum of several
+    small modes (four are half a unit) would round the result up."""
+    print(f"object gradient order N=256 S=2 M=8 B={B}", flush=True)
+    c = Case(synth.small_case(N=256, S=2, M=1, B=B, H=300, W=310, seed=59))
+    args, meas = list(c.gpu_args()), T(c.meas)
+    one = c.engine().adjoint(*args, meas)
+    args[2] = torch.cat([args[2]] + 7 * [args[2] * 2.0 ** -13]).contiguous()
+    eng = Engine(256, 8, 2, c.w.H, c.w.W, B, c.w.dx, c.lam, device=meas.device)
+    eight = eng.adjoint(*args, meas)
+    eng.sync()
+    assert torch.equal(one[0], eight[0])
+    assert float(torch.linalg.norm(one[1]["phase"])) > 0.0
+    for k in ("amp", "phase"):
+        assert torch.equal(one[1][k], eight[1][k]), k
 
 
 @pytest.mark.parametrize("B", [2, 36])
