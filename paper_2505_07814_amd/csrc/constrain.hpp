@@ -117,13 +117,27 @@ __device__ __forceinline__ double rcp_nr(double x) {
     return y;
 }
 
+// place of eigenvalue k in decreasing order, ties in index order, NaN last: a
+// permutation whatever the values
+__device__ __forceinline__ int eig_rank(const double* lam, int M, int k) {
+    const double x = lam[k];
+    int rank = 0;
+    for (int j = 0; j < M; ++j) {
+        const double y = lam[j];
+        const bool before = isnan(x) ? !isnan(y) || j < k : y > x || (y == x && j < k);
+        rank += before ? 1 : 0;
+    }
+    return rank;
+}
+
 // Eigenvectors of the Hermitian overlap matrix (summed from the chunk
 // partials) by complex Jacobi rotations in double, by a workgroup of at least
 // two waves, of which wave 0 rotates the matrix and wave 1 the vectors (lane k
 // = 0..63 of either), then ordered by decreasing eigenvalue; each eigenvector is scaled by
 // a unit phase so that its largest-magnitude entry (first of equals) is real
 // and positive.  Writes V (M x M, column k = mode k's mixing coefficients) as
-// float pairs and the eigenvalues.
+// float pairs and the eigenvalues.  A NaN in a mode is in its overlaps with every
+// other, so the rotations make all of V NaN.
 // A sweep is m - 1 rounds (m = M rounded up to even) of m / 2 disjoint pairs
 // in the round-robin order, whose rotations are formed and applied together:
 // the kernel is one serial chain of square roots and divisions, M (M - 1) / 2
@@ -177,7 +191,7 @@ __device__ void probe_eig(EigLds& L, const cd* part, int nchunk, int M, float2* 
                 EigLds::Rot w{{1.0, 0.0}, 1.0, 0.0, p, -1};             // q = -1: nothing to rotate
                 const cd apq = q < M ? A[p * M + q] : cd{0.0, 0.0};
                 const double mag2 = apq.re * apq.re + apq.im * apq.im;
-                if (mag2 > small) {
+                if (!(mag2 <= small)) {                                 // NaN rotates too, and so spreads
                     // U = D P: D_qq = exp(-i alpha) makes the (p, q) entry real
                     // (alpha = arg a_pq), P the real Jacobi rotation that zeroes it
                     const double inv = rsqrt_nr(mag2);
@@ -229,11 +243,7 @@ __device__ void probe_eig(EigLds& L, const cd* part, int nchunk, int M, float2* 
     if (wave != 0) return;
     if (k < M) L.lam[k] = A[k * M + k].re;
     eig_sync();
-    if (k < M) {                                          // rank by decreasing eigenvalue, ties in index order
-        int rank = 0;
-        for (int j = 0; j < M; ++j) rank += L.lam[j] > L.lam[k] || (L.lam[j] == L.lam[k] && j < k) ? 1 : 0;
-        L.order[rank] = k;
-    }
+    if (k < M) L.order[eig_rank(L.lam, M, k)] = k;
     eig_sync();
     if (k < M) {                                          // lane k: output column k
         const int src = L.order[k];
