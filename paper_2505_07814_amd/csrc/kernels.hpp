@@ -60,8 +60,8 @@ struct WaveArgs {
     float2* gO;            // B x M x S x N x N object-patch gradients
     float2* gPhat;         // B x M x N x N probe-spectrum gradients
     double* part;          // B x M x 8 scalar partial sums (N = 256: per line block)
-    const float4* tw;      // N = 64, 128: twiddles (k_twiddles) ...
-    const float4* tab;     // ... and B PosTab<N>, the rows' propagator and shift factors (k_prepare)
+    const float4* tw;      // N = 64, 128: twiddles ...
+    const float4* tab;     // ... and B PosTab<N>, the rows' propagator and shift factors (both k_prepare)
 };
 
 // probe spectrum and object transmission (all slices) of chain mode e
@@ -636,16 +636,19 @@ __global__ __launch_bounds__(N * N / 16) void k_gradient(WaveArgs a, LossFinalAr
 
 // One N x N 2-D DFT of sign SG by a whole workgroup (N*N/16 threads), scaled
 // by 1/N (orthonormal); the result is written to dst, or added to it (ACC).
-// twg: the twiddles of k_twiddles.
+// twg: the twiddles, or null to form them here and leave them in keep (if any).
 template <int N, int SG, bool ACC>
-__device__ __forceinline__ void fft2_block(const float2* src, float2* dst, const float4* twg) {
+__device__ __forceinline__ void fft2_block(const float2* src, float2* dst, const float4* twg, float4* keep) {
     __shared__ float2 lds[WaveGeo<N>::LDS_SLOTS];
     __shared__ float4 tw[N];
     int l, c;
     line_of<N>(threadIdx.x, l, c);
     float2 v[16];
     wload<N, ROW, NAT>(v, src, N, l, c);
-    for (int n = threadIdx.x; n < N; n += blockDim.x) tw[n] = twg[n];
+    for (int n = threadIdx.x; n < N; n += blockDim.x) {
+        tw[n] = twg ? twg[n] : twiddle_entry<N>(n);
+        if (keep) keep[n] = tw[n];
+    }
     __syncthreads();
     nat2mid<WaveGeo<N>, SG>(v, lds, tw, l, c);
     relayout<N, ROW, MID, COL, NAT>(v, lds, l, c);
@@ -661,11 +664,7 @@ __device__ __forceinline__ void fft2_block(const float2* src, float2* dst, const
 // the 2-D DFT of each of gridDim.x fields (one workgroup each)
 template <int N, int SG, bool ACC>
 __global__ __launch_bounds__(N * N / 16) void k_fft2(const float2* in, float2* out, const float4* tw) {
-    fft2_block<N, SG, ACC>(in + (size_t)blockIdx.x * N * N, out + (size_t)blockIdx.x * N * N, tw);
-}
-// the twiddles of length N, once per context
-template <int N> __global__ void k_twiddles(float4* tw) {
-    if (threadIdx.x < N) tw[threadIdx.x] = twiddle_entry<N>(threadIdx.x);
+    fft2_block<N, SG, ACC>(in + (size_t)blockIdx.x * N * N, out + (size_t)blockIdx.x * N * N, tw, nullptr);
 }
 
 }  // namespace ptyr

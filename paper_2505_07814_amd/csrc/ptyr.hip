@@ -131,7 +131,8 @@ __global__ void k_check_distinct(const int* idx, int B, PosInfo* pinfo, int* err
 }
 
 // The work a batch shares, in one launch (N = 64, 128): workgroups 0 .. M-1
-// transform the probe modes (long, one compute unit each), the next nt form
+// transform the probe modes (long, one compute unit each; the first leaves
+// its twiddles for the kernels after this launch), the next nt form
 // the rows' propagator and shift factors (PosTab, T / (4 N) rows each), the
 // others the transmission of every slice, and the first of them the
 // positions, so the transform overlaps the streaming pass instead of following
@@ -143,8 +144,7 @@ struct PrepareArgs {
     const float2* probe;
     float2 *Oc, *Phat;
     PosInfo* pinfo;
-    const float4* tw;
-    float4* tab;
+    float4 *tw, *tab;
     int* err;
     size_t nobj;
     int n_rows, B, H, W, M, nt, distinct, global_tilt;
@@ -154,7 +154,8 @@ template <int N> __global__ __launch_bounds__(N * N / 16) void k_prepare(Prepare
     constexpr int T = N * N / 16, RPB = T / (4 * N);
     const int b = blockIdx.x;
     if (b < p.M) {
-        fft2_block<N, -1, false>(p.probe + (size_t)b * N * N, p.Phat + (size_t)b * N * N, p.tw);
+        fft2_block<N, -1, false>(p.probe + (size_t)b * N * N, p.Phat + (size_t)b * N * N, nullptr,
+                                 b == 0 ? p.tw : nullptr);
         return;
     }
     if (b < p.M + p.nt) {
@@ -1115,8 +1116,6 @@ ptyr_status ptyr_create(const ptyr_geom* g, void* workspace, size_t ws_bytes, vo
     if (std::max(g->S, std::max(g->H, g->W)) <= KZ_MAX_SIDE)
         hipLaunchKernelGGL(k_kz_twiddles, dim3(grid_for(g->W + g->H + g->S)), dim3(256), 0, c->stream,
                            at<float2>(c, L.kz) + (size_t)g->S * g->H * g->W, g->W, g->H, g->S);
-    if (g->N == 64) hipLaunchKernelGGL(k_twiddles<64>, dim3(1), dim3(64), 0, c->stream, at<float4>(c, L.tw));
-    if (g->N == 128) hipLaunchKernelGGL(k_twiddles<128>, dim3(1), dim3(128), 0, c->stream, at<float4>(c, L.tw));
     if (hipGetLastError() != hipSuccess) { (void)ptyr_destroy(c); return PTYR_E_DEVICE; }
     *out = c;
     return PTYR_OK;

@@ -1,10 +1,13 @@
 """The paths a call takes by its sizes: each side of a dispatch rule against
 the FP64 oracle, at the sizes where a rule or a remainder changes."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
 
 from oracle import constraints as oc
+from paper_2505_07814_amd import _lib as L
 from paper_2505_07814_amd import cnn, synth
 from paper_2505_07814_amd.ptyr import AdamState, Engine
 from test_gpu_cnn import make_case
@@ -171,6 +174,41 @@ def test_object_gradient_256_adds_modes_in_order(B):
     assert float(torch.linalg.norm(one[1]["phase"])) > 0.0
     for k in ("amp", "phase"):
         assert torch.equal(one[1][k], eight[1][k]), k
+
+
+def on_workspace(eng, ws):
+    """The engine's context bound to `ws` instead of its own workspace."""
+    lib, ctx = eng.lib, C.c_void_p()
+    base = (ws.data_ptr() + 255) // 256 * 256
+    assert base + eng._ws_bytes <= ws.data_ptr() + ws.numel()
+    L.check(lib.ptyr_destroy(eng._ctx), "ptyr_destroy")
+    L.check(lib.ptyr_create(C.byref(eng.geom), C.c_void_p(base), eng._ws_bytes, C.c_void_p(eng.stream.cuda_stream),
+                            C.byref(ctx)), "ptyr_create")
+    eng._ctx = ctx
+    return eng
+
+
+@pytest.mark.parametrize("N", [64, 128, 256])
+def test_contexts_taking_turns_on_one_workspace(N):
+    """A forward or a gradient forms all it reads from the workspace: contexts
+    of two geometries on one workspace, overwritten between the calls, give
+    bitwise the results of contexts with a workspace each."""
+    print(f"shared workspace N={N}", flush=True)
+    cases = [Case(synth.small_case(N=N, S=S, M=M, B=3, H=N + 40, W=N + 45, seed=61)) for S, M in ((2, 1), (3, 2))]
+    ref = []
+    for c in cases:
+        eng = c.engine()
+        ref.append((eng.forward(*c.gpu_args()).clone(), eng.adjoint(*c.gpu_args(), T(c.meas))))
+        eng.sync()
+    ws = torch.empty(max(c.engine()._ws_bytes for c in cases) + 256, dtype=torch.uint8, device="cuda:0")
+    engines = [on_workspace(c.engine(), ws) for c in cases]
+    for c, eng, (I, (loss, g)) in 2 * list(zip(cases, engines, ref)):
+        ws.fill_(0xFF)
+        assert torch.equal(eng.forward(*c.gpu_args()), I)
+        ws.fill_(0xFF)
+        loss2, g2 = eng.adjoint(*c.gpu_args(), T(c.meas))
+        assert torch.equal(loss2, loss) and all(torch.equal(g2[k], g[k]) for k in g)
+    torch.cuda.synchronize()
 
 
 @pytest.mark.parametrize("B", [2, 36])
