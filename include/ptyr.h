@@ -166,7 +166,11 @@ ptyr_status ptyr_checkpoint_plan(const ptyr_geom* g, int* stride);
 
 /* Bind a context to a workspace (device, caller-owned, >= ptyr_workspace_bytes,
  * 256-byte aligned) and a stream (hipStream_t as void*; NULL = the default
- * stream), on the current device.  Besides pointers the context owns one
+ * stream), on the current device.  Between calls the workspace holds the error
+ * flags (until ptyr_sync reads them), ptyr_step's cleared gradient buffers
+ * (from the first step on) and, after a forward, what
+ * ptyr_adjoint(PTYR_REUSE_FORWARD) reads; everything else a call reads it
+ * forms itself.  Besides pointers the context owns one
  * extra stream of default priority and seven events: a batch with more
  * (row, mode) chains than the device has compute units runs part of its
  * chains on that stream, and a step may run its object scatter there, joined

@@ -620,20 +620,34 @@ __device__ __forceinline__ void kz_stage(const KzPass& p, int i, float2* t, cons
     __syncthreads();
 }
 
+// exp(-2 pi i k / n) (in double, rounded to float)
+__device__ __forceinline__ float2 kz_twiddle(int k, int n) {
+    double sn, cs;
+    sincospi(2.0 * k / n, &sn, &cs);
+    return make_float2((float)cs, (float)-sn);
+}
+
 // F: KZ_IN_FIELDS reads amplitude and phase instead of z, KZ_OUT_FIELDS writes
-// them.  Workgroups past the tiles (nw of them, before the others) form the
-// weight table: per (k_y, k_x) A = beta^2 / (k_r^2 + 1e-3) and E = exp(-alpha
-// k_r^2) / (S H W), k_r^2 in double, k from fftfreq with the pixel size.
+// them.  In the first launch of a call nw workgroups before the others form
+// what the later launches read: the weight table, per (k_y, k_x) A = beta^2 /
+// (k_r^2 + 1e-3) and E = exp(-alpha k_r^2) / (S H W), k_r^2 in double, k from
+// fftfreq with the pixel size, and the twiddle tables of W, H and S.  That
+// launch's own workgroups form the twiddles they need themselves.
 struct KzWeight {
     int nw, S, H, W;
     double beta, alpha, dx;
+    float2* tw;
 };
 template <int F>
 __global__ __launch_bounds__(KZ_MAX_THREADS, 8) void k_kz_pass(KzPass p, KzWeight w, float2* z, float* amp,
                                                                float* phase, float2* wtab) {
     extern __shared__ float2 kz_lds[];
     if ((int)blockIdx.x < w.nw) {
-        for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < w.H * w.W; i += w.nw * blockDim.x) {
+        const int id = blockIdx.x * blockDim.x + threadIdx.x;
+        for (int i = id; i < w.W + w.H + w.S; i += w.nw * blockDim.x)
+            w.tw[i] = i < w.W ? kz_twiddle(i, w.W)
+                              : (i < w.W + w.H ? kz_twiddle(i - w.W, w.H) : kz_twiddle(i - w.W - w.H, w.S));
+        for (int i = id; i < w.H * w.W; i += w.nw * blockDim.x) {
             const int y = i / w.W, x = i - y * w.W;
             const double kx = (x < (w.W + 1) / 2 ? x : x - w.W) / (w.W * w.dx);
             const double ky = (y < (w.H + 1) / 2 ? y : y - w.H) / (w.H * w.dx);
@@ -654,8 +668,12 @@ __global__ __launch_bounds__(KZ_MAX_THREADS, 8) void k_kz_pass(KzPass p, KzWeigh
     const int cnt_a = last ? p.rest_a : p.A, cnt_b = last ? p.rest_b : p.B;
     const size_t base = (size_t)(tile / p.tpg) * p.gs + (size_t)u * p.gt;
     float2* tw = kz_lds + p.A * p.pitch;                  // twiddles along b, then along a
-    for (int k = threadIdx.x; k < p.use_b + p.use_a; k += blockDim.x)
-        tw[k] = k < p.use_b ? p.twb[k] : p.twa[k - p.use_b];
+    if (w.nw > 0)
+        for (int k = threadIdx.x; k < p.use_b + p.use_a; k += blockDim.x)
+            tw[k] = k < p.use_b ? kz_twiddle(k, p.B) : kz_twiddle(k - p.use_b, p.A);
+    else
+        for (int k = threadIdx.x; k < p.use_b + p.use_a; k += blockDim.x)
+            tw[k] = k < p.use_b ? p.twb[k] : p.twa[k - p.use_b];
     // the first stage needs no twiddles; its closing barrier publishes them
     for (int i = 0; i < p.nst; ++i) {
         auto run = [&](auto sg) {
@@ -675,16 +693,6 @@ __global__ __launch_bounds__(KZ_MAX_THREADS, 8) void k_kz_pass(KzPass p, KzWeigh
         };
         if (i < p.nfwd) run(std::integral_constant<int, -1>());
         else run(std::integral_constant<int, +1>());
-    }
-}
-
-// exp(-2 pi i k / n) for k < n (in double, rounded to float)
-__global__ void k_kz_twiddles(float2* tw, int n0, int n1, int n2) {      // three tables, one after the other
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n0 + n1 + n2; i += gridDim.x * blockDim.x) {
-        const int n = i < n0 ? n0 : (i < n0 + n1 ? n1 : n2), k = i < n0 ? i : (i < n0 + n1 ? i - n0 : i - n0 - n1);
-        double sn, cs;
-        sincospi(2.0 * k / n, &sn, &cs);
-        tw[i] = make_float2((float)cs, (float)-sn);
     }
 }
 

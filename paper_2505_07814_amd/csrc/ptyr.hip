@@ -1112,10 +1112,6 @@ ptyr_status ptyr_create(const ptyr_geom* g, void* workspace, size_t ws_bytes, vo
         return PTYR_E_DEVICE;
     }
     hipLaunchKernelGGL(k_zero, dim3(1), dim3(64), 0, c->stream, at<float>(c, L.err), (size_t)1);
-    // twiddles of the k_z filter's lines, where its lengths are allowed (k_kz_twiddles: 5 us of a 104 us call)
-    if (std::max(g->S, std::max(g->H, g->W)) <= KZ_MAX_SIDE)
-        hipLaunchKernelGGL(k_kz_twiddles, dim3(grid_for(g->W + g->H + g->S)), dim3(256), 0, c->stream,
-                           at<float2>(c, L.kz) + (size_t)g->S * g->H * g->W, g->W, g->H, g->S);
     if (hipGetLastError() != hipSuccess) { (void)ptyr_destroy(c); return PTYR_E_DEVICE; }
     *out = c;
     return PTYR_OK;
@@ -1859,9 +1855,9 @@ ptyr_status ptyr_constrain(ptyr_ctx* c, float* amp, float* phase, float* probe, 
         float* const phase_o = phase ? phase + (size_t)ob * g.S * HW : nullptr;
         if (kz) {
             // amplitude + i phase through the passes of kz_plan; the first
-            // launch also forms the weight table
+            // launch also forms the weight table and the twiddles
             float2* zb = at<float2>(c, c->L.kz);
-            float2* twx = zb + (size_t)g.S * HW;           // twiddle tables of the three line lengths
+            float2* twx = zb + (size_t)g.S * HW;           // twiddle tables of the three line lengths, in this order
             float2* twy = twx + g.W;
             float2* twz = twy + g.H;
             float2* wtab = twz + g.S;
@@ -1870,7 +1866,7 @@ ptyr_status ptyr_constrain(ptyr_ctx* c, float* amp, float* phase, float* probe, 
                                    (float)(1.0 / (g.S * (double)cfg->kz_dz)), plans);
             for (int i = 0; i < np; ++i) {
                 const KzPlan& q = plans[i];
-                KzWeight kw{0, g.S, g.H, g.W, (double)cfg->kz_beta, (double)cfg->kz_alpha, g.dx};
+                KzWeight kw{0, g.S, g.H, g.W, (double)cfg->kz_beta, (double)cfg->kz_alpha, g.dx, twx};
                 if (i == 0 && ob == 0) kw.nw = (int)((HW + q.threads - 1) / q.threads);
                 const auto kernel = q.in ? k_kz_pass<KZ_IN_FIELDS> : (q.out ? k_kz_pass<KZ_OUT_FIELDS> : k_kz_pass<0>);
                 hipLaunchKernelGGL(kernel, dim3(kw.nw + ((q.p.tiles + 7) & ~7)), dim3(q.threads), kz_lds_bytes(q.p), st,

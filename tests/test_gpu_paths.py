@@ -211,6 +211,29 @@ def test_contexts_taking_turns_on_one_workspace(N):
     torch.cuda.synchronize()
 
 
+def test_constraints_on_a_shared_workspace():
+    """The same for the constraints: k_z filter (x and z in one pass and apart),
+    depth filter and eigen-solve form all they read in the call."""
+    print("constraints on a shared workspace", flush=True)
+    rng = np.random.default_rng(67)
+    sizes = ((6, 96, 90), (24, 100, 640))
+    ws = torch.empty(max(engine(*s, 64, 3)._ws_bytes for s in sizes) + 256, dtype=torch.uint8, device="cuda:0")
+    kw = dict(rz_sigma=0.8, phase_positive=True, probe_orthogonal=True, kz_beta=0.8, kz_alpha=0.5, kz_dz=5.0)
+    runs = []
+    for S, H, W in sizes:
+        f = [rng.uniform(0.5, 1.5, (S, H, W)).astype(np.float32) for _ in range(2)]
+        f.append((rng.standard_normal((3, 64, 64)) + 1j * rng.standard_normal((3, 64, 64))).astype(np.complex64))
+        own, out = engine(S, H, W, 64, 3), [T(x) for x in f]
+        own.constrain(*out, **kw)
+        runs.append((f, out, on_workspace(engine(S, H, W, 64, 3), ws)))
+    for f, out, eng in 2 * runs:
+        ws.fill_(0xFF)
+        got = [T(x) for x in f]
+        eng.constrain(*got, **kw)
+        assert all(torch.equal(a, b) for a, b in zip(got, out))
+    torch.cuda.synchronize()
+
+
 @pytest.mark.parametrize("B", [2, 36])
 def test_conv_net_gradient_is_the_mean_of_its_halves(B):
     """Weight gradients over fewer tiles than workgroups and (36 samples of 8
