@@ -533,14 +533,14 @@ struct KzPass {
     const float2 *twa, *twb;   // exp(-2 pi i k / A), exp(-2 pi i k / B)
     int use_a, use_b;          // entries of them the stages need
     int wgroup, W;             // weight: slice = t / tpg (wgroup), row length of the table
-    float kz_step;             // 1 / (S dz)
+    double sdz;                // S dz
     int S;
 };
 
 template <int R, int SG, int F>
 __device__ __forceinline__ void kz_stage(const KzPass& p, int i, float2* t, const float2* twl, float2* z, float* amp,
-                                         float* phase, const float2* wtab, size_t base, int tile, int cnt_a,
-                                         int cnt_b) {
+                                         float* phase, const float2* wtab, float kz, size_t base, int tile,
+                                         int cnt_a, int cnt_b) {
     const KzStage s = p.st[i];
     const int m = s.n / R, id = threadIdx.x;
     int line, j;
@@ -587,12 +587,12 @@ __device__ __forceinline__ void kz_stage(const KzPass& p, int i, float2* t, cons
         kz_dft<R, SG>(v);
         if (p.wgroup && i == p.nfwd - 1) {
             // W_a(k) / (S H W) of element (k_z, k_y, k_x): (1 - (2 / pi) atan(A k_z^2)) E
-            const int sl = tile / p.tpg, x0 = (tile % p.tpg) * (int)p.gt;
-            const float kz = (float)(sl < (p.S + 1) / 2 ? sl : sl - p.S) * p.kz_step, kz2 = kz * kz;
+            // (A k_z first: k_z^2 alone may overflow)
+            const int x0 = (tile % p.tpg) * (int)p.gt;
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const float2 ae = wtab[(size_t)(o0 + r * s.Ns) * p.W + x0 + line];
-                const float wt = (1.0f - 0.63661977236758134308f * atanf(ae.x * kz2)) * ae.y;
+                const float wt = (1.0f - 0.63661977236758134308f * atanf(ae.x * kz * kz)) * ae.y;
                 v[r] = make_float2(v[r].x * wt, v[r].y * wt);
             }
         }
@@ -674,21 +674,23 @@ __global__ __launch_bounds__(KZ_MAX_THREADS, 8) void k_kz_pass(KzPass p, KzWeigh
     else
         for (int k = threadIdx.x; k < p.use_b + p.use_a; k += blockDim.x)
             tw[k] = k < p.use_b ? p.twb[k] : p.twa[k - p.use_b];
+    const int sl = tile / p.tpg;                          // k_z in double, rounded once
+    const float kz = p.wgroup ? (float)((sl < (p.S + 1) / 2 ? sl : sl - p.S) / p.sdz) : 0.f;
     // the first stage needs no twiddles; its closing barrier publishes them
     for (int i = 0; i < p.nst; ++i) {
         auto run = [&](auto sg) {
             constexpr int SG = decltype(sg)::value;
             switch (p.st[i].R) {
-                case 2: kz_stage<2, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
-                case 3: kz_stage<3, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
-                case 4: kz_stage<4, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
-                case 5: kz_stage<5, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
-                case 6: kz_stage<6, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
-                case 8: kz_stage<8, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
-                case 9: kz_stage<9, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
-                case 10: kz_stage<10, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
-                case 15: kz_stage<15, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
-                default: kz_stage<12, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, base, tile, cnt_a, cnt_b); break;
+                case 2: kz_stage<2, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, kz, base, tile, cnt_a, cnt_b); break;
+                case 3: kz_stage<3, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, kz, base, tile, cnt_a, cnt_b); break;
+                case 4: kz_stage<4, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, kz, base, tile, cnt_a, cnt_b); break;
+                case 5: kz_stage<5, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, kz, base, tile, cnt_a, cnt_b); break;
+                case 6: kz_stage<6, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, kz, base, tile, cnt_a, cnt_b); break;
+                case 8: kz_stage<8, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, kz, base, tile, cnt_a, cnt_b); break;
+                case 9: kz_stage<9, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, kz, base, tile, cnt_a, cnt_b); break;
+                case 10: kz_stage<10, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, kz, base, tile, cnt_a, cnt_b); break;
+                case 15: kz_stage<15, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, kz, base, tile, cnt_a, cnt_b); break;
+                default: kz_stage<12, SG, F>(p, i, kz_lds, tw, z, amp, phase, wtab, kz, base, tile, cnt_a, cnt_b); break;
             }
         };
         if (i < p.nfwd) run(std::integral_constant<int, -1>());
@@ -755,7 +757,7 @@ struct KzPlan {
     int threads, in, out;
 };
 inline int kz_plan(int S, int H, int W, const int* rx, int nx, const int* ry, int ny, const int* rz, int nz,
-                   const float2* twx, const float2* twy, const float2* twz, float kz_step, KzPlan* plans) {
+                   const float2* twx, const float2* twy, const float2* twz, double sdz, KzPlan* plans) {
     const size_t HW = (size_t)H * W;
     int np = 0;
     auto finish = [&](KzPass& p, int threads, int in, int out) {
@@ -841,7 +843,7 @@ inline int kz_plan(int S, int H, int W, const int* rx, int nx, const int* ry, in
     y.wgroup = 1;
     y.W = W;
     y.S = S;
-    y.kz_step = kz_step;
+    y.sdz = sdz;
     kz_add_axis(y, 1, H, ry, ny);
     y.nfwd = y.nst;
     kz_add_axis(y, 1, H, ry, ny);

@@ -1863,7 +1863,7 @@ ptyr_status ptyr_constrain(ptyr_ctx* c, float* amp, float* phase, float* probe, 
             float2* wtab = twz + g.S;
             KzPlan plans[5];
             const int np = kz_plan(g.S, g.H, g.W, rad[0], nrad[0], rad[1], nrad[1], rad[2], nrad[2], twx, twy, twz,
-                                   (float)(1.0 / (g.S * (double)cfg->kz_dz)), plans);
+                                   g.S * (double)cfg->kz_dz, plans);
             for (int i = 0; i < np; ++i) {
                 const KzPlan& q = plans[i];
                 KzWeight kw{0, g.S, g.H, g.W, (double)cfg->kz_beta, (double)cfg->kz_alpha, g.dx, twx};

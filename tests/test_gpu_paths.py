@@ -176,6 +176,22 @@ def test_object_gradient_256_adds_modes_in_order(B):
         assert torch.equal(one[1][k], eight[1][k]), k
 
 
+def test_kz_filter_of_a_tiny_spacing():
+    """A spacing so small that k_z^2 alone overflows float32 while the weight's
+    beta^2 k_z^2 / (k_r^2 + 1e-3) stays below 1e-5: the filter leaves the object
+    as it is."""
+    print("kz filter, tiny spacing", flush=True)
+    rng = np.random.default_rng(71)
+    f = [rng.uniform(0.5, 1.5, (6, 64, 72)).astype(np.float32) for _ in range(2)]
+    eng = engine(6, 64, 72)
+    got = [T(x) for x in f]
+    eng.constrain(*got, kz_beta=1e-25, kz_dz=1e-21)
+    eng.sync()
+    for g, x in zip(got, f):
+        ref = oc.kz_filter(x, 1e-25, 0.0, 0.2, 1e-21)
+        assert np.linalg.norm(g.cpu().numpy() - ref) <= 1e-5 * np.linalg.norm(ref)
+
+
 def on_workspace(eng, ws):
     """The engine's context bound to `ws` instead of its own workspace."""
     lib, ctx = eng.lib, C.c_void_p()
