@@ -26,9 +26,12 @@ constexpr int LOSS_BLOCKS = 256;
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// workgroups (partial sums) of layer l's weight gradient for B samples
+// workgroups (partial sums) of layer l's weight gradient for B samples: one
+// per tile up to WPARTS, then as many as keep every float32 sum within
+// WPIXELS pixels at any batch (from 257 samples on in layer 0, 1025 in others)
 template <int L> int wgrad_parts(int B) {
-    return (int)std::min<long>((long)B * WGrad<L>::TPS, WPARTS);
+    const long tiles = (long)B * WGrad<L>::TPS, most = WGrad<L>::TMAX;
+    return (int)std::max(std::min(tiles, (long)WPARTS), (tiles + most - 1) / most);
 }
 
 // workspace offsets for batches of up to B neighbourhoods

@@ -56,7 +56,8 @@ constexpr int NPARAM = b_off(NLAYER - 1) + COUTP[NLAYER - 1];
 constexpr int wt_size(int l) { return CINP[l] * kd(l); }
 constexpr int wt_off(int l) { return l == 0 ? 0 : wt_off(l - 1) + wt_size(l - 1); }
 constexpr int WT_TOTAL = wt_off(NLAYER - 1) + wt_size(NLAYER - 1);
-constexpr int WPARTS = 256;                    // weight-gradient partial sums per layer, at most
+constexpr int WPARTS = 256;                    // weight-gradient partial sums per layer while batches are small
+constexpr int WPIXELS = 2048;                  // pixels that one float32 accumulator of them adds, at most
 constexpr int ERR_INDEX = 1;
 
 // per-sample element counts of the stored BF16 tensors
@@ -233,6 +234,7 @@ template <int L> struct WGrad {
     static constexpr int ACC = 4 * 64 * (TPW * MT * 4 + MT) * 4;              // the second half's sums
     static constexpr int LDS = GB + XB > ACC ? GB + XB : ACC;
     static constexpr int TPS = hout / TR;                       // tiles per sample
+    static constexpr int TMAX = 2 * WPIXELS / PX;               // tiles per workgroup at most (its halves share them)
     static constexpr int NGI = PX * coutp / 8, NXI = XR * hin * cinp / 8;      // 16-byte pieces
     static constexpr int NG = (NGI + 511) / 512, NX = (NXI + 511) / 512;
 };

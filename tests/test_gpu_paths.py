@@ -273,6 +273,29 @@ def test_conv_net_gradient_is_the_mean_of_its_halves(B):
     assert float(torch.linalg.norm(whole - halves)) <= 1e-5 * float(torch.linalg.norm(halves))
 
 
+def test_conv_net_sums_of_a_large_batch():
+    """A float32 sum of the weight gradient takes at most 2048 pixels whatever
+    the batch (4096 samples here): one sample is off by 16 and the others by
+    2^-14, whose output gradients, 2^-18 of the first's, vanish in a sum that
+    holds the first sample, and so must share it with three other samples at
+    most.  The last bias's gradient is the sum of the output gradients, known
+    exactly; the later adding of the parts is exact for these values."""
+    B = 4096
+    print(f"conv net sums B={B}", flush=True)
+    _, vec, pats, nbr, _ = make_case(4, 40, 73)
+    net, V, P = cnn.ConvInit(B), T(vec), T(pats)
+    n = T(np.tile(nbr, (B // 4, 1)))
+    out = net.forward(V, P, n)
+    off = torch.full((B, 1, 1), 2.0 ** -14, device=out.device)
+    off[0] = 16.0
+    grad = torch.zeros(cnn.param_count(), dtype=torch.float32, device=out.device)
+    net.gradient(V, P, n, out - off, grad)
+    net.sync()
+    got = cnn.unpack_params(grad.cpu().numpy())[4][1][0]
+    want = 1024 * (16.0 + (B - 1) * 2.0 ** -14) * 2 / (B * 1024)
+    assert abs(got - want) <= 2.0 ** -16 * want
+
+
 @pytest.mark.parametrize("P,H,W", [(0, 40, 33), (1, 32, 32), (70, 100, 90)])
 def test_stitch_tiles(P, H, W):
     """Patches over image edges, more than 64 of them, ragged tiles; the sum
