@@ -354,12 +354,14 @@ __global__ __launch_bounds__(256) void k256_grad_col(Pass256 P) {
 // groups over more units.  The sum stays in probe-mode order, the same bits whatever HV and NL:
 // half 1 hands its product over in LDS and half 0 adds the two, its own first,
 // one barrier later (two buffers, so one barrier per pair of chains).
+// The x ramp that slice 0's wave still lacks is read through LDS: with its
+// global addresses the loop took 256 registers and 40 bytes of scratch.
 template <int HV, int NL>
 __global__ __launch_bounds__(16 * NL * HV, 2) void k256_grad_row(Pass256 P) {
     constexpr int T = 16 * NL, NBLK = N256 / NL;
     __shared__ float2 lds[HV * NL * RowGeo256::SL / 2];
     __shared__ float4 tw[N256];
-    __shared__ float2 hand[HV == 2 ? 2 * 16 * T : 1];
+    __shared__ float2 hand[HV == 2 ? 2 * 16 * T : 1], ramp[N256];
     const WaveArgs& a = P.a;
     const int mg = P.mg, grp = a.chain0 / mg + blockIdx.x / NBLK, blk = blockIdx.x % NBLK;
     const int ch0 = grp * mg, j = ch0 / a.M;
@@ -367,7 +369,10 @@ __global__ __launch_bounds__(16 * NL * HV, 2) void k256_grad_row(Pass256 P) {
     if (pi.ty < 0) return;
     const int half = threadIdx.x / T, t = threadIdx.x % T;
     const int ll = threadIdx.x / 16, c = threadIdx.x % 16, y = blk * NL + ll % NL;   // ll: LDS line
-    for (int i = threadIdx.x; i < N256; i += HV * T) tw[i] = P.tw[i];
+    for (int i = threadIdx.x; i < N256; i += HV * T) {
+        tw[i] = P.tw[i];
+        if (P.s == 0) ramp[i] = P.tab[j].r[1][i];
+    }
     __syncthreads();
     float2 v[16], ph[16], ov[16], acc[16];
     if (half < mg) {
@@ -389,7 +394,7 @@ __global__ __launch_bounds__(16 * NL * HV, 2) void k256_grad_row(Pass256 P) {
         if (HV == 1 || p < mg) {                                           // exchanges are within a wave: no barriers
             if (P.s == 0) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) ph[r] = cmul(ph[r], P.tab[j].r[1][c + 16 * r]);
+                for (int r = 0; r < 16; ++r) ph[r] = cmul(ph[r], ramp[c + 16 * r]);
             }
             mid2nat<RowGeo256, +1>(ph, lds, tw, ll, c);                    // phi_s (space)
             mid2nat<RowGeo256, +1>(v, lds, tw, ll, c);                     // G_chi_s (space)
