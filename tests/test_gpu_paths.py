@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from oracle import constraints as oc
+from oracle.adam import adam_step
 from paper_2505_07814_amd import _lib as L
 from paper_2505_07814_amd import cnn, synth
 from paper_2505_07814_amd.ptyr import AdamState, Engine
@@ -177,6 +178,40 @@ def test_gradient_256_groups_of_two_object_modes(B, two):
     c = ModeCase(256, 2, 8, B, seed=83, H=290, W=300)
     for k, e in _grad_errors(c, c.engine()).items():
         assert e < (1e-6 if k == "loss" else 1e-4), (k, e)
+
+
+@pytest.mark.parametrize("which", ["one term", "all terms"])
+def test_step_with_the_scatter_beside_the_reductions(which):
+    """A one-stream N = 128 step whose object scatter moves enough to run on the
+    side stream beside the probe's and parameters' reductions and Adam: the
+    gradients of ptyr_adjoint followed by Adam in float64, over two steps (the
+    second starts after the join)."""
+    S, M, B = 7, 4, 40
+    H, W = 180, 190
+    assert B * M <= _units() and B * M * S * 128 * 128 * 8 + S * H * W * 48 >= 128e6
+    print(f"step N=128 S={S} M={M} B={B}, {which}", flush=True)
+    c = Case(synth.small_case(N=128, S=S, M=M, B=B, H=H, W=W, seed=89))
+    lr = dict(amp=1e-3, phase=2e-3, probe=1e-2, pos=1e-2, tilt=1e-4, dz=1e-1)
+    kw = dict(w_gaussian=0.7, w_poisson=0.4, pacbed_w=0.5, sparse_w=0.1) if which == "all terms" else {}
+    eng, ref_eng = c.engine(n_scan=B, **kw), c.engine(**kw)
+    st, meas = AdamState(*c.gpu_args()), T(c.meas)
+    b1, b2, eps = (float(np.float32(x)) for x in (0.9, 0.999, 1e-8))
+    real = lambda x: np.ravel(x.cpu().numpy()).view(np.float32).astype(np.float64)
+    for t in range(2):
+        idx = T(np.roll(np.arange(B, dtype=np.int32), t))
+        before = [getattr(st, k).clone() for k in st.NAMES]
+        m0, v0 = ({k: x[k].clone() for k in st.NAMES} for x in (st.m, st.v))
+        loss = eng.step(st, idx, meas, lr).clone()
+        ref_loss, g = ref_eng.adjoint(*before, meas, idx=idx)
+        eng.sync()
+        ref_eng.sync()
+        assert torch.equal(loss, ref_loss)
+        for k, old in zip(st.NAMES, before):
+            p0 = real(old)
+            want, _, _ = adam_step(p0, real(g[k]), real(m0[k]), real(v0[k]), t, lr[k], beta1=b1, beta2=b2, eps=eps)
+            # the float32 parameter is the reference update rounded, to 2 ulp, and the update to float32 arithmetic
+            tol = 2 * np.spacing(np.abs(want).astype(np.float32)) + 1e-5 * np.abs(want - p0)
+            assert np.all(np.abs(real(getattr(st, k)) - want) <= tol), (t, k)
 
 
 @pytest.mark.parametrize("B", [1, 2, 16, 32])
