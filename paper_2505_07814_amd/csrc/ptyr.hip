@@ -271,62 +271,7 @@ __global__ __launch_bounds__(256) void k_loss_partial(const float* Im, const flo
     block_partials<NLP>(v, part);
 }
 
-// pass 2: fixed-order totals, loss and the gradient scales.  Per term t
-//   Gaussian: L_t = sqrt(D)/Z, dL/dA = (A-E) / (K sqrt(D) Z)
-//   Poisson : L_t = -mean(E log(A+eps) - A)/Z, dL/dA = -(E/(A+eps) - 1)/(K Z)
-// and L = sum_t w_t L_t.  scal[5 + t] = w_t c_t (the batch factor of term t,
-// which the per-pixel dI of term_val is missing); scal[1] = the factor the
-// gradient reductions apply to the weights of k_loss_rows (w_0 c_0, or 1
-// when two terms are folded into the weights by k_loss_mix); scal[2] = Z_0.
-__global__ void k_loss_final(const double* part, int nblk, double K, LossTerms lt, int check, double* scal,
-                             double* loss_out, int* err, const double* spart, int nsp, double spw) {
-    // the sparsity term's partial sums ride along as one more column (one
-    // thread adding its B S entries in turn took 27 us at 882 of them)
-    __shared__ double sh[(NLP + 1) * 256];
-    double s[NLP + 1] = {0, 0, 0, 0, 0, 0};
-    for (int b = threadIdx.x; b < nblk; b += 256)
-        for (int k = 0; k < NLP; ++k) s[k] += part[NLP * b + k];
-    for (int b = threadIdx.x; b < nsp; b += 256) s[NLP] += spart[b];
-    for (int k = 0; k <= NLP; ++k) sh[k * 256 + threadIdx.x] = s[k];
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o)
-            for (int k = 0; k <= NLP; ++k) sh[k * 256 + threadIdx.x] += sh[k * 256 + threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        const double bad = sh[4 * 256];
-        double L = 0.0, c[2] = {0.0, 0.0}, Z0 = 0.0;
-        bool zero_mean = false;
-        for (int t = 0; t < lt.n; ++t) {
-            const double sE = sh[(2 * t) * 256], sR = sh[(2 * t + 1) * 256];
-            const double Z = sE / K;
-            if (t == 0) Z0 = Z;
-            if (!(Z > 0.0)) { zero_mean = true; continue; }
-            if (lt.k[t] == PTYR_LOSS_GAUSSIAN) {
-                const double D = sR / K;
-                L += lt.w[t] * sqrt(D) / Z;
-                c[t] = D > 0.0 ? lt.w[t] / (K * sqrt(D) * Z) : 0.0;
-            } else {
-                L += lt.w[t] * (-(sR / K) / Z);
-                c[t] = lt.w[t] / (K * Z);
-            }
-        }
-        if (zero_mean) {
-            atomicOr(err, ERR_ZERO_MEAN);
-            L = 0.0; c[0] = c[1] = 0.0;
-        }
-        if (nsp > 0) L += spw * sh[NLP * 256];         // + sparsity term
-        if (check && (bad > 0.0 || !isfinite(L))) atomicOr(err, ERR_NONFINITE);
-        scal[0] = L;
-        scal[1] = lt.n > 1 ? 1.0 : c[0];
-        scal[2] = Z0;
-        scal[5] = c[0];
-        scal[6] = c[1];
-        if (loss_out) *loss_out = L;
-    }
-}
-
+// pass 2 of the loss (loss.hpp) on its own
 __global__ __launch_bounds__(256) void k_loss_final(LossFinalArgs a) {
     __shared__ double sh[LOSS_FINAL_LDS];
     loss_final_block(a, sh);
