@@ -746,7 +746,8 @@ __global__ __launch_bounds__(256) void k_reduce(const float2* src, float2* dst, 
 // All parameter blocks of a step in one launch: segment k covers elements
 // [off[k], off[k+1]) of the concatenated index range.  Each gradient entry
 // is cleared once read, so the step's gradient buffers start the next step
-// at zero; a segment with upd = 0 (learning rate 0) is only cleared.
+// at zero.  A frozen parameter (learning rate 0) has an empty segment: its
+// gradient is not formed, so its buffer stays zero.
 constexpr int ADAM_SEGS = 6;
 struct AdamSegs {
     float* p[ADAM_SEGS];
@@ -755,7 +756,6 @@ struct AdamSegs {
     float* v[ADAM_SEGS];
     size_t off[ADAM_SEGS + 1];
     float lr[ADAM_SEGS];
-    int upd[ADAM_SEGS];
 };
 // the Adam constants of one step beside the segments
 struct SegAdam {
@@ -772,7 +772,6 @@ __global__ void k_adam_segs(AdamSegs a, float b1, float b2, float eps, float bc1
         const size_t e = i - a.off[k];
         const float gi = a.g[k][e];
         a.g[k][e] = 0.f;
-        if (!a.upd[k]) continue;
         adam_elem(a.p[k][e], a.m[k][e], a.v[k][e], gi, a.lr[k], b1, b2, eps, bc1, bc2s);
     }
 }
@@ -1918,7 +1917,6 @@ ptyr_status ptyr_step(ptyr_ctx* c, ptyr_params* p, const int* idx, int B, const 
             A.m[k] = mv[k][0];
             A.v[k] = mv[k][1];
             A.lr[k] = rates[k];
-            A.upd[k] = on ? 1 : 0;
             A.off[k + 1] = A.off[k] + (on ? sizes[k] : 0);
         }
         sa.b1 = lr->beta1;
