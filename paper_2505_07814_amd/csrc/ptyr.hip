@@ -1163,7 +1163,7 @@ WaveArgs wave_args(ptyr_ctx* c, const float* tilt, const float* dz, int B) {
 }
 
 // the fused kernels over chains [c0, c0 + nc) (chain = row * M + mode) on stream st
-// WIDE (N = 64, every wave kept): see wide_chains.
+// WIDE (N = 64, every wave kept): see wide_forward.
 template <int N, bool WIDE = false> void launch_forward(ptyr_ctx* c, WaveArgs a, int c0, int nc, hipStream_t st) {
     TimedLaunch t(c, PTYR_K_FORWARD, st, true);
     a.chain0 = c0;
@@ -1247,16 +1247,22 @@ void gradient256(ptyr_ctx* c, WaveArgs a, int c0, int nc, hipStream_t st) {
         hipLaunchKernelGGL(grad_col, grid, blk, 0, st, pass256(c, a, s));
     }
 }
-// N = 64 with at most two chains per compute unit: the fused kernels run with
-// their twiddles in registers, without the fences that bound N = 128's
-// register use, and the gradient reads a slice ahead (WIDE: one workgroup per
-// compute unit in the gradient, 288 registers).  Measured, step of 12 slices:
-// 400 chains 494 -> 469 us, 480 chains 524 -> 494 us; 24 slices, 16 chains
-// 425 -> 393 us; but 1200 chains of 6 slices 626 -> 695 us, where three
-// narrow workgroups per compute unit hide each other's latencies.
-bool wide_chains(const ptyr_ctx* c, const WaveArgs& a) { return a.B * a.M <= 2 * c->n_cu; }
+// N = 64 with few chains: the fused kernels run with their twiddles in
+// registers, without the fences that bound N = 128's register use, and the
+// gradient reads a slice ahead (WIDE).  The wide gradient holds 280 registers,
+// one workgroup per compute unit where three narrow ones hide each other's
+// latencies, so it takes batches of at most one chain per unit: steps (narrow
+// / wide) of 24 slices 240 chains 553 / 535 us, 12 slices 144 chains 292 / 282
+// and 256 chains 355 / 350; gradient calls of 24 slices 200 chains 630 / 612,
+// but 264 chains 724 / 860 and 12 slices 480 chains 566 / 632 (some two-stream
+// steps gain up to two chains per unit, 480 chains 535 / 515, others lose, 300
+// chains 470 / 488).  The wide forward takes 165 registers, as many workgroups
+// as the narrow one, and two chains per unit: 12 slices 400 chains 129 / 127,
+// 260 chains 125.7 / 124.6.
+bool wide_forward(const ptyr_ctx* c, const WaveArgs& a) { return a.B * a.M <= 2 * c->n_cu; }
+bool wide_gradient(const ptyr_ctx* c, const WaveArgs& a) { return a.B * a.M <= c->n_cu; }
 void forward_chains(ptyr_ctx* c, const WaveArgs& a, int c0, int nc, hipStream_t st) {
-    if (c->g.N == 64 && wide_chains(c, a)) launch_forward<64, true>(c, a, c0, nc, st);
+    if (c->g.N == 64 && wide_forward(c, a)) launch_forward<64, true>(c, a, c0, nc, st);
     else if (c->g.N == 64) launch_forward<64>(c, a, c0, nc, st);
     else if (c->g.N == 128) launch_forward<128>(c, a, c0, nc, st);
     else forward256(c, a, c0, nc, st);
@@ -1264,7 +1270,7 @@ void forward_chains(ptyr_ctx* c, const WaveArgs& a, int c0, int nc, hipStream_t 
 // lf: N = 64 and 128 only
 void gradient_chains(ptyr_ctx* c, const WaveArgs& a, int c0, int nc, hipStream_t st,
                      const LossFinalArgs* lf = nullptr) {
-    if (c->g.N == 64 && wide_chains(c, a)) launch_gradient<64, true>(c, a, c0, nc, st, lf);
+    if (c->g.N == 64 && wide_gradient(c, a)) launch_gradient<64, true>(c, a, c0, nc, st, lf);
     else if (c->g.N == 64) launch_gradient<64>(c, a, c0, nc, st, lf);
     else if (c->g.N == 128) launch_gradient<128>(c, a, c0, nc, st, lf);
     else gradient256(c, a, c0, nc, st);

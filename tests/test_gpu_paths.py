@@ -37,6 +37,22 @@ def test_gradient_by_chains_per_compute_unit(B, M, budget):
     _check_grads(c, c.engine(wave_budget=budget))
 
 
+def test_gradient_between_one_and_two_chains_per_compute_unit():
+    """N = 64: the forward with its twiddles in registers followed by the
+    gradient without (one to two chains per compute unit), in one call and
+    reusing the forward's waves."""
+    B, M = 60, 5
+    assert _units() < B * M <= 2 * _units()
+    print(f"gradient N=64 S=3 B={B} M={M}", flush=True)
+    c = Case(synth.small_case(N=64, S=3, M=M, B=B, H=110, W=121, seed=97))
+    eng = c.engine()
+    whole = _check_grads(c, eng)
+    eng.forward(*c.gpu_args())
+    reused = _check_grads(c, eng, reuse=True)
+    # (the object's sums run over two ranges of rows in the first, over one in the second)
+    assert all(torch.equal(whole[k], reused[k]) for k in ("probe", "pos", "tilt", "dz"))
+
+
 @pytest.mark.parametrize("S,H,W,M", [(5, 64, 66, 2), (5, 65, 67, 7), (17, 64, 66, 24), (33, 64, 64, 3)])
 def test_orthogonalisation_beside_the_depth_filter(S, H, W, M):
     """The eigen-solve inside the depth filter's launch (both filter kernels),
