@@ -1234,11 +1234,13 @@ void gradient256(ptyr_ctx* c, WaveArgs a, int c0, int nc, hipStream_t st) {
     // multiples of it: N = 256 batches are not split)
     const int mg = row_group(c->g), groups = nc / mg;
     // Two halves and 4 lines per workgroup (k256_grad_row) where one half and
-    // 16 lines give less than two workgroups per compute unit.  Step times,
-    // one half / two: 8 modes, 16 positions, 30 slices (256 workgroups of 16
-    // lines) 5684 / 5341 us, 20 positions, 6 slices (320) 1475 / 1458; from
-    // 512 on (8 modes, 32 positions, 4 slices) 1491 / 1542.
-    const bool two = mg > 1 && groups * NBLK256 < 2 * c->n_cu;
+    // 16 lines give at most one workgroup per compute unit.  Step times, one
+    // half / two, 8 slices: 16 positions (256 workgroups) of 2, 3 and 5 modes
+    // 676 / 660, 808 / 789 and 1138 / 1089 us, 8 positions of 2 modes 567 / 537;
+    // 20 positions (320) of 4, 5 and 7 modes 1145 / 1135, 1347 / 1360 and 1701 /
+    // 1703; 24 (384) of 2, 5 and 8 modes 810 / 835, 1486 / 1530 and 2123 / 2142;
+    // 8 modes, 16 positions, 30 slices 5684 / 5341.
+    const bool two = mg > 1 && groups * NBLK256 <= c->n_cu;
     for (int s = a.S - 1; s >= 0; --s) {
         Pass256 P = pass256(c, a, s);
         P.mg = mg;

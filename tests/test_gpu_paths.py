@@ -178,9 +178,9 @@ def _units():
 @pytest.mark.parametrize("S,M,B,two", [(12, 8, 2, True), (2, 8, 32, False)])
 def test_gradient_256_groups_deep_and_in_one_half(S, M, B, two):
     """N = 256 row pass: a deep stack (every gradient, dz among them) with two
-    halves per workgroup, and groups of 8 modes taken by one half, which it is
-    from two workgroups of 16 lines per compute unit on."""
-    assert (B * 16 < 2 * _units()) == two
+    halves per workgroup, and groups of 8 modes taken by one half, as they are
+    from more than one workgroup of 16 lines per compute unit on."""
+    assert (B * 16 <= _units()) == two
     print(f"gradient N=256 S={S} M={M} B={B} halves={1 + two}", flush=True)
     c = Case(synth.small_case(N=256, S=S, M=M, B=B, H=290, W=300, seed=79))
     _check_grads(c, c.engine())
@@ -189,7 +189,7 @@ def test_gradient_256_groups_deep_and_in_one_half(S, M, B, two):
 @pytest.mark.parametrize("B,two", [(3, True), (16, False)])
 def test_gradient_256_groups_of_two_object_modes(B, two):
     """Groups of probe modes stay within their object mode."""
-    assert (2 * B * 16 < 2 * _units()) == two
+    assert (2 * B * 16 <= _units()) == two
     print(f"gradient N=256 S=2 M=8 n_obj=2 B={B} halves={1 + two}", flush=True)
     c = ModeCase(256, 2, 8, B, seed=83, H=290, W=300)
     for k, e in _grad_errors(c, c.engine()).items():
