@@ -382,8 +382,9 @@ __global__ void k_clip_negative(float* v, size_t n) {
 // writes its results there.  At most 64 registers, for two 1024-thread
 // workgroups per compute unit: with one (80 registers, five passes, four
 // stages of at most radix 8, tiles staged through LDS at both ends) every
-// barrier left the unit idle and a 12 x 640 x 640 call took 235 us; now 104 us
-// (31 + 46 + 30 us, 79 MB each).
+// barrier left the unit idle and a 12 x 640 x 640 call took 235 us; now 103 us
+// (32 + 45 + 31 us; 82, 120 and 79 MB, of which the middle pass's 40 MB over
+// its fields are the weight table, read once per k_z).
 
 constexpr int KZ_MAX_THREADS = 1024;
 constexpr int KZ_MAX_SIDE = 4096;

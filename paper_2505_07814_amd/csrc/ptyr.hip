@@ -1672,8 +1672,12 @@ ptyr_status run_adjoint(ptyr_ctx* c, const float* amp, const float* phase, const
         // or a few workgroups long each (about 40 us at N = 128).  Where the
         // object scatter of a step is at least as long (some 3 TB/s over the
         // patch gradients and the object's Adam) it runs beside them on the
-        // other stream: 12 modes, 6 slices, 270 MB: step 439 -> 423 us.  The
-        // fork and join cost about 10 us, which the shorter reductions at
+        // other stream.  Steps in a row / beside: 134 MB (12 modes, 6 slices,
+        // 13 rows, 200 x 200) 446 / 439 us, 160 MB (one mode, 8 slices, 120
+        // rows, 300 x 300) 534 / 504, 270 MB (12 modes, 6 slices, 16 rows, 640 x
+        // 640) 448 / 436; no more than 0.3 % lost where the object is most of
+        // the bytes (252 MB: one mode, 12 slices, 10 rows, 640 x 640, 599 / 600).
+        // The fork and join cost about 10 us, which the shorter reductions at
         // N = 64 do not repay (395 -> 402 us), and at N = 256 the scatter
         // fills the memory either way (5450 -> 5474 us).
         const size_t scatter_bytes = ((size_t)BM * g.S * g.N * g.N * 8) + (size_t)obj_modes(g) * g.S * g.H * g.W * 48;
